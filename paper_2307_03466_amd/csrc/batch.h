@@ -181,6 +181,8 @@ struct scylla_batch {
     // FP64 data
     DevMem c64, corig64, l64, u64, b64, dr64, dc64;
     DevMem st, info;
+    DevMem norm_part;       // partial sums of the norms
+    int32_t norm_slots = 1; // most pieces of an instance's norms
     DevMem ax;              // running A x of the row pass (adaptive steps)
     DevMem ibnd;            // [2 * count] (l, u) shared by all columns of an
                             // instance, NaN where they differ
@@ -280,7 +282,12 @@ int validate_params(const scylla_params *p);
 int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scylla_result *results,
                      const int64_t *k_limits = nullptr, int32_t q0 = 0, int32_t q1 = -1);
 void ensure_q(scylla_batch *h);
-void cast_q(scylla_batch *h);
+// Path-precision copies of the objective / Hessian entries [lo, hi).
+void cast_c(scylla_batch *h, int32_t lo, int32_t hi);
+void cast_q(scylla_batch *h, int32_t lo, int32_t hi);
+// Norms and cold-start weights of the instances [q0, q1) for their current
+// objective (rows: and right-hand side).
+void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows = false);
 
 // ---- defined in fixprop_dev.hip
 // Batched fix-and-propagate of every wanted instance on the device.

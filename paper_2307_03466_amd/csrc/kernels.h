@@ -190,8 +190,23 @@ void launch_start_check(const double *x, int n, const double *y, int m, int *fla
 void launch_scale_reduce(const MatView &M, int fmt, int rows, const double *drow, const double *dcol,
                          double *out, int mode, hipStream_t s);
 void launch_scale_apply(double *d, const double *r, int len, hipStream_t s);
-void launch_inst_norms(const InstInfo *info, int count, const double *b, const double *c,
-                       const double *dr, const double *dc, InstState *st, hipStream_t s);
+// Norms of the instances [q0, q1) after their objective (and, with rows set,
+// their right-hand side) was written; part holds 4 doubles per instance and
+// slot, slots = the most pieces of any instance of the handle.
+constexpr int NORM_CHUNK = 8192, NORM_MAX_BLOCKS = 256;
+__host__ __device__ inline int norm_blocks(int m, int n)
+{
+    const int64_t nb = ((int64_t)m + n + NORM_CHUNK - 1) / NORM_CHUNK;
+    return nb < 1 ? 1 : (nb > NORM_MAX_BLOCKS ? NORM_MAX_BLOCKS : (int)nb);
+}
+struct NormArgs {
+    const InstInfo *info;
+    const double *b, *c, *dr, *dc;
+    InstState *st;
+    double *part;
+    int32_t slots, q0, rows;
+};
+void launch_norms(const NormArgs &a, int q1, hipStream_t s);
 template <class V>
 void launch_finish_diag(const double *d, V *d2, int len, hipStream_t s);
 template <class V>

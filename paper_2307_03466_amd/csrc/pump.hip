@@ -95,10 +95,8 @@ void reset_objective(scylla_batch *h)
         HIPC(hipMemsetAsync(h->qv.p, 0, h->qv.bytes, h->stream));
     }
     HIPC(hipMemcpyAsync(h->c64.p, h->corig64.p, sizeof(double) * h->N, hipMemcpyDeviceToDevice, h->stream));
-    if (h->vbytes == 4) launch_cast<float>(h->c64.as<double>(), h->cv.as<float>(), h->N, h->stream);
-    else launch_cast<double>(h->c64.as<double>(), h->cv.as<double>(), h->N, h->stream);
-    launch_inst_norms(h->info.as<InstInfo>(), h->count, h->b64.as<double>(), h->c64.as<double>(),
-                      h->dr64.as<double>(), h->dc64.as<double>(), h->st.as<InstState>(), h->stream);
+    cast_c(h, 0, h->N);
+    refresh_norms(h, 0, h->count);
     HIPC(hipGetLastError());
 }
 
@@ -425,9 +423,8 @@ int pump_impl(scylla_batch *h, const scylla_params *p, const uint8_t *is_int, co
                                 hipMemcpyHostToDevice, h->stream));
             HIPC(hipMemcpyAsync(h->q64.as<double>() + c0, qhat.data() + c0, sizeof(double) * (c1 - c0),
                                 hipMemcpyHostToDevice, h->stream));
-            if (h->vbytes == 4) launch_cast<float>(h->c64.as<double>() + c0, h->cv.as<float>() + c0, c1 - c0, h->stream);
-            else launch_cast<double>(h->c64.as<double>() + c0, h->cv.as<double>() + c0, c1 - c0, h->stream);
-            cast_q(h);
+            cast_c(h, c0, c1);
+            cast_q(h, c0, c1);
         } else if (g.K < o.rounds && any) {
             const double a = pow(o.alpha, (double)g.K);
             const size_t b0 = boff[g.q0], b1 = boff[g.q1];
@@ -447,8 +444,7 @@ int pump_impl(scylla_batch *h, const scylla_params *p, const uint8_t *is_int, co
             }
         }
         if (g.K < o.rounds && any) {
-            launch_inst_norms(h->info.as<InstInfo>(), h->count, h->b64.as<double>(), h->c64.as<double>(),
-                              h->dr64.as<double>(), h->dc64.as<double>(), h->st.as<InstState>(), h->stream);
+            refresh_norms(h, g.q0, g.q1);
             HIPC(hipGetLastError());
             HIPC(hipStreamSynchronize(h->stream));
         }

@@ -1251,8 +1251,11 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     set_plan(h, h->orow, 0, 8);
     set_plan(h, h->ocol, 0, 8);
     refresh_info(h);
-    launch_inst_norms(h->info.as<InstInfo>(), h->count, h->b64.as<double>(), h->c64.as<double>(),
-                      h->dr64.as<double>(), h->dc64.as<double>(), h->st.as<InstState>(), s);
+    for (int32_t q = 0; q < h->count; ++q)
+        h->norm_slots = std::max(h->norm_slots, norm_blocks(h->row_off[q + 1] - h->row_off[q],
+                                                            h->col_off[q + 1] - h->col_off[q]));
+    if (h->norm_slots > 1) h->norm_part.alloc(32 * (size_t)h->norm_slots * h->count);
+    refresh_norms(h, 0, h->count, true);
     HIPC(hipGetLastError());
     // fused-window eligibility: every instance fits in LDS
     size_t need = 0;
@@ -1503,10 +1506,22 @@ void ensure_q(scylla_batch *h)
     invalidate_graph(h);
 }
 
-void cast_q(scylla_batch *h)
+static void cast_range(scylla_batch *h, const DevMem &src, DevMem &dst, int32_t lo, int32_t hi)
 {
-    if (h->vbytes == 4) launch_cast<float>(h->q64.as<double>(), h->qv.as<float>(), h->N, h->stream);
-    else launch_cast<double>(h->q64.as<double>(), h->qv.as<double>(), h->N, h->stream);
+    const double *s = src.as<double>() + lo;
+    if (h->vbytes == 4) launch_cast<float>(s, dst.as<float>() + lo, hi - lo, h->stream);
+    else launch_cast<double>(s, dst.as<double>() + lo, hi - lo, h->stream);
+}
+
+void cast_c(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->c64, h->cv, lo, hi); }
+void cast_q(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->q64, h->qv, lo, hi); }
+
+void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows)
+{
+    const NormArgs a{h->info.as<InstInfo>(), h->b64.as<double>(), h->c64.as<double>(), h->dr64.as<double>(),
+                     h->dc64.as<double>(), h->st.as<InstState>(), h->norm_part.as<double>(), h->norm_slots, q0,
+                     rows ? 1 : 0};
+    launch_norms(a, q1, h->stream);
 }
 
 }  // namespace scy
@@ -1625,10 +1640,8 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
         for (int32_t j = 0; j < len; ++j)
             if (!isfinite(c_hat[j])) throw_err(-EINVAL, "non-finite objective");
         HIPC(hipMemcpyAsync(h->c64.as<double>() + lo, c_hat, sizeof(double) * len, hipMemcpyHostToDevice, h->stream));
-        if (h->vbytes == 4) launch_cast<float>(h->c64.as<double>(), h->cv.as<float>(), h->N, h->stream);
-        else launch_cast<double>(h->c64.as<double>(), h->cv.as<double>(), h->N, h->stream);
-        launch_inst_norms(h->info.as<InstInfo>(), h->count, h->b64.as<double>(), h->c64.as<double>(),
-                          h->dr64.as<double>(), h->dc64.as<double>(), h->st.as<InstState>(), h->stream);
+        cast_c(h, lo, lo + len);
+        refresh_norms(h, inst, inst + 1);
         HIPC(hipGetLastError());
         HIPC(hipStreamSynchronize(h->stream));
         return 0;
@@ -1651,7 +1664,7 @@ int scylla_batch_set_quadratic(scylla_batch *h, int32_t inst, const double *q)
         } else {
             HIPC(hipMemsetAsync(h->q64.as<double>() + lo, 0, sizeof(double) * len, h->stream));
         }
-        cast_q(h);
+        cast_q(h, lo, lo + len);
         HIPC(hipGetLastError());
         HIPC(hipStreamSynchronize(h->stream));
         return 0;
@@ -1678,8 +1691,7 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         else
             launch_blend<double>(h->corig64.as<double>(), h->bits_tmp.as<uint8_t>(), ib, a, kappa,
                                  h->c64.as<double>(), h->cv.as<double>(), lo, hi, h->stream);
-        launch_inst_norms(h->info.as<InstInfo>(), h->count, h->b64.as<double>(), h->c64.as<double>(),
-                          h->dr64.as<double>(), h->dc64.as<double>(), h->st.as<InstState>(), h->stream);
+        refresh_norms(h, inst, inst + 1);
         HIPC(hipGetLastError());
         HIPC(hipStreamSynchronize(h->stream));
         return 0;

@@ -51,7 +51,7 @@ struct InstState {
     int64_t k;            // iterations done at the last check
     int64_t k_limit;      // iteration limit of this call
     int64_t kr;           // iteration of the last restart
-    int64_t pad2;
+    double bscale;        // ||D_r b||_2 of the instance
     double t, s;          // primal / dual step (eta / omega, eta * omega)
     double omega, eta;
     double tol;
