@@ -197,11 +197,10 @@ struct scylla_batch {
     DevMem mip_isint, mip_rbad, mip_cbad, mip_ok;  // MIP-feasibility check
     // graph
     hipGraphExec_t gexec = nullptr;
-    // window graph over the compacted tile lists, and earlier ones of the
+    // iteration graph over the compacted tile lists, and earlier ones of the
     // same solve (destroyed once the stream has drained)
     hipGraphExec_t cexec = nullptr;
     std::vector<hipGraphExec_t> retired;
-    int64_t graph_tiles = 0;          // tiles of the current graph's iteration launches
     std::vector<InstInfo> hinfo_c;    // instance info with the compacted slot ranges
     void *cstage = nullptr;           // pinned staging of the cut lists
     size_t cstage_bytes = 0;
@@ -210,7 +209,6 @@ struct scylla_batch {
     int32_t lds_max = 65536;  // dynamic LDS bytes a workgroup may use
     bool tiny_ok = false;     // every instance fits the fused window
     size_t tiny_shmem = 0;
-    bool graph_tiny = false;
     bool graph_adapt = false;
     bool graph_avg = false;
     // host copy of the problem (for the pump's rounding on the host)
@@ -226,8 +224,11 @@ struct scylla_batch {
     FPDev fpd;  // batched fix-and-propagate on the device
     // host mirrors
     std::vector<InstInfo> hinfo;
-    InstState *pinned = nullptr;  // 2 * count states
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    // pinned mirror of the states: all of them at the start of a solve, then
+    // each as its instance stops; read once a check has completed
+    InstState *pinned = nullptr;
+    int64_t *limits = nullptr;  // pinned [count]: iteration limits of a solve
+    hipEvent_t ev = nullptr;
     double setup_seconds = 0.0;
 
     ~scylla_batch()
@@ -237,8 +238,8 @@ struct scylla_batch {
         for (hipGraphExec_t g : retired) (void)hipGraphExecDestroy(g);
         if (pinned) (void)hipHostFree(pinned);
         if (cstage) (void)hipHostFree(cstage);
-        for (auto &e : ev)
-            if (e) (void)hipEventDestroy(e);
+        if (limits) (void)hipHostFree(limits);
+        if (ev) (void)hipEventDestroy(ev);
         if (cap) (void)hipStreamDestroy(cap);
         if (side) (void)hipStreamDestroy(side);
         if (fork) (void)hipEventDestroy(fork);

@@ -135,6 +135,7 @@ struct TinyArgs {
     V *xp, *yp;           // point of the previous check
     double *axp, *atyp;   // its products A x, A^T y
     InstState *st;
+    InstState *mirror;    // pinned host copy, written when an instance stops
     const InstInfo *info;
     int32_t adapt;  // adaptive step sizes
 };
@@ -149,10 +150,12 @@ inline size_t tiny_lds_bytes(int m, int n, int rnnz, int cnnz, int vb)
 }
 
 template <class V>
-void launch_tiny(const TinyArgs<V> &a, int fmt, int count, int R, size_t shmem, hipStream_t s, bool prepare);
+void launch_tiny(const TinyArgs<V> &a, int fmt, int count, int R, int nwin, size_t shmem, hipStream_t s,
+                 bool prepare);
 
 struct DecideArgs {
     InstState *st;
+    InstState *mirror;  // pinned host copy, written when an instance stops
     const InstInfo *info;
     const double *rpart, *lrpart, *cpart, *lcpart;
     int32_t R;
@@ -182,6 +185,23 @@ void launch_direct(const PassArgs<V> &p, int fmt, int dir, int k, int jw, size_t
 // to the sliced plan's combine tiles, slice count and partials.
 template <class V>
 void launch_combine(const PassArgs<V> &p, int dir, int jw, hipStream_t s);
+// Start of a solve: state of every instance from the parameters (limits:
+// per-instance iteration limits or null; <= 0 takes no part), start points of
+// the columns [clo, chi) and rows [rlo, rhi) zeroed (cold) and projected.
+template <class V>
+struct BeginArgs {
+    InstState *st, *mirror;
+    const int64_t *limits;
+    V *x, *y;
+    const V *l, *u;
+    const uint8_t *sense;
+    int64_t iter_limit;
+    double eta, tol, infeas_tol, stall_tol;
+    int32_t count, clo, chi, rlo, rhi;
+    int32_t warm, restarts, avg, stall_checks;
+};
+template <class V>
+void launch_begin(const BeginArgs<V> &a, hipStream_t s);
 void launch_decide(const DecideArgs &d, int count, hipStream_t s);
 void launch_force_stop(InstState *st, int count, hipStream_t s);
 // flag |= 1 if x[0, n) holds a NaN, |= 2 if y[0, m) holds a non-finite value

@@ -1189,6 +1189,7 @@ __global__ __launch_bounds__(256) void k_decide(const DecideArgs d)
     }
     if (threadIdx.x != 0) return;
     decide_state(S, tot, d.rpart2 ? tot2 : nullptr, d.R);
+    if (S.status != ST_RUN) d.mirror[inst] = S;
 }
 
 // ------------------------------------------------------- adaptive steps
@@ -1252,12 +1253,14 @@ __global__ __launch_bounds__(STEP_NT) void k_step(const StepArgs a)
 }
 
 // --------------------------------------------- fused window (tiny instances)
-// One workgroup per instance runs a whole check window -- FP64 KKT check,
+// One workgroup per instance runs up to nwin check windows -- FP64 KKT check,
 // decision, then up to R iterations -- with the instance's matrix (both
 // orientations, decoded to local index + value) and vectors held in LDS and
 // workgroup barriers between the passes.  Used when every instance of the
 // handle fits in LDS; it removes the per-pass launch latency that dominates
-// such instances.  No workgroup ever waits for another.
+// such instances, and with many windows a launch also the reload of the
+// instance and the host's turn per window.  No workgroup ever waits for
+// another.
 template <class V>
 struct TinyLds {
     int *rptr, *cptr, *rcol, *ccol;
@@ -1300,7 +1303,7 @@ __device__ __forceinline__ TinyLds<V> tiny_carve(unsigned char *base, int m, int
 }
 
 template <class V, int FMT>
-__global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R)
+__global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R, const int nwin)
 {
     constexpr int NT = 1024;
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1353,6 +1356,8 @@ __global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R)
         L.sense[i] = a.sense[g];
     }
     __syncthreads();
+    int win = 0;
+    for (; win < nwin; ++win) {
     // ---- FP64 KKT check of the current point (Section 2.2)
     double acc[NTOT] = {};
     for (int i = tid; i < m; i += NT) {
@@ -1433,13 +1438,14 @@ __global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R)
     if (tid == 0) {
         decide_state(S, tot, nullptr, R);
         sh_nrun = S.status == ST_RUN ? S.nrun : 0;
+        if (S.status != ST_RUN) a.mirror[inst] = S;
         sh_restart = S.restart_now;
         sh_t = (V)S.t;
         sh_s = (V)S.s;
     }
     __syncthreads();
     const int nrun = sh_nrun;
-    if (nrun == 0) return;
+    if (nrun == 0) break;
     V t = sh_t, sd = sh_s;
     // lane groups: a power of two of lanes per column / row, as many as fit
     const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
@@ -1505,6 +1511,8 @@ __global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R)
             sd = sh_s;
         }
     }
+    }
+    if (win == 0) return;
     // ---- write the iterates back
     for (int j = tid; j < n; j += NT) {
         const int g = I.col0 + j;
@@ -1520,12 +1528,13 @@ __global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R)
 }
 
 template <class V>
-void launch_tiny(const TinyArgs<V> &a, int fmt, int count, int R, size_t shmem, hipStream_t s, bool prepare)
+void launch_tiny(const TinyArgs<V> &a, int fmt, int count, int R, int nwin, size_t shmem, hipStream_t s,
+                 bool prepare)
 {
     auto run = [&](auto fn) {
         if (prepare) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)shmem);
-        else hipLaunchKernelGGL(fn, dim3(count), dim3(1024), shmem, s, a, R);
+        else hipLaunchKernelGGL(fn, dim3(count), dim3(1024), shmem, s, a, R, nwin);
     };
     if constexpr (sizeof(V) == 8) {
         run(k_tiny<V, FMT_F64>);
@@ -1712,6 +1721,77 @@ __global__ void k_project_primal(V *x, const V *l, const V *u, int lo, int hi, i
     v = v < l[j] ? l[j] : v;
     v = v > u[j] ? u[j] : v;
     x[j] = v;
+}
+
+// Start of a solve in one launch: thread q sets instance q's state (and its
+// host mirror), and the threads of the start ranges project the start points
+// (zeroed first on a cold start).  States set on the host cost two copies
+// and two waits before the first window, ~60 us a solve.
+template <class V>
+__global__ __launch_bounds__(256) void k_begin(const BeginArgs<V> a)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < a.chi - a.clo) {
+        const int j = a.clo + i;
+        V v = a.warm ? a.x[j] : (V)0;
+        v = v < a.l[j] ? a.l[j] : v;
+        v = v > a.u[j] ? a.u[j] : v;
+        a.x[j] = v;
+    }
+    if (i < a.rhi - a.rlo) {
+        const int r = a.rlo + i;
+        V v = a.warm ? a.y[r] : (V)0;
+        const uint8_t sn = a.sense[r];
+        if (sn == 'G') v = v > (V)0 ? v : (V)0;
+        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
+        a.y[r] = v;
+    }
+    if (i >= a.count) return;
+    InstState &S = a.st[i];
+    int64_t lim = a.iter_limit;
+    if (a.limits) {
+        const int64_t own = a.limits[i];
+        if (own <= 0) {  // takes no part
+            if (S.status == ST_RUN) S.status = ST_ITER;
+            a.mirror[i] = S;
+            return;
+        }
+        if (own < lim) lim = own;
+    }
+    const double omega = (a.warm && S.omega > 0.0) ? S.omega : S.omega0;
+    S.status = ST_RUN;
+    S.nrun = 0;
+    S.restarts = 0;
+    S.restart_now = 0;
+    S.restart_on = a.restarts;
+    S.avg_on = a.avg;
+    S.take_avg = 0;
+    S.force_stop = 0;
+    S.k = 0;
+    S.k_limit = lim;
+    S.kr = 0;
+    S.omega = omega;
+    S.eta = a.eta;
+    S.t = a.eta / omega;
+    S.s = a.eta * omega;
+    S.tol = a.tol;
+    S.infeas_tol = a.infeas_tol;
+    S.stall_tol = a.stall_tol;
+    S.stall_checks = a.stall_checks;
+    S.nstall = 0;
+    S.pprev = S.dprev = 0.0;
+    S.Er = S.Ep = 0.0;
+    S.rel = S.rho_p = S.rho_d = S.rho_g = S.pobj = S.dobj = 0.0;
+    a.mirror[i] = S;
+}
+
+template <class V>
+void launch_begin(const BeginArgs<V> &a, hipStream_t s)
+{
+    int len = a.count;
+    if (a.chi - a.clo > len) len = a.chi - a.clo;
+    if (a.rhi - a.rlo > len) len = a.rhi - a.rlo;
+    hipLaunchKernelGGL(k_begin<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, a);
 }
 
 // flag |= 1 if some x[j] is NaN, |= 2 if some y[i] is not finite (a warm
@@ -2147,7 +2227,7 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
 }
 
 #define SCY_INST(V)                                                                                    \
-    template void launch_tiny<V>(const TinyArgs<V> &, int, int, int, size_t, hipStream_t, bool);       \
+    template void launch_tiny<V>(const TinyArgs<V> &, int, int, int, int, size_t, hipStream_t, bool);  \
     template void launch_staged<V>(const PassArgs<V> &, int, int, int, int, size_t, hipStream_t, bool); \
     template void launch_pass<V>(const PassArgs<V> &, int, int, int, int, bool, bool, hipStream_t);    \
     template void launch_combine<V>(const PassArgs<V> &, int, int, hipStream_t);                       \
@@ -2155,6 +2235,7 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
     template void launch_finish_diag<V>(const double *, V *, int, hipStream_t);                        \
     template void launch_take_avg<V>(InstState *, const InstInfo *, V *, V *, const V *, const V *,      \
                                      double *, const double *, int, hipStream_t);                       \
+    template void launch_begin<V>(const BeginArgs<V> &, hipStream_t);                                  \
     template void launch_cast<V>(const double *, V *, int, hipStream_t);                               \
     template void launch_project<V>(V *, const V *, const V *, int, int, V *, const uint8_t *, int, int, \
                                     int, hipStream_t);                                                 \

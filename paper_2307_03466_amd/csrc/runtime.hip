@@ -1,7 +1,7 @@
 // Solver runtime and C ABI of the PDHG library: device-resident batches of
 // LPs, device-side preconditioning, tile plans and their autotuner, hipGraph
-// capture of one check window (KKT check + decision + R iterations), and
-// the host loop that launches windows and polls one status copy per window.
+// capture of the iterations between two checks, and the host loop that
+// launches checks and iterations and reads the states that a check stopped.
 // The pump loop of Algorithm 1 is in pump.hip.
 #include "batch.h"
 
@@ -516,6 +516,7 @@ TinyArgs<V> tiny_args(scylla_batch *h)
     a.dr64 = h->dr64.as<double>();
     a.dc64 = h->dc64.as<double>();
     a.st = h->st.as<InstState>();
+    a.mirror = h->pinned;
     a.info = h->info.as<InstInfo>();
     a.adapt = h->adaptive ? 1 : 0;
     a.xp = h->xp.as<V>();
@@ -529,17 +530,15 @@ TinyArgs<V> tiny_args(scylla_batch *h)
     return a;
 }
 
+// KKT check and decision of every running instance (with restarts to the
+// average: of the running average too).
 template <class V>
-void enqueue_window(scylla_batch *h, int32_t R, bool tiny, hipStream_t s)
+void enqueue_check(scylla_batch *h, int32_t R, hipStream_t s)
 {
-    if (tiny) {
-        launch_tiny<V>(tiny_args<V>(h), h->fmt, h->count, R, h->tiny_shmem, s, false);
-        return;
-    }
     const PassArgs<V> rc = orient_args<V>(h, h->orow, true), cc = orient_args<V>(h, h->ocol, true);
     launch_orient<V>(h, h->orow, rc, 0, true, s);
     launch_orient<V>(h, h->ocol, cc, 0, true, s);
-    DecideArgs d{h->st.as<InstState>(), h->info.as<InstInfo>(), h->orow.part.as<double>(),
+    DecideArgs d{h->st.as<InstState>(), h->pinned, h->info.as<InstInfo>(), h->orow.part.as<double>(),
                  h->orow.lpart.as<double>(), h->ocol.part.as<double>(), h->ocol.lpart.as<double>(), R};
     if (h->avg_on) {
         // the same check of the running average (x_avg, y_avg), into its own
@@ -570,8 +569,14 @@ void enqueue_window(scylla_batch *h, int32_t R, bool tiny, hipStream_t s)
         launch_take_avg<V>(h->st.as<InstState>(), h->info.as<InstInfo>(), h->x.as<V>(), h->y.as<V>(),
                            h->xavg.as<V>(), h->yavg.as<V>(), h->adaptive ? h->ax.as<double>() : nullptr,
                            h->adaptive ? h->axavg.as<double>() : nullptr, h->count, s);
+}
+
+// The first n iterations after a check.
+template <class V>
+void enqueue_iters(scylla_batch *h, int32_t n, hipStream_t s)
+{
     const PassArgs<V> ri = orient_args<V>(h, h->orow, false), ci = orient_args<V>(h, h->ocol, false);
-    for (int32_t j = 0; j < R; ++j) {
+    for (int32_t j = 0; j < n; ++j) {
         launch_orient<V>(h, h->ocol, ci, j, false, s);
         launch_orient<V>(h, h->orow, ri, j, false, s);
         if (h->adaptive) {
@@ -582,15 +587,14 @@ void enqueue_window(scylla_batch *h, int32_t R, bool tiny, hipStream_t s)
     }
 }
 
-// Captures and instantiates one check window of R iterations with the
-// current tile lists.
-hipGraphExec_t capture_window(scylla_batch *h, int32_t R, bool tiny)
+// Captures and instantiates R iterations with the current tile lists.
+hipGraphExec_t capture_iters(scylla_batch *h, int32_t R)
 {
     hipGraph_t g = nullptr;
     hipGraphExec_t ex = nullptr;
     HIPC(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-    if (h->vbytes == 4) enqueue_window<float>(h, R, tiny, h->cap);
-    else enqueue_window<double>(h, R, tiny, h->cap);
+    if (h->vbytes == 4) enqueue_iters<float>(h, R, h->cap);
+    else enqueue_iters<double>(h, R, h->cap);
     HIPC(hipStreamEndCapture(h->cap, &g));
     hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
@@ -598,24 +602,23 @@ hipGraphExec_t capture_window(scylla_batch *h, int32_t R, bool tiny)
     return ex;
 }
 
-void ensure_graph(scylla_batch *h, int32_t R, bool tiny)
+void ensure_graph(scylla_batch *h, int32_t R)
 {
-    if (h->gexec && h->graph_R == R && h->graph_tiny == tiny && h->graph_adapt == h->adaptive &&
-        h->graph_avg == h->avg_on)
-        return;
+    if (h->gexec && h->graph_R == R && h->graph_adapt == h->adaptive && h->graph_avg == h->avg_on) return;
     invalidate_graph(h);
-    if (h->avg_on && !tiny) {
-        // partials of the running average's check (allocated before capture)
-        for (OrientRT *o : {&h->orow, &h->ocol}) {
-            if (o->part2.bytes < o->part.bytes) o->part2.alloc(o->part.bytes);
-            if (o->lpart2.bytes < o->lpart.bytes) o->lpart2.alloc(o->lpart.bytes);
-        }
-    }
-    h->gexec = capture_window(h, R, tiny);
+    h->gexec = capture_iters(h, R);
     h->graph_R = R;
-    h->graph_tiny = tiny;
     h->graph_adapt = h->adaptive;
     h->graph_avg = h->avg_on;
+}
+
+// Partials of the running average's check.
+void ensure_avg_parts(scylla_batch *h)
+{
+    for (OrientRT *o : {&h->orow, &h->ocol}) {
+        if (o->part2.bytes < o->part.bytes) o->part2.alloc(o->part.bytes);
+        if (o->lpart2.bytes < o->lpart.bytes) o->lpart2.alloc(o->lpart.bytes);
+    }
 }
 
 // ---- finished instances out of the iteration launches
@@ -623,11 +626,11 @@ void ensure_graph(scylla_batch *h, int32_t R, bool tiny)
 // A finished instance's workgroups still start, read their tile and the
 // instance state, and exit; late in a batched solve that costs more than
 // the running instances' work.  When the tiles of the running instances
-// fall to half of those the window graph launches, the tile lists of the
+// fall to half of those the iteration graph launches, the tile lists of the
 // iteration launches are cut to the running instances (in their order, so
 // every result is unchanged bit for bit), the adaptive-step slot ranges are
-// renumbered to match, and a window graph over the cut lists takes over.
-// The copies are ordered on the stream behind the windows in flight; an
+// renumbered to match, and an iteration graph over the cut lists takes over.
+// The copies are ordered on the stream behind the window in flight; an
 // instance that stops never runs again within a solve, so lists cut from an
 // earlier state hold every tile that can still run.  The check launches
 // keep the full lists (once per window).  Gather-blocked orientations (one
@@ -1269,7 +1272,7 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     h->tiny_shmem = need;
     if (h->tiny_ok) {
         TinyArgs<V> a{};
-        launch_tiny<V>(a, h->fmt, h->count, 1, need, s, true);
+        launch_tiny<V>(a, h->fmt, h->count, 1, 1, need, s, true);
     }
     HIPC(hipStreamSynchronize(s));
 }
@@ -1325,6 +1328,47 @@ void project_range(scylla_batch *h, int32_t q0, int32_t q1, int zero)
                       h->sense.as<uint8_t>(), h->row_off[q0], h->row_off[q1], zero, h->stream);
 }
 
+// States of a solve from its parameters, start points of instances [q0, q1).
+template <class V>
+void begin_solve(scylla_batch *h, const scylla_params *p, int32_t warm, const int64_t *limits, int32_t q0, int32_t q1)
+{
+    BeginArgs<V> a{};
+    a.st = h->st.as<InstState>();
+    a.mirror = h->pinned;
+    a.limits = limits;
+    a.x = h->x.as<V>();
+    a.y = h->y.as<V>();
+    a.l = h->lv.as<V>();
+    a.u = h->uv.as<V>();
+    a.sense = h->sense.as<uint8_t>();
+    a.iter_limit = p->iter_limit;
+    a.eta = p->eta;
+    a.tol = p->tol;
+    a.infeas_tol = p->infeas_tol;
+    a.stall_tol = p->stall_tol;
+    a.count = h->count;
+    if (q1 > q0) {
+        a.clo = h->col_off[q0];
+        a.chi = h->col_off[q1];
+        a.rlo = h->row_off[q0];
+        a.rhi = h->row_off[q1];
+    }
+    a.warm = warm ? 1 : 0;
+    a.restarts = p->restarts ? 1 : 0;
+    a.avg = p->restart_avg ? 1 : 0;
+    a.stall_checks = p->stall_checks;
+    launch_begin<V>(a, h->stream);
+}
+
+// nwin check windows of the fused form (check, decision, iterations).
+void launch_windows_tiny(scylla_batch *h, int32_t R, int32_t nwin)
+{
+    if (h->vbytes == 4)
+        launch_tiny<float>(tiny_args<float>(h), h->fmt, h->count, R, nwin, h->tiny_shmem, h->stream, false);
+    else
+        launch_tiny<double>(tiny_args<double>(h), h->fmt, h->count, R, nwin, h->tiny_shmem, h->stream, false);
+}
+
 void read_states(scylla_batch *h, std::vector<InstState> &out)
 {
     out.resize(h->count);
@@ -1375,46 +1419,33 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
         else autotune<double>(h);
         tune_s = now_s() - tt;
     }
-    std::vector<InstState> st;
-    read_states(h, st);
-    for (int32_t q = 0; q < h->count; ++q) {
-        InstState &S = st[q];
-        if (k_limits && k_limits[q] <= 0) {
-            if (S.status == ST_RUN) S.status = ST_ITER;
-            continue;
+    // the largest iteration limit: the check that reaches it stops everything
+    int64_t lim = k_limits ? 0 : p->iter_limit;
+    if (k_limits) {
+        if (!h->limits)
+            HIPC(hipHostMalloc((void **)&h->limits, sizeof(int64_t) * (size_t)h->count, hipHostMallocCoherent));
+        for (int32_t q = 0; q < h->count; ++q) {
+            h->limits[q] = k_limits[q];
+            lim = std::max(lim, std::min(k_limits[q], p->iter_limit));
         }
-        const double omega = (warm && S.omega > 0.0) ? S.omega : S.omega0;
-        S.status = ST_RUN;
-        S.nrun = 0;
-        S.restarts = 0;
-        S.restart_now = 0;
-        S.restart_on = p->restarts ? 1 : 0;
-        S.avg_on = p->restart_avg ? 1 : 0;
-        S.take_avg = 0;
-        S.force_stop = 0;
-        S.k = 0;
-        S.k_limit = k_limits ? std::min<int64_t>(k_limits[q], p->iter_limit) : p->iter_limit;
-        S.kr = 0;
-        S.omega = omega;
-        S.eta = p->eta;
-        S.t = p->eta / omega;
-        S.s = p->eta * omega;
-        S.tol = p->tol;
-        S.infeas_tol = p->infeas_tol;
-        S.stall_tol = p->stall_tol;
-        S.stall_checks = p->stall_checks;
-        S.nstall = 0;
-        S.pprev = S.dprev = 0.0;
-        S.Er = S.Ep = 0.0;
-        S.rel = S.rho_p = S.rho_d = S.rho_g = S.pobj = S.dobj = 0.0;
     }
-    if (q1 > q0) {
-        if (h->vbytes == 4) project_range<float>(h, q0, q1, warm ? 0 : 1);
-        else project_range<double>(h, q0, q1, warm ? 0 : 1);
-    }
-    HIPC(hipMemcpyAsync(h->st.p, st.data(), sizeof(InstState) * h->count, hipMemcpyHostToDevice, h->stream));
-    HIPC(hipStreamSynchronize(h->stream));
-    ensure_graph(h, p->check_period, tiny);
+    if (h->vbytes == 4) begin_solve<float>(h, p, warm, k_limits ? h->limits : nullptr, q0, q1);
+    else begin_solve<double>(h, p, warm, k_limits ? h->limits : nullptr, q0, q1);
+    const double t0 = now_s();
+    const int32_t R = p->check_period;
+    auto running = [&](int32_t q) { return h->pinned[q].status == ST_RUN; };
+    auto any_running = [&]() {
+        for (int32_t q = 0; q < h->count; ++q)
+            if (running(q)) return true;
+        return false;
+    };
+    bool forced = false;
+    auto watch_time = [&]() {
+        if (forced || p->time_limit_s <= 0.0 || now_s() - t0 <= p->time_limit_s) return;
+        launch_force_stop(h->st.as<InstState>(), h->count, h->stream);
+        HIPC(hipGetLastError());
+        forced = true;
+    };
 
     // cutting finished instances out of the iteration launches (results
     // unchanged); the full lists come back when the solve ends
@@ -1425,17 +1456,16 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
     const bool can_cut = p->compact != 0 && !tiny && (iter_tiles(h->orow, nullptr) + iter_tiles(h->ocol, nullptr)) > 0;
     const bool cut_trace = getenv("SCYLLA_CUT_TRACE") != nullptr;
     std::vector<uint8_t> run(h->count, 0);
-    int64_t graph_tiles = 0, cut_after = -1, next = 0;
+    int64_t graph_tiles = 0;
     auto maybe_cut = [&](int64_t window) {
         const int64_t live = iter_tiles(h->orow, run.data()) + iter_tiles(h->ocol, run.data());
         // at most half the launched tiles still run, and at least 16 fewer
         if (live * 2 > graph_tiles || graph_tiles - live < 16) return;
-        cut_after = next;  // the first window launched over the cut lists
         const double tc = now_s();
         cut_lists(h, run.data());
         if (h->cexec) h->retired.push_back(h->cexec);
         h->cexec = nullptr;
-        h->cexec = capture_window(h, p->check_period, false);
+        h->cexec = capture_iters(h, R);
         if (cut_trace)
             fprintf(stderr, "cut after window %lld: %lld -> %lld tiles, %.2f ms on the host\n", (long long)window,
                     (long long)graph_tiles, (long long)live, (now_s() - tc) * 1e3);
@@ -1444,49 +1474,67 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
     if (can_cut) {
         prepare_cut(h);
         graph_tiles = iter_tiles(h->orow, nullptr) + iter_tiles(h->ocol, nullptr);
-        for (int32_t q = 0; q < h->count; ++q) run[q] = st[q].status == ST_RUN ? 1 : 0;
+        for (int32_t q = 0; q < h->count; ++q) run[q] = !k_limits || k_limits[q] > 0 ? 1 : 0;
         maybe_cut(-1);  // instances with no iterations in this solve
     }
+    if (h->avg_on && !tiny) ensure_avg_parts(h);
 
-    const size_t sb = sizeof(InstState) * (size_t)h->count;
-    const double t0 = now_s();
-    int64_t insp = 0;
-    bool done = false, forced = false;
-    int64_t last_slot = 0;
-    for (;;) {
-        while (!done && next - insp < 2) {
-            const int slot = (int)(next & 1);
-            HIPC(hipGraphLaunch(h->cexec ? h->cexec : h->gexec, h->stream));
-            HIPC(hipMemcpyAsync(h->pinned + (size_t)slot * h->count, h->st.p, sb, hipMemcpyDeviceToHost, h->stream));
-            HIPC(hipEventRecord(h->ev[slot], h->stream));
-            ++next;
-        }
-        if (insp == next) break;
-        const int slot = (int)(insp & 1);
-        HIPC(hipEventSynchronize(h->ev[slot]));
-        last_slot = slot;
-        ++insp;
-        bool running = false;
-        for (int32_t q = 0; q < h->count; ++q)
-            if (h->pinned[(size_t)slot * h->count + q].status == ST_RUN) running = true;
-        if (!running) {
-            done = true;
-        } else if (!forced && p->time_limit_s > 0.0 && now_s() - t0 > p->time_limit_s) {
-            launch_force_stop(h->st.as<InstState>(), h->count, h->stream);
+    if (tiny) {
+        // As many windows a launch as make 4096 iterations (6-10 ms on a
+        // 200 x 500 set cover): the host's turn between launches then costs
+        // under 1 %, and the GPU is not held for long.  With a time limit one
+        // window, so that it is seen after each.
+        const int64_t per = p->time_limit_s > 0.0 ? 1 : std::max(1, 4096 / R), checks = (lim + R - 1) / R + 1;
+        for (int64_t w = 0; w < checks; w += per) {
+            launch_windows_tiny(h, R, (int32_t)std::min(per, checks - w));
             HIPC(hipGetLastError());
-            forced = true;
-        } else if (can_cut && insp > cut_after) {
-            // the staging of the last cut is free once a window launched
-            // behind its copies has been inspected
-            for (int32_t q = 0; q < h->count; ++q)
-                run[q] = h->pinned[(size_t)slot * h->count + q].status == ST_RUN ? 1 : 0;
-            maybe_cut(insp - 1);
+            HIPC(hipEventRecord(h->ev, h->stream));
+            HIPC(hipEventSynchronize(h->ev));
+            if (!any_running()) break;
+            watch_time();
+        }
+    }
+    // Window w: the check of iteration wR, then the iterations up to the next
+    // check, launched before the check's outcome is known (the device decides
+    // itself; one window of launches is empty when everything stopped).  The
+    // host reads the outcome while they run, so nothing waits, and launches no
+    // iterations behind the check that ends every instance at its limit.  (Two
+    // windows launched ahead of their outcome left 128 of 192 launched
+    // iterations empty in a solve of 64: 2.80 -> 1.82 ms for 32 adaptive FP64
+    // iterations of a 200k x 400k LP, 2.08 -> 1.61 ms for 192 of a 5k x 10k one.)
+    for (int64_t w = 0; !tiny; ++w) {
+        const bool last = w * R >= lim;
+        if (h->vbytes == 4) enqueue_check<float>(h, R, h->stream);
+        else enqueue_check<double>(h, R, h->stream);
+        HIPC(hipGetLastError());
+        HIPC(hipEventRecord(h->ev, h->stream));
+        if (!last) {
+            const int64_t n = std::min<int64_t>(R, lim - w * R);
+            if (2 * n <= R) {
+                // a short last window is not worth a graph of its own, nor
+                // R - n empty iterations
+                if (h->vbytes == 4) enqueue_iters<float>(h, (int32_t)n, h->stream);
+                else enqueue_iters<double>(h, (int32_t)n, h->stream);
+                HIPC(hipGetLastError());
+            } else {
+                if (!h->cexec) ensure_graph(h, R);
+                HIPC(hipGraphLaunch(h->cexec ? h->cexec : h->gexec, h->stream));
+            }
+        }
+        HIPC(hipEventSynchronize(h->ev));
+        if (last || !any_running()) break;
+        watch_time();
+        if (can_cut) {
+            // the copies of the last cut are complete: this check was
+            // launched behind them
+            for (int32_t q = 0; q < h->count; ++q) run[q] = running(q) ? 1 : 0;
+            maybe_cut(w);
         }
     }
     HIPC(hipStreamSynchronize(h->stream));
     const double solve_s = now_s() - t0;
     for (int32_t q = 0; q < h->count; ++q) {
-        fill_result(h->pinned[(size_t)last_slot * h->count + q], results[q], solve_s, h->setup_seconds);
+        fill_result(h->pinned[q], results[q], solve_s, h->setup_seconds);
         results[q].tune_seconds = tune_s;
     }
     return 0;
@@ -1608,9 +1656,8 @@ int scylla_batch_create(const scylla_lp *lps, int32_t count, int32_t precision, 
         HIPC(hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking));
         HIPC(hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
         HIPC(hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
-        HIPC(hipEventCreateWithFlags(&h->ev[0], hipEventDisableTiming));
-        HIPC(hipEventCreateWithFlags(&h->ev[1], hipEventDisableTiming));
-        HIPC(hipHostMalloc((void **)&h->pinned, sizeof(InstState) * 2 * (size_t)count, hipHostMallocDefault));
+        HIPC(hipEventCreateWithFlags(&h->ev, hipEventDisableTiming));
+        HIPC(hipHostMalloc((void **)&h->pinned, sizeof(InstState) * (size_t)count, hipHostMallocCoherent));
         if (h->vbytes == 4) setup_device<float>(h.get(), lps, csr, csc);
         else setup_device<double>(h.get(), lps, csr, csc);
         h->hval.resize(h->NNZ);
