@@ -140,7 +140,10 @@ struct TinyArgs {
     int32_t adapt;  // adaptive step sizes
 };
 
-// LDS bytes k_tiny needs for an instance (must match its carving).
+// Bytes of the zero element at the start of k_tiny's dynamic LDS; with its
+// static LDS at most 1024.
+constexpr int TINY_ZERO = 16;
+// LDS bytes k_tiny needs for an instance beside that (must match its carving).
 inline size_t tiny_lds_bytes(int m, int n, int rnnz, int cnnz, int vb)
 {
     auto al = [](size_t b) { return (b + 15) & ~(size_t)15; };

@@ -51,6 +51,40 @@ __device__ __forceinline__ V wave_sum_width(V v, int width)
     return v;
 }
 
+// v of the lane that CTRL pairs this one with (data-parallel primitives: a
+// register operand modifier, against an LDS round trip for a shuffle).
+template <int CTRL, class V>
+__device__ __forceinline__ V dpp_pair(V v)
+{
+    if constexpr (sizeof(V) == 8) {
+        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+        return __hiloint2double(hi, lo);
+    } else {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+    }
+}
+
+// Sum over aligned groups of `width` lanes (a power of two), in every lane:
+// neighbours, pairs of neighbours, then mirrored halves, whose lanes hold
+// equal partial sums.
+template <class V>
+__device__ __forceinline__ V group_sum(V v, int width)
+{
+    if (width < 2) return v;
+    v += dpp_pair<0xb1>(v);  // quad lanes 1 0 3 2
+    if (width < 4) return v;
+    v += dpp_pair<0x4e>(v);  // quad lanes 2 3 0 1
+    if (width < 8) return v;
+    v += dpp_pair<0x141>(v);  // mirror of 8 lanes
+    if (width < 16) return v;
+    v += dpp_pair<0x140>(v);  // mirror of 16 lanes
+    if (width < 32) return v;
+    v += __shfl_xor(v, 16, 64);
+    if (width < 64) return v;
+    return v + __shfl_xor(v, 32, 64);
+}
+
 // Fixed-order block sum (result valid in thread 0).
 template <class V, int NT>
 __device__ __forceinline__ V block_sum(V v, V *red)
@@ -1264,6 +1298,7 @@ __global__ __launch_bounds__(STEP_NT) void k_step(const StepArgs a)
 template <class V>
 struct TinyLds {
     int *rptr, *cptr, *rcol, *ccol;
+    V *zero;  // element 0 of the dynamic LDS, holds zero
     V *rval, *cval, *x, *xb, *xr, *c, *l, *u, *dc2, *q, *y, *yr, *b, *dr2;
     double *ax;
     uint8_t *sense;
@@ -1279,6 +1314,7 @@ __device__ __forceinline__ TinyLds<V> tiny_carve(unsigned char *base, int m, int
         q += (bytes + 15) & ~(size_t)15;
         return p;
     };
+    t.zero = (V *)take(sizeof(V));
     t.rptr = (int *)take(4 * (size_t)(m + 1));
     t.cptr = (int *)take(4 * (size_t)(n + 1));
     t.rcol = (int *)take(4 * (size_t)rnnz);
@@ -1302,23 +1338,290 @@ __device__ __forceinline__ TinyLds<V> tiny_carve(unsigned char *base, int m, int
     return t;
 }
 
-template <class V, int FMT>
-__global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R, const int nwin)
+// A lane's share of one row (column) of the fused window, in registers: its
+// entries lane, lane + L, ... of the row, at most K, as value and 16-bit
+// element index of what they gather, counted from the start of the dynamic
+// LDS.  Slots beyond the lane's entries gather element 0, which holds zero
+// (so the sums need no masks, and 0 * 0 is added, never 0 * inf).
+template <class V, int K>
+struct LaneRow {
+    uint32_t idx[K / 2];  // two indices a word
+    V val[K];
+    int wcnt;             // the most entries of any lane of the wave
+};
+
+template <class V, int K>
+__device__ __forceinline__ void lane_row_load(LaneRow<V, K> &r, const int *ptr, const int *col, const V *val, int vec0,
+                                              int row, bool on, int lane, int L)
 {
-    constexpr int NT = 1024;
+    const int e0 = on ? ptr[row] + lane : 0, e1 = on ? ptr[row + 1] : 0;
+    int cnt = e0 < e1 ? (e1 - e0 + L - 1) / L : 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool in = k < cnt;
+        const int e = in ? e0 + k * L : 0;  // (element 0 is read in any case)
+        const int j = col[e];
+        const V v = val[e];
+        const uint32_t c = in ? (uint32_t)(vec0 + j) : 0;
+        r.idx[k / 2] = k % 2 ? r.idx[k / 2] | c << 16 : c;
+        r.val[k] = in ? v : (V)0;
+    }
+    for (int off = 32; off > 0; off >>= 1) cnt = max(cnt, __shfl_xor(cnt, off, 64));
+    r.wcnt = __builtin_amdgcn_readfirstlane(cnt);
+}
+
+// sum of val * lds[idx] over the row's lanes; the gathers of four slots go
+// out before the first product waits.
+template <class V, int K>
+__device__ __forceinline__ V lane_row_dot(const LaneRow<V, K> &r, const V *lds, int L)
+{
+    V s = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += 4)
+        if (k0 < r.wcnt) {
+            V g[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) g[k] = lds[(r.idx[(k0 + k) / 2] >> (16 * (k % 2))) & 0xffff];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s += r.val[k0 + k] * g[k];
+        }
+    return group_sum(s, L);
+}
+
+// The decision and the step rule, by one thread, as calls: inlined, their
+// logarithms and powers take the registers that the iterations need.
+__device__ __attribute__((noinline)) void tiny_decide(InstState *S, const double *tot, int R)
+{
+    decide_state(*S, tot, nullptr, R);
+}
+
+__device__ __attribute__((noinline)) void tiny_adapt(InstState *S, double nx, double ny, double inter, int64_t k)
+{
+    adapt_step(*S, nx, ny, inter, k);
+}
+
+constexpr int TINY_NT = 1024;
+// Entries of a row that a lane can hold in registers (of the 128 a thread of
+// a 1024-thread workgroup has, an entry takes 1.5 in FP32 and 2.5 in FP64).
+template <class V>
+constexpr int TINY_K = sizeof(V) == 8 ? 8 : 16;
+
+// Scratch of the fused window in static LDS (its dynamic LDS leaves 1024 B).
+struct TinyShared {
+    InstState S;
+    double red[4 * TINY_NT / 64];
+    double tot[NTOT + 2];
+    int nrun, restart;
+    double t, s;
+};
+
+// Sums of acc over the workgroup into sh.tot, four at a time, waves in order.
+__device__ __forceinline__ void tiny_totals(double (&acc)[NTOT], TinyShared &sh)
+{
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+#pragma unroll
+    for (int k0 = 0; k0 < NTOT; k0 += 4) {
+#pragma unroll
+        for (int k = k0; k < k0 + 4 && k < NTOT; ++k) {
+            const double v = group_sum(acc[k], 64);
+            if (l == 0) sh.red[4 * w + k - k0] = v;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < TINY_NT / 64; ++q) s += sh.red[4 * q + threadIdx.x];
+            sh.tot[k0 + threadIdx.x] = s;
+        }
+        __syncthreads();
+    }
+}
+
+// nrun PDHG iterations (Algorithm 1), column pass, barrier, row pass, with
+// every row and column spread over at most one group of lanes: entries and
+// epilogue operands sit in registers, LDS holds only what is gathered (x_bar
+// and y), so a pass is one round of LDS gathers, a few data-parallel adds and
+// the update.  Bound by LDS latency and gather throughput.  With every operand
+// read from LDS in a chain (pointers, entry, gather, operands) an iteration of
+// a 200 x 500 set cover took 1.5 us in FP64 and 256 of them (FP32, 192
+// iterations) 740 us a solve; now 0.7 us and 430 us.
+template <class V, int K, bool ADAPT>
+__device__ __forceinline__ void tiny_iters_reg(const TinyArgs<V> &a, const TinyLds<V> &L, TinyShared &sh, int tid, int m,
+                                               int n)
+{
+    constexpr int NT = TINY_NT;
+    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
+    const int j = tid / Lc, i = tid / Lr;
+    const bool jon = j < n, ion = i < m;
+    const bool jw = jon && (tid & (Lc - 1)) == 0, iw = ion && (tid & (Lr - 1)) == 0;
+    LaneRow<V, K> C, R;
+    lane_row_load<V, K>(C, L.cptr, L.ccol, L.cval, (int)(L.y - L.zero), j, jon, tid & (Lc - 1), Lc);
+    lane_row_load<V, K>(R, L.rptr, L.rcol, L.rval, (int)(L.xb - L.zero), i, ion, tid & (Lr - 1), Lr);
+    V x = 0, c = 0, lo = 0, hi = 0, dc2 = 0, q = 0, y = 0, b = 0, dr2 = 0;
+    double ax = 0.0;
+    uint8_t sn = 'E';
+    if (jon) {
+        x = L.x[j];
+        c = L.c[j];
+        lo = L.l[j];
+        hi = L.u[j];
+        dc2 = L.dc2[j];
+        q = L.q[j];
+    }
+    if (ion) {
+        y = L.y[i];
+        b = L.b[i];
+        dr2 = L.dr2[i];
+        sn = L.sense[i];
+        ax = L.ax[i];
+    }
+    if (sh.restart) {
+        if (jw) L.xr[j] = x;
+        if (iw) L.yr[i] = y;
+    }
+    const int nrun = sh.nrun;
+    V t = (V)sh.t, sd = (V)sh.s;
+    for (int it = 0; it < nrun; ++it) {
+        double nx = 0.0, ny = 0.0, inter = 0.0;
+        const V aty = lane_row_dot<V, K>(C, L.zero, Lc);
+        V xn = x + t * dc2 * (aty - c);
+        if (a.q) xn /= (V)1 + t * dc2 * q;
+        xn = xn < lo ? lo : xn;
+        xn = xn > hi ? hi : xn;
+        if (jw) L.xb[j] = ADAPT ? xn - x : (V)2 * xn - x;  // adaptive: the move dx
+        if (ADAPT && jw) {
+            const double d = (double)xn - (double)x;
+            nx = d * d / (double)dc2;
+        }
+        x = xn;
+        __syncthreads();
+        const V axb = lane_row_dot<V, K>(R, L.zero, Lr);
+        // adaptive: axb = (A dx)_i and (A x_bar)_i = (A x)_i + 2 (A dx)_i
+        const V res = ADAPT ? (V)((double)b - (ax + 2.0 * (double)axb)) : b - axb;
+        V v = y + sd * dr2 * res;
+        if (sn == 'G') v = v > (V)0 ? v : (V)0;
+        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
+        if (iw) L.y[i] = v;
+        if (ADAPT) {
+            if (iw) {
+                const double dy = (double)v - (double)y;
+                ny = dy * dy / (double)dr2;
+                inter = dy * (double)axb;
+            }
+            ax += (double)axb;
+        }
+        y = v;
+        __syncthreads();
+        if (ADAPT) {
+            double zero = 0.0;
+            block_sum2<NT>(nx, zero, sh.red);
+            block_sum2<NT>(ny, inter, sh.red);
+            if (tid == 0) {
+                tiny_adapt(&sh.S, nx, ny, inter, sh.S.k + it + 1);
+                sh.t = sh.S.t;
+                sh.s = sh.S.s;
+            }
+            __syncthreads();
+            t = (V)sh.t;
+            sd = (V)sh.s;
+        }
+    }
+    if (jw) L.x[j] = x;
+    __syncthreads();
+}
+
+// The same iterations with the matrix read from LDS: more rows or columns
+// than threads, or a row with more entries than its lanes hold.
+template <class V>
+__device__ __forceinline__ void tiny_iters_lds(const TinyArgs<V> &a, const TinyLds<V> &L, TinyShared &sh, int tid, int m,
+                                               int n)
+{
+    constexpr int NT = TINY_NT;
+    const int nrun = sh.nrun;
+    V t = (V)sh.t, sd = (V)sh.s;
+    // lane groups: a power of two of lanes per column / row, as many as fit
+    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
+    const int lc = tid & (Lc - 1), lr = tid & (Lr - 1);
+    for (int it = 0; it < nrun; ++it) {
+        const bool copy_ref = it == 0 && sh.restart != 0;
+        double nx = 0.0, ny = 0.0, inter = 0.0;
+        for (int j = tid / Lc; j < n; j += NT / Lc) {
+            V aty = 0;
+            for (int e = L.cptr[j] + lc; e < L.cptr[j + 1]; e += Lc) aty += L.cval[e] * L.y[L.ccol[e]];
+            if (Lc > 1) aty = group_sum(aty, Lc);
+            if (lc == 0) {
+                const V xj = L.x[j];
+                V xn = xj + t * L.dc2[j] * (aty - L.c[j]);
+                if (a.q) xn /= (V)1 + t * L.dc2[j] * L.q[j];
+                xn = xn < L.l[j] ? L.l[j] : xn;
+                xn = xn > L.u[j] ? L.u[j] : xn;
+                if (copy_ref) L.xr[j] = xj;
+                L.xb[j] = a.adapt ? xn - xj : (V)2 * xn - xj;  // adaptive: the move dx
+                L.x[j] = xn;
+                if (a.adapt) {
+                    const double d = (double)xn - (double)xj;
+                    nx += d * d / (double)L.dc2[j];
+                }
+            }
+        }
+        __syncthreads();
+        for (int i = tid / Lr; i < m; i += NT / Lr) {
+            V axb = 0;
+            for (int e = L.rptr[i] + lr; e < L.rptr[i + 1]; e += Lr) axb += L.rval[e] * L.xb[L.rcol[e]];
+            if (Lr > 1) axb = group_sum(axb, Lr);
+            if (lr == 0) {
+                const V yi = L.y[i];
+                // adaptive: axb = (A dx)_i and (A x_bar)_i = (A x)_i + 2 (A dx)_i
+                const V res = a.adapt ? (V)((double)L.b[i] - (L.ax[i] + 2.0 * (double)axb)) : L.b[i] - axb;
+                V v = yi + sd * L.dr2[i] * res;
+                const uint8_t sn = L.sense[i];
+                if (sn == 'G') v = v > (V)0 ? v : (V)0;
+                else if (sn == 'L') v = v < (V)0 ? v : (V)0;
+                if (copy_ref) L.yr[i] = yi;
+                L.y[i] = v;
+                if (a.adapt) {
+                    const double dy = (double)v - (double)yi;
+                    ny += dy * dy / (double)L.dr2[i];
+                    inter += dy * (double)axb;
+                    L.ax[i] += (double)axb;
+                }
+            }
+        }
+        __syncthreads();
+        if (a.adapt) {
+            double zero = 0.0;
+            block_sum2<NT>(nx, zero, sh.red);
+            block_sum2<NT>(ny, inter, sh.red);
+            if (tid == 0) {
+                tiny_adapt(&sh.S, nx, ny, inter, sh.S.k + it + 1);
+                sh.t = sh.S.t;
+                sh.s = sh.S.s;
+            }
+            __syncthreads();
+            t = (V)sh.t;
+            sd = (V)sh.s;
+        }
+    }
+}
+
+template <class V, int FMT>
+__global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int R, const int nwin)
+{
+    constexpr int NT = TINY_NT, K = TINY_K<V>;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    __shared__ double red[NT / 64];
-    __shared__ double red2[2 * NT / 64];
-    __shared__ int sh_nrun, sh_restart;
-    __shared__ V sh_t, sh_s;
+    __shared__ TinyShared sh;
+    static_assert(sizeof(TinyShared) + TINY_ZERO <= 1024, "static LDS of the fused window");
     const int inst = blockIdx.x, tid = threadIdx.x;
-    InstState &S = a.st[inst];
-    if (S.status != ST_RUN) return;
-    const InstInfo I = a.info[inst];
+    if (a.st[inst].status != ST_RUN) return;
+    const InstInfo &I = a.info[inst];
     const int m = I.row1 - I.row0, n = I.col1 - I.col0;
     const int re0 = a.R.ptr[I.row0], rnnz = a.R.ptr[I.row1] - re0;
     const int ce0 = a.C.ptr[I.col0], cnnz = a.C.ptr[I.col1] - ce0;
     const TinyLds<V> L = tiny_carve<V>(lds_raw, m, n, rnnz, cnnz);
+    if (tid == 0) {
+        sh.S = a.st[inst];
+        *L.zero = (V)0;
+    }
     // ---- load the instance into LDS
     for (int i = tid; i <= m; i += NT) L.rptr[i] = a.R.ptr[I.row0 + i] - re0;
     for (int j = tid; j <= n; j += NT) L.cptr[j] = a.C.ptr[I.col0 + j] - ce0;
@@ -1356,161 +1659,117 @@ __global__ __launch_bounds__(1024) void k_tiny(const TinyArgs<V> a, const int R,
         L.sense[i] = a.sense[g];
     }
     __syncthreads();
+    // lanes per column and row, and whether every lane's share fits registers
+    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
+    bool wide = n > NT || m > NT;
+    if (tid < n) wide |= L.cptr[tid + 1] - L.cptr[tid] > K * Lc;
+    if (tid < m) wide |= L.rptr[tid + 1] - L.rptr[tid] > K * Lr;
+    if (tid == 0) sh.nrun = 0;
+    __syncthreads();
+    if (wide) sh.nrun = 1;
+    __syncthreads();
+    const bool regs = sh.nrun == 0;
     int win = 0;
     for (; win < nwin; ++win) {
-    // ---- FP64 KKT check of the current point (Section 2.2)
-    double acc[NTOT] = {};
-    for (int i = tid; i < m; i += NT) {
-        double ax = 0.0;
-        for (int e = L.rptr[i]; e < L.rptr[i + 1]; ++e) ax += (double)L.rval[e] * (double)L.x[L.rcol[e]];
-        const double bb = a.b64[I.row0 + i];
-        const uint8_t sn = L.sense[i];
-        double r;
-        if (sn == 'G') r = fmax(bb - ax, 0.0);
-        else if (sn == 'L') r = fmax(ax - bb, 0.0);
-        else r = bb - ax;
-        const double yy = (double)L.y[i];
-        const double dy = (yy - (double)L.yr[i]) / a.dr64[I.row0 + i];
-        L.ax[i] = ax;  // A x of the current point in FP64 (adaptive steps)
-        acc[0] += r * r;
-        acc[1] += bb * yy;
-        acc[2] += dy * dy;
-        // moves since the previous check (infeasibility certificates)
-        const int gi = I.row0 + i;
-        const double v = yy - (double)a.yp[gi];
-        const double vp = sn == 'G' ? fmax(v, 0.0) : (sn == 'L' ? fmin(v, 0.0) : v);
-        const double ad = ax - a.axp[gi];
-        const double viol = sn == 'G' ? fmax(-ad, 0.0) : (sn == 'L' ? fmax(ad, 0.0) : ad);
-        acc[7] += bb * v;
-        acc[8] += (v - vp) * (v - vp);
-        acc[9] += viol * viol;
-        a.yp[gi] = L.y[i];
-        a.axp[gi] = ax;
-    }
-    for (int j = tid; j < n; j += NT) {
-        double aty = 0.0;
-        for (int e = L.cptr[j]; e < L.cptr[j + 1]; ++e) aty += (double)L.cval[e] * (double)L.y[L.ccol[e]];
-        const int g = I.col0 + j;
-        const double cc = a.c64[g], lo = a.l64[g], hi = a.u64[g];
-        const double xq = (double)L.x[j];
-        const double qx = a.q64 ? a.q64[g] * xq : 0.0;
-        const double gr = cc + qx - aty;
-        const bool lf = isfinite(lo), uf = isfinite(hi);
-        double lam;
-        if (lf && uf) lam = gr;
-        else if (lf) lam = fmax(gr, 0.0);
-        else if (uf) lam = fmin(gr, 0.0);
-        else lam = 0.0;
-        const double rd = gr - lam;
-        const double dx = (xq - (double)L.xr[j]) / a.dc64[g];
-        acc[3] += rd * rd;
-        acc[4] += cc * xq + 0.5 * qx * xq;
-        if (lf && lam > 0.0) acc[5] += lo * lam;
-        if (uf && lam < 0.0) acc[5] += hi * lam;
-        acc[5] -= 0.5 * qx * xq;
-        acc[6] += dx * dx;
-        const double w = aty - a.atyp[g];
-        double rl;
-        if (lf && uf) rl = -w;
-        else if (lf) rl = fmax(-w, 0.0);
-        else if (uf) rl = fmin(-w, 0.0);
-        else rl = 0.0;
-        acc[10] += (w + rl) * (w + rl);
-        if (lf && rl > 0.0) acc[11] += lo * rl;
-        if (uf && rl < 0.0) acc[11] += hi * rl;
-        const double d = xq - (double)a.xp[g];
-        acc[12] += cc * d;
-        double bv;
-        if (lf && uf) bv = d;
-        else if (lf) bv = fmin(d, 0.0);
-        else if (uf) bv = fmax(d, 0.0);
-        else bv = 0.0;
-        acc[13] += bv * bv;
-        if (a.q64) acc[13] += (a.q64[g] * d) * (a.q64[g] * d);
-        a.xp[g] = L.x[j];
-        a.atyp[g] = aty;
-    }
-    double tot[NTOT];
-    for (int k = 0; k < NTOT; ++k) {
+        // the thread index behind a barrier for the optimiser: addresses made
+        // from it are not kept in registers from window to window (they are
+        // enough to spill)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lc = tid & (Lc - 1), lr = tid & (Lr - 1);
+        // ---- FP64 KKT check of the current point (Section 2.2)
+        double acc[NTOT] = {};
+        for (int i = tid / Lr; i < m; i += NT / Lr) {
+            double ax = 0.0;
+            for (int e = L.rptr[i] + lr; e < L.rptr[i + 1]; e += Lr) ax += (double)L.rval[e] * (double)L.x[L.rcol[e]];
+            ax = group_sum(ax, Lr);
+            if (lr != 0) continue;
+            const double bb = a.b64[I.row0 + i];
+            const uint8_t sn = L.sense[i];
+            double r;
+            if (sn == 'G') r = fmax(bb - ax, 0.0);
+            else if (sn == 'L') r = fmax(ax - bb, 0.0);
+            else r = bb - ax;
+            const double yy = (double)L.y[i];
+            const double dy = (yy - (double)L.yr[i]) / a.dr64[I.row0 + i];
+            L.ax[i] = ax;  // A x of the current point in FP64 (adaptive steps)
+            acc[0] += r * r;
+            acc[1] += bb * yy;
+            acc[2] += dy * dy;
+            // moves since the previous check (infeasibility certificates)
+            const int gi = I.row0 + i;
+            const double v = yy - (double)a.yp[gi];
+            const double vp = sn == 'G' ? fmax(v, 0.0) : (sn == 'L' ? fmin(v, 0.0) : v);
+            const double ad = ax - a.axp[gi];
+            const double viol = sn == 'G' ? fmax(-ad, 0.0) : (sn == 'L' ? fmax(ad, 0.0) : ad);
+            acc[7] += bb * v;
+            acc[8] += (v - vp) * (v - vp);
+            acc[9] += viol * viol;
+            a.yp[gi] = L.y[i];
+            a.axp[gi] = ax;
+        }
+        for (int j = tid / Lc; j < n; j += NT / Lc) {
+            double aty = 0.0;
+            for (int e = L.cptr[j] + lc; e < L.cptr[j + 1]; e += Lc) aty += (double)L.cval[e] * (double)L.y[L.ccol[e]];
+            aty = group_sum(aty, Lc);
+            if (lc != 0) continue;
+            const int g = I.col0 + j;
+            const double cc = a.c64[g], lo = a.l64[g], hi = a.u64[g];
+            const double xq = (double)L.x[j];
+            const double qx = a.q64 ? a.q64[g] * xq : 0.0;
+            const double gr = cc + qx - aty;
+            const bool lf = isfinite(lo), uf = isfinite(hi);
+            double lam;
+            if (lf && uf) lam = gr;
+            else if (lf) lam = fmax(gr, 0.0);
+            else if (uf) lam = fmin(gr, 0.0);
+            else lam = 0.0;
+            const double rd = gr - lam;
+            const double dx = (xq - (double)L.xr[j]) / a.dc64[g];
+            acc[3] += rd * rd;
+            acc[4] += cc * xq + 0.5 * qx * xq;
+            if (lf && lam > 0.0) acc[5] += lo * lam;
+            if (uf && lam < 0.0) acc[5] += hi * lam;
+            acc[5] -= 0.5 * qx * xq;
+            acc[6] += dx * dx;
+            const double w = aty - a.atyp[g];
+            double rl;
+            if (lf && uf) rl = -w;
+            else if (lf) rl = fmax(-w, 0.0);
+            else if (uf) rl = fmin(-w, 0.0);
+            else rl = 0.0;
+            acc[10] += (w + rl) * (w + rl);
+            if (lf && rl > 0.0) acc[11] += lo * rl;
+            if (uf && rl < 0.0) acc[11] += hi * rl;
+            const double d = xq - (double)a.xp[g];
+            acc[12] += cc * d;
+            double bv;
+            if (lf && uf) bv = d;
+            else if (lf) bv = fmin(d, 0.0);
+            else if (uf) bv = fmax(d, 0.0);
+            else bv = 0.0;
+            acc[13] += bv * bv;
+            if (a.q64) acc[13] += (a.q64[g] * d) * (a.q64[g] * d);
+            a.xp[g] = L.x[j];
+            a.atyp[g] = aty;
+        }
+        tiny_totals(acc, sh);
+        if (tid == 0) {
+            tiny_decide(&sh.S, sh.tot, R);
+            sh.nrun = sh.S.status == ST_RUN ? sh.S.nrun : 0;
+            sh.restart = sh.S.restart_now;
+            sh.t = sh.S.t;
+            sh.s = sh.S.s;
+        }
         __syncthreads();
-        tot[k] = block_sum<double, NT>(acc[k], red);
+        if (sh.nrun == 0) break;
+        if (!regs) tiny_iters_lds<V>(a, L, sh, tid, m, n);
+        else if (a.adapt) tiny_iters_reg<V, K, true>(a, L, sh, tid, m, n);
+        else tiny_iters_reg<V, K, false>(a, L, sh, tid, m, n);
     }
     if (tid == 0) {
-        decide_state(S, tot, nullptr, R);
-        sh_nrun = S.status == ST_RUN ? S.nrun : 0;
-        if (S.status != ST_RUN) a.mirror[inst] = S;
-        sh_restart = S.restart_now;
-        sh_t = (V)S.t;
-        sh_s = (V)S.s;
-    }
-    __syncthreads();
-    const int nrun = sh_nrun;
-    if (nrun == 0) break;
-    V t = sh_t, sd = sh_s;
-    // lane groups: a power of two of lanes per column / row, as many as fit
-    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
-    const int lc = tid & (Lc - 1), lr = tid & (Lr - 1);
-    // ---- nrun PDHG iterations (Algorithm 1): column pass, barrier, row pass
-    for (int it = 0; it < nrun; ++it) {
-        const bool copy_ref = it == 0 && sh_restart != 0;
-        double nx = 0.0, ny = 0.0, inter = 0.0;
-        for (int j = tid / Lc; j < n; j += NT / Lc) {
-            V aty = 0;
-            for (int e = L.cptr[j] + lc; e < L.cptr[j + 1]; e += Lc) aty += L.cval[e] * L.y[L.ccol[e]];
-            if (Lc > 1) aty = wave_sum_width(aty, Lc);
-            if (lc == 0) {
-                const V xj = L.x[j];
-                V xn = xj + t * L.dc2[j] * (aty - L.c[j]);
-                if (a.q) xn /= (V)1 + t * L.dc2[j] * L.q[j];
-                xn = xn < L.l[j] ? L.l[j] : xn;
-                xn = xn > L.u[j] ? L.u[j] : xn;
-                if (copy_ref) L.xr[j] = xj;
-                L.xb[j] = a.adapt ? xn - xj : (V)2 * xn - xj;  // adaptive: the move dx
-                L.x[j] = xn;
-                if (a.adapt) {
-                    const double d = (double)xn - (double)xj;
-                    nx += d * d / (double)L.dc2[j];
-                }
-            }
-        }
-        __syncthreads();
-        for (int i = tid / Lr; i < m; i += NT / Lr) {
-            V axb = 0;
-            for (int e = L.rptr[i] + lr; e < L.rptr[i + 1]; e += Lr) axb += L.rval[e] * L.xb[L.rcol[e]];
-            if (Lr > 1) axb = wave_sum_width(axb, Lr);
-            if (lr == 0) {
-                const V yi = L.y[i];
-                // adaptive: axb = (A dx)_i and (A x_bar)_i = (A x)_i + 2 (A dx)_i
-                const V res = a.adapt ? (V)((double)L.b[i] - (L.ax[i] + 2.0 * (double)axb)) : L.b[i] - axb;
-                V v = yi + sd * L.dr2[i] * res;
-                const uint8_t sn = L.sense[i];
-                if (sn == 'G') v = v > (V)0 ? v : (V)0;
-                else if (sn == 'L') v = v < (V)0 ? v : (V)0;
-                if (copy_ref) L.yr[i] = yi;
-                L.y[i] = v;
-                if (a.adapt) {
-                    const double dy = (double)v - (double)yi;
-                    ny += dy * dy / (double)L.dr2[i];
-                    inter += dy * (double)axb;
-                    L.ax[i] += (double)axb;
-                }
-            }
-        }
-        __syncthreads();
-        if (a.adapt) {
-            double zero = 0.0;
-            block_sum2<NT>(nx, zero, red2);
-            block_sum2<NT>(ny, inter, red2);
-            if (tid == 0) {
-                adapt_step(S, nx, ny, inter, S.k + it + 1);
-                sh_t = (V)S.t;
-                sh_s = (V)S.s;
-            }
-            __syncthreads();
-            t = sh_t;
-            sd = sh_s;
-        }
-    }
+        a.st[inst] = sh.S;
+        if (sh.S.status != ST_RUN) a.mirror[inst] = sh.S;
     }
     if (win == 0) return;
     // ---- write the iterates back

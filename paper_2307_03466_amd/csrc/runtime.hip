@@ -1269,6 +1269,7 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
         need = std::max(need, tiny_lds_bytes(m, n, rn, cn, (int)sizeof(V)));
     }
     h->tiny_ok = need + 1024 <= (size_t)h->lds_max;  // room for the kernel's static LDS
+    need += TINY_ZERO;
     h->tiny_shmem = need;
     if (h->tiny_ok) {
         TinyArgs<V> a{};
