@@ -197,6 +197,16 @@ int build_orientations(const scylla_lp *lps, int32_t count, int32_t precision, H
     return 0;
 }
 
+void seal_tiles(const std::vector<int32_t> &ptr, std::vector<int32_t> &tiles)
+{
+    for (size_t i = 0; i + 3 < tiles.size(); i += 4) {
+        if (tiles[i + 3] >= 0) continue;
+        const int32_t r0 = tiles[i], r1 = tiles[i + 1];
+        tiles[i + 1] = (r1 - r0) | ((ptr[r1] - ptr[r0]) << TILE_ROW_BITS);
+        tiles[i + 3] = ~ptr[r0];
+    }
+}
+
 void plan_tiles(const std::vector<int32_t> &ptr, const std::vector<int32_t> &inst_off,
                 int32_t chunk, int32_t max_rows, TilePlan &plan, const uint8_t *skip)
 {

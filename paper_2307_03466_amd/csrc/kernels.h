@@ -23,8 +23,9 @@ struct MatView {
 template <class V>
 struct PassArgs {
     MatView M;
-    const int4 *tiles;
+    const int4 *tiles;    // normal tiles as seal_tiles leaves them
     int32_t ntiles;
+    int32_t early;        // normal tiles: load entries before the state
     const int4 *longs;    // long-row descriptors {row, slot0, nseg, inst}
     int32_t nlong;
     const V *gvec;        // gathered vector: x_bar (row pass), y (column

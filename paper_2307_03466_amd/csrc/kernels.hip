@@ -177,21 +177,25 @@ __device__ __forceinline__ int decode_entry(const MatView &M, uint32_t w, A &a)
     }
 }
 
-// Stage prod[e - e0] = a_e * vec[idx_e] for e in [e0, e1), e1 - e0 <= NT*EPT.
-template <class A, class GV, int FMT, int NT, int EPT>
-__device__ __forceinline__ void stage_products(const MatView &M, const GV *__restrict__ vec, int e0,
-                                               int e1, A *prod)
+// Entries e0 + q NT + tid < e1 of a tile, q < EPT, in registers.
+template <class A, int FMT, int NT, int EPT>
+__device__ __forceinline__ void load_tile(const MatView &M, int e0, int e1, uint32_t (&w)[EPT], A (&a)[EPT])
 {
-    const int tid = threadIdx.x;
-    uint32_t w[EPT];
-    A a[EPT];
 #pragma unroll
     for (int q = 0; q < EPT; ++q) {
-        const int e = e0 + q * NT + tid;
+        const int e = e0 + q * NT + (int)threadIdx.x;
         w[q] = 0;
         a[q] = (A)0;
         if (e < e1) load_entry<FMT, A>(M, e, w[q], a[q]);
     }
+}
+
+// prod[e - e0] = a_e * vec[idx_e] of the loaded entries.
+template <class A, class GV, int FMT, int NT, int EPT>
+__device__ __forceinline__ void tile_products(const MatView &M, const GV *__restrict__ vec, int e0, int e1,
+                                              const uint32_t (&w)[EPT], A (&a)[EPT], A *prod)
+{
+    const int tid = threadIdx.x;
     A g[EPT];
 #pragma unroll
     for (int q = 0; q < EPT; ++q) {
@@ -207,6 +211,17 @@ __device__ __forceinline__ void stage_products(const MatView &M, const GV *__res
         const int e = e0 + q * NT + tid;
         if (e < e1) prod[e - e0] = a[q] * g[q];
     }
+}
+
+// Stage prod[e - e0] = a_e * vec[idx_e] for e in [e0, e1), e1 - e0 <= NT*EPT.
+template <class A, class GV, int FMT, int NT, int EPT>
+__device__ __forceinline__ void stage_products(const MatView &M, const GV *__restrict__ vec, int e0,
+                                               int e1, A *prod)
+{
+    uint32_t w[EPT];
+    A a[EPT];
+    load_tile<A, FMT, NT, EPT>(M, e0, e1, w, a);
+    tile_products<A, GV, FMT, NT, EPT>(M, vec, e0, e1, w, a, prod);
 }
 
 // ------------------------------------------------------------ epilogues
@@ -328,8 +343,20 @@ __device__ __forceinline__ int lanes_per_row(int nrows)
     return L;
 }
 
+// Nonzeros [e0, e1) and, for a tile of whole rows, the rows of a normal tile.
+struct TileRange {
+    int e0, e1, rows;
+};
+
+__device__ __forceinline__ TileRange tile_range(const int4 &T)
+{
+    if (T.w >= 0) return {T.x, T.y, 0};
+    const int e0 = ~T.w;
+    return {e0, e0 + (T.y >> TILE_ROW_BITS), T.y & ((1 << TILE_ROW_BITS) - 1)};
+}
+
 // ------------------------------------------------------- iteration pass
-template <class V, int FMT, int DIR, int NT, int EPT>
+template <class V, int FMT, int DIR, int NT, int EPT, bool EARLY>
 __global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
 {
     constexpr int CH = NT * EPT;
@@ -338,18 +365,31 @@ __global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
     __shared__ double red2[2 * NT / 64];
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     const int4 T = p.tiles[t];
+    // EARLY (one instance): the entries go out before the state is read, so a
+    // workgroup waits for three loads in a row (tile, entries, gather), not
+    // for five (state and row pointers between); with too few workgroups to
+    // cover them they are most of its time (32 adaptive FP64 iterations of a
+    // 200k x 400k LP 1.82 -> 1.61 ms, 64 FP32 ones of a 300k x 600k LP 3.10 ->
+    // 2.96 ms).  Batches read the state first: their stopped instances would
+    // load in vain.
+    const int r0 = T.x;
+    const TileRange R = tile_range(T);
+    uint32_t w[EPT];
+    V a[EPT];
+    if constexpr (EARLY) load_tile<V, FMT, NT, EPT>(p.M, R.e0, R.e1, w, a);
     const InstState &S = p.st[T.z];
     if (S.status != ST_RUN || jw >= S.nrun) return;
+    if constexpr (!EARLY) load_tile<V, FMT, NT, EPT>(p.M, R.e0, R.e1, w, a);
     const bool copy_ref = (jw == 0) && (S.restart_now != 0);
     const V step = DIR == DIR_COL ? (V)S.t : (V)S.s;
     const V acnt = avg_count(p, S, jw);
     const int tid = threadIdx.x;
     const InstBounds<V> ib = inst_bounds<V, DIR>(p, T.z);
     if (T.w >= 0) {  // one segment of a long row: partial sum only
-        stage_products<V, V, FMT, NT, EPT>(p.M, p.gvec, T.x, T.y, prod);
+        tile_products<V, V, FMT, NT, EPT>(p.M, p.gvec, R.e0, R.e1, w, a, prod);
         __syncthreads();
         V s = 0;
-        for (int q = tid; q < T.y - T.x; q += NT) s += prod[q];
+        for (int q = tid; q < R.e1 - R.e0; q += NT) s += prod[q];
         s = block_sum<V, NT>(s, red);
         if (tid == 0) {
             p.seg[T.w] = s;
@@ -358,8 +398,7 @@ __global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
         return;
     }
     double ip[2] = {0.0, 0.0};
-    const int r0 = T.x, nrows = T.y - T.x;
-    const int e0 = p.M.ptr[r0], e1 = p.M.ptr[T.y];
+    const int nrows = R.rows, e0 = R.e0;
     const int L = lanes_per_row<NT>(nrows);
     const int groups = NT / L, lane = tid & (L - 1);
     // first row of this lane group: bounds and epilogue operands up front
@@ -371,7 +410,7 @@ __global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
         re = p.M.ptr[r0 + r + 1] - e0;
         if (lane == 0) load_ops<V, DIR>(p, r0 + r, ops, ib);
     }
-    stage_products<V, V, FMT, NT, EPT>(p.M, p.gvec, e0, e1, prod);
+    tile_products<V, V, FMT, NT, EPT>(p.M, p.gvec, e0, R.e1, w, a, prod);
     __syncthreads();
     for (; r < nrows; r += groups) {
         V s = 0;
@@ -951,14 +990,8 @@ __global__ __launch_bounds__(NT) void k_check(const PassArgs<V> p)
     const int4 T = p.tiles[t];
     const InstState &S = p.st[T.z];
     if (S.status != ST_RUN) return;
-    int e0, e1;
-    if (T.w >= 0) {
-        e0 = T.x;
-        e1 = T.y;
-    } else {
-        e0 = p.M.ptr[T.x];
-        e1 = p.M.ptr[T.y];
-    }
+    const TileRange R = tile_range(T);
+    const int e0 = R.e0, e1 = R.e1;
     // row check gathers x (not x_bar), column check gathers y
     stage_products<double, V, FMT, NT, EPT>(p.M, p.gvec, e0, e1, prod);
     __syncthreads();
@@ -975,7 +1008,7 @@ __global__ __launch_bounds__(NT) void k_check(const PassArgs<V> p)
         }
         return;
     }
-    const int r0 = T.x, nrows = T.y - T.x;
+    const int r0 = T.x, nrows = R.rows;
     int L = 1;
     while (L < 64 && nrows * (L << 1) <= NT) L <<= 1;
     const int groups = NT / L, lane = tid & (L - 1);
@@ -2164,7 +2197,8 @@ __global__ __launch_bounds__(256) void k_mip_reduce(const InstInfo *__restrict__
 template <class V, int FMT, int DIR, int NT, int EPT>
 static void launch_pass_t(const PassArgs<V> &p, int jw, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
+    if (p.early) hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT, true>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
+    else hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT, false>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
 }
 
 template <class V, int FMT, int DIR, int NT, int EPT>

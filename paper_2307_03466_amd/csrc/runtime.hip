@@ -47,6 +47,7 @@ PassArgs<V> orient_args(scylla_batch *h, OrientRT &o, bool check)
     p.P64 = o.P64.as<double>();
     p.ctiles = o.ctiles.as<int4>();
     p.nctiles = o.blocked ? (int32_t)(o.bplan.ctiles.size() / 4) : 0;
+    p.early = h->count == 1 ? 1 : 0;
     p.adapt = h->adaptive ? 1 : 0;
     p.ax = h->ax.as<double>();
     p.own_prev = o.row ? h->yp.as<V>() : h->xp.as<V>();
@@ -171,6 +172,7 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
     } else {
         o.blocked = false;
         plan_tiles(o.host.ptr, off, chunk, 1024, o.plan);
+        seal_tiles(o.host.ptr, o.plan.tiles);
         upload(o.tiles, o.plan.tiles, h->stream);
         upload(o.longs, o.plan.longs, h->stream);
         o.seg.alloc(std::max<size_t>(1, o.plan.nslots) * vb);
@@ -258,6 +260,7 @@ void set_staged(scylla_batch *h, OrientRT &o, int32_t ept, int32_t group_nnz, in
     o.stiles_h = tiles;
     upload(o.subtiles, o.splan.sub.tiles, h->stream);
     upload(o.gofs, gofs, h->stream);
+    seal_tiles(o.host.ptr, o.splan.rest.tiles);
     upload(o.rtiles, o.splan.rest.tiles, h->stream);
     upload(o.rlongs, o.splan.rest.longs, h->stream);
     o.rseg.alloc(std::max<size_t>(1, o.splan.rest.nslots) * h->vbytes);
@@ -294,6 +297,7 @@ void set_direct(scylla_batch *h, OrientRT &o, int32_t ept, int32_t group_nnz, in
     upload(o.dtiles, o.dtiles_h, h->stream);
     plan_tiles(o.host.ptr, off, 256 * std::abs(ept), 1024, o.splan.rest, o.dinst.data());
     upload(o.gofs, gofs, h->stream);
+    seal_tiles(o.host.ptr, o.splan.rest.tiles);
     upload(o.rtiles, o.splan.rest.tiles, h->stream);
     upload(o.rlongs, o.splan.rest.longs, h->stream);
     o.rseg.alloc(std::max<size_t>(1, o.splan.rest.nslots) * h->vbytes);

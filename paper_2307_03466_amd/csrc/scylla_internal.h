@@ -214,6 +214,13 @@ int build_orientations(const scylla_lp *lps, int32_t count, int32_t precision, H
 void plan_tiles(const std::vector<int32_t> &ptr, const std::vector<int32_t> &inst_off,
                 int32_t chunk, int32_t max_rows, TilePlan &plan, const uint8_t *skip = nullptr);
 
+// The device form of normal tiles: a tile of rows {r0, r1, inst, -1} becomes
+// {r0, rows | nonzeros << TILE_ROW_BITS, inst, ~first nonzero}, so that a
+// workgroup knows its nonzeros without reading row pointers; segment tiles
+// stay.  Needs at most 2047 rows and 2^20 nonzeros a tile.
+constexpr int32_t TILE_ROW_BITS = 11;
+void seal_tiles(const std::vector<int32_t> &ptr, std::vector<int32_t> &tiles);
+
 uint16_t f64_to_bf16_exact(double v, bool &exact);
 
 }  // namespace scy
