@@ -173,6 +173,7 @@ struct scylla_batch {
     hipEvent_t fork = nullptr, join = nullptr;
     int32_t M = 0, N = 0;
     int64_t NNZ = 0;
+    int32_t longest = 0;  // most rows or columns of an instance
     std::vector<int32_t> row_off, col_off;
     OrientRT orow, ocol;
     // vectors in the path precision

@@ -106,10 +106,11 @@ struct StepArgs {
 };
 void launch_step(const StepArgs &a, int count, hipStream_t s);
 // Restart to the average: instances whose decision took the average copy it
-// over their iterate (and with adaptive steps its A x over the running one).
+// over their iterate (and with adaptive steps its A x over the running one);
+// longest: the most columns or rows of an instance.
 template <class V>
-void launch_take_avg(InstState *st, const InstInfo *info, V *x, V *y, const V *xa, const V *ya, double *ax,
-                     const double *axa, int count, hipStream_t s);
+void launch_take_avg(const InstState *st, const InstInfo *info, V *x, V *y, const V *xa, const V *ya, double *ax,
+                     const double *axa, int count, int longest, hipStream_t s);
 
 // LDS-staged pass: 1024 threads; variant v: nonzeros per thread per
 // sub-tile 4 (v = 0, 1) or 8 (v = 2, 3); odd v prefetch the next

@@ -127,6 +127,26 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, double *red)
     }
 }
 
+// Fixed-order block sums of N values to out[N] (one thread each); red holds
+// NT / 64 * N doubles.  One barrier, where a block sum per value takes two.
+template <int NT, int N>
+__device__ __forceinline__ void block_sums(const double (&acc)[N], double *red, double *out)
+{
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double v = group_sum(acc[k], 64);
+        if (l == 0) red[N * w + k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < NT / 64; ++q) s += red[N * q + threadIdx.x];
+        out[threadIdx.x] = s;
+    }
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t h)
 {
     return __uint_as_float(((uint32_t)h) << 16);
@@ -484,23 +504,6 @@ __global__ __launch_bounds__(NT) void k_bpart(const PassArgs<V> p, const int jw,
             re = ptr[r0 + rn + 1] - e0;
         }
     }
-}
-
-// Long sub-rows of a blocked orientation: P[b][row] = sum of its segments.
-template <class V, class A>
-__global__ __launch_bounds__(256) void k_bseg(const PassArgs<V> p, const int jw, const int check)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= p.nlong) return;
-    const int4 L = p.longs[q];
-    const int inst = L.w & 0xffffff, b = L.w >> 24;
-    const InstState &S = p.st[inst];
-    if (S.status != ST_RUN || (!check && jw >= S.nrun)) return;
-    const A *seg = (const A *)(check ? (const void *)p.seg64 : (const void *)p.seg);
-    A s = 0;
-    for (int k = 0; k < L.z; ++k) s += seg[L.y + k];
-    A *P = (A *)(check ? (void *)p.P64 : (void *)p.P);
-    P[(size_t)b * p.rows + L.x] = s;
 }
 
 // Combine of a blocked orientation (one thread per row, 256 rows of one
@@ -876,19 +879,49 @@ __global__ __launch_bounds__(NT) void k_dpass(const PassArgs<V> p, const int jw)
     }
 }
 
-// Long rows: add the segment partials in segment order, then the epilogue.
+// Sum of a long row's n segment partials, COMB_L lanes (in every lane): a row
+// of 25k nonzeros has 49 segments, read one after another by one thread they
+// took 7.8 us of a skewed 9.4M-nonzero LP's 92 us iteration.
+constexpr int COMB_L = 16, COMB_ROWS = 256 / COMB_L;
+
+template <class A>
+__device__ __forceinline__ A segment_sum(const A *seg, int n)
+{
+    A s = 0;
+    for (int k = threadIdx.x & (COMB_L - 1); k < n; k += COMB_L) s += seg[k];
+    return group_sum(s, COMB_L);
+}
+
+// Long sub-rows of a blocked orientation: P[b][row] = sum of its segments.
+template <class V, class A>
+__global__ __launch_bounds__(256) void k_bseg(const PassArgs<V> p, const int jw, const int check)
+{
+    const int q = blockIdx.x * COMB_ROWS + threadIdx.x / COMB_L;
+    if (q >= p.nlong) return;
+    const int4 L = p.longs[q];
+    const int inst = L.w & 0xffffff, b = L.w >> 24;
+    const InstState &S = p.st[inst];
+    if (S.status != ST_RUN || (!check && jw >= S.nrun)) return;
+    const A *seg = (const A *)(check ? (const void *)p.seg64 : (const void *)p.seg);
+    const A s = segment_sum(seg + L.y, L.z);
+    if ((threadIdx.x & (COMB_L - 1)) != 0) return;
+    A *P = (A *)(check ? (void *)p.P64 : (void *)p.P);
+    P[(size_t)b * p.rows + L.x] = s;
+}
+
+// Long rows: add the segment partials, then the epilogue.
 template <class V, int DIR>
 __global__ __launch_bounds__(256) void k_combine(const PassArgs<V> p, const int jw)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    const int q = blockIdx.x * COMB_ROWS + threadIdx.x / COMB_L;
     if (q >= p.nlong) return;
     const int4 L = p.longs[q];
     const InstState &S = p.st[L.w];
     if (S.status != ST_RUN || jw >= S.nrun) return;
     const bool copy_ref = (jw == 0) && (S.restart_now != 0);
     const InstBounds<V> ib = inst_bounds<V, DIR>(p, L.w);
-    V s = 0;
-    for (int k = 0; k < L.z; ++k) s += p.seg[L.y + k];
+    const V s = segment_sum(p.seg + L.y, L.z);
+    if ((threadIdx.x & (COMB_L - 1)) != 0) return;
     RowOps<V> ops;
     load_ops<V, DIR>(p, L.x, ops, ib);
     double ip[2] = {0.0, 0.0};
@@ -985,7 +1018,7 @@ __global__ __launch_bounds__(NT) void k_check(const PassArgs<V> p)
 {
     constexpr int CH = NT * EPT;
     __shared__ double prod[CH];
-    __shared__ double red[NT / 64];
+    __shared__ double red[NT / 64 * CHK];
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     const int4 T = p.tiles[t];
     const InstState &S = p.st[T.z];
@@ -1027,24 +1060,19 @@ __global__ __launch_bounds__(NT) void k_check(const PassArgs<V> p)
             }
         }
     }
-#pragma unroll
-    for (int k = 0; k < CHK; ++k) {
-        __syncthreads();
-        const double v = block_sum<double, NT>(q[k], red);
-        if (tid == 0) p.part[CHK * t + k] = v;
-    }
+    block_sums<NT, CHK>(q, red, p.part + CHK * (size_t)t);
 }
 
 template <class V, int DIR>
 __global__ __launch_bounds__(256) void k_combine_check(const PassArgs<V> p)
 {
-    const int qi = blockIdx.x * blockDim.x + threadIdx.x;
+    const int qi = blockIdx.x * COMB_ROWS + threadIdx.x / COMB_L;
     if (qi >= p.nlong) return;
     const int4 L = p.longs[qi];
     const InstState &S = p.st[L.w];
     if (S.status != ST_RUN) return;
-    double s = 0;
-    for (int k = 0; k < L.z; ++k) s += p.seg64[L.y + k];
+    const double s = segment_sum(p.seg64 + L.y, L.z);
+    if ((threadIdx.x & (COMB_L - 1)) != 0) return;
     double q[CHK] = {};
     if (DIR == DIR_COL) {
         col_terms(p, L.x, s, q);
@@ -1060,7 +1088,7 @@ __global__ __launch_bounds__(256) void k_combine_check(const PassArgs<V> p)
 template <class V, int DIR>
 __global__ __launch_bounds__(256) void k_bcombine_check(const PassArgs<V> p)
 {
-    __shared__ double red[4];
+    __shared__ double red[4 * CHK];
     const int ct = blockIdx.x;
     const int4 T = p.ctiles[ct];
     const InstState &S = p.st[T.z];
@@ -1077,12 +1105,7 @@ __global__ __launch_bounds__(256) void k_bcombine_check(const PassArgs<V> p)
             if (p.adapt) p.ax[i] = s;
         }
     }
-#pragma unroll
-    for (int k = 0; k < CHK; ++k) {
-        __syncthreads();
-        const double v = block_sum<double, 256>(q[k], red);
-        if (threadIdx.x == 0) p.part[CHK * ct + k] = v;
-    }
+    block_sums<256, CHK>(q, red, p.part + CHK * (size_t)ct);
 }
 
 // ------------------------------------------------------------- decision
@@ -1214,46 +1237,67 @@ __device__ void decide_state(InstState &S, const double tot[NTOT], const double 
 
 // One workgroup per instance: fixed-order FP64 reduction of the check
 // partials, then termination (Section 2.2), restart and primal-weight
-// update, all in FP64.
-__global__ __launch_bounds__(256) void k_decide(const DecideArgs d)
+// update, all in FP64.  Bound by latency: the partials of a large LP's 10-25k
+// tiles an orientation are read by one compute unit, so 1024 threads take
+// DECIDE_U tiles each at a time, and the sums share their barriers (256
+// threads, one tile after another and two barriers a sum: 28 us for the
+// 1M x 2M LP, 48 us for a skewed one of 9.4M nonzeros, 14 us for a 5k x 10k
+// one with the averages).
+constexpr int DECIDE_NT = 1024, DECIDE_U = 4;
+
+// Adds the N partials of the slots [lo, hi) whose index in a slot starts at
+// from.
+template <int N>
+__device__ __forceinline__ void decide_add(const double *part, int lo, int hi, int from, double *acc)
 {
+    for (int t0 = lo + (int)threadIdx.x; t0 < hi; t0 += DECIDE_NT * DECIDE_U) {
+        double v[DECIDE_U][N];
+#pragma unroll
+        for (int u = 0; u < DECIDE_U; ++u) {
+            const int t = t0 + u * DECIDE_NT;
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[u][k] = t < hi ? part[CHK * (size_t)t + from + k] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < DECIDE_U; ++u)
+#pragma unroll
+            for (int k = 0; k < N; ++k) acc[k] += v[u][k];
+    }
+}
+
+// tot layout as in decide_state: rows {0, 1, 2} and {7, 8, 9}, columns
+// {3, 4, 5, 6} and {10, 11, 12, 13}.
+__device__ __forceinline__ void decide_totals(const InstInfo &I, const double *rpart, const double *lrpart,
+                                              const double *cpart, const double *lcpart, double *red, double *tot)
+{
+    double acc[NTOT] = {};
+    for (int half = 0; half < 2; ++half) {
+        double r[3] = {}, c[4] = {};
+        decide_add<3>(rpart, I.rt0, I.rt1, 4 * half, r);
+        decide_add<3>(lrpart, I.lr0, I.lr1, 4 * half, r);
+        decide_add<4>(cpart, I.ct0, I.ct1, 4 * half, c);
+        decide_add<4>(lcpart, I.lc0, I.lc1, 4 * half, c);
+        for (int k = 0; k < 3; ++k) acc[7 * half + k] = r[k];
+        for (int k = 0; k < 4; ++k) acc[7 * half + 3 + k] = c[k];
+    }
+    block_sums<DECIDE_NT, NTOT>(acc, red, tot);
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(DECIDE_NT) void k_decide(const DecideArgs d)
+{
+    __shared__ double red[DECIDE_NT / 64 * NTOT], tot[NTOT], tot2[NTOT];
     const int inst = blockIdx.x;
     InstState &S = d.st[inst];
-    if (S.status != ST_RUN) return;
+    if (S.status != ST_RUN) {
+        // stopped on the average at an earlier check: it has been taken
+        if (threadIdx.x == 0) S.take_avg = 0;
+        return;
+    }
     const InstInfo I = d.info[inst];
-    __shared__ double red[4];
-    // tot layout as in decide_state: rows {0, 1, 2} and {7, 8, 9}, columns
-    // {3, 4, 5, 6} and {10, 11, 12, 13}
-    double acc[NTOT] = {};
-    auto row_add = [&](const double *q) {
-        for (int k = 0; k < 3; ++k) acc[k] += q[k];
-        for (int k = 0; k < 3; ++k) acc[7 + k] += q[4 + k];
-    };
-    auto col_add = [&](const double *q) {
-        for (int k = 0; k < 4; ++k) acc[3 + k] += q[k];
-        for (int k = 0; k < 4; ++k) acc[10 + k] += q[4 + k];
-    };
-    for (int t = I.rt0 + threadIdx.x; t < I.rt1; t += 256) row_add(d.rpart + CHK * t);
-    for (int t = I.lr0 + threadIdx.x; t < I.lr1; t += 256) row_add(d.lrpart + CHK * t);
-    for (int t = I.ct0 + threadIdx.x; t < I.ct1; t += 256) col_add(d.cpart + CHK * t);
-    for (int t = I.lc0 + threadIdx.x; t < I.lc1; t += 256) col_add(d.lcpart + CHK * t);
-    double tot[NTOT], tot2[NTOT];
-    for (int k = 0; k < NTOT; ++k) {
-        __syncthreads();
-        tot[k] = block_sum<double, 256>(acc[k], red);
-    }
-    if (d.rpart2) {
-        // the same reduction over the running average's check
-        for (int k = 0; k < NTOT; ++k) acc[k] = 0.0;
-        for (int t = I.rt0 + threadIdx.x; t < I.rt1; t += 256) row_add(d.rpart2 + CHK * t);
-        for (int t = I.lr0 + threadIdx.x; t < I.lr1; t += 256) row_add(d.lrpart2 + CHK * t);
-        for (int t = I.ct0 + threadIdx.x; t < I.ct1; t += 256) col_add(d.cpart2 + CHK * t);
-        for (int t = I.lc0 + threadIdx.x; t < I.lc1; t += 256) col_add(d.lcpart2 + CHK * t);
-        for (int k = 0; k < NTOT; ++k) {
-            __syncthreads();
-            tot2[k] = block_sum<double, 256>(acc[k], red);
-        }
-    }
+    decide_totals(I, d.rpart, d.lrpart, d.cpart, d.lcpart, red, tot);
+    // the same reduction over the running average's check
+    if (d.rpart2) decide_totals(I, d.rpart2, d.lrpart2, d.cpart2, d.lcpart2, red, tot2);
     if (threadIdx.x != 0) return;
     decide_state(S, tot, d.rpart2 ? tot2 : nullptr, d.R);
     if (S.status != ST_RUN) d.mirror[inst] = S;
@@ -1837,24 +1881,23 @@ void launch_tiny(const TinyArgs<V> &a, int fmt, int count, int R, int nwin, size
     }
 }
 
-// Restart to the average: one workgroup per instance copies the running
-// mean over the iterate where the decision took it (restart, OPTIMAL or
-// iteration-limit stop), then clears the flag.  The restart reference is
-// copied from the new iterate by the next iteration, as for any restart.
+// Restart to the average: copies the running mean over the iterate where the
+// decision took it (restart, OPTIMAL or iteration-limit stop); blocks
+// workgroups an instance.  The next decision clears the flag.  The restart
+// reference is copied from the new iterate by the next iteration, as for any
+// restart.
 template <class V>
-__global__ __launch_bounds__(256) void k_take_avg(InstState *st, const InstInfo *info, V *x, V *y, const V *xa,
-                                                  const V *ya, double *ax, const double *axa)
+__global__ __launch_bounds__(256) void k_take_avg(const InstState *st, const InstInfo *info, V *x, V *y, const V *xa,
+                                                  const V *ya, double *ax, const double *axa, int blocks)
 {
-    const int inst = blockIdx.x;
+    const int inst = blockIdx.x / blocks, first = (blockIdx.x % blocks) * 256 + threadIdx.x, step = blocks * 256;
     if (!st[inst].take_avg) return;
-    const InstInfo I = info[inst];
-    for (int j = I.col0 + threadIdx.x; j < I.col1; j += 256) x[j] = xa[j];
-    for (int i = I.row0 + threadIdx.x; i < I.row1; i += 256) {
+    const InstInfo &I = info[inst];
+    for (int j = I.col0 + first; j < I.col1; j += step) x[j] = xa[j];
+    for (int i = I.row0 + first; i < I.row1; i += step) {
         y[i] = ya[i];
         if (ax) ax[i] = axa[i];
     }
-    __syncthreads();
-    if (threadIdx.x == 0) st[inst].take_avg = 0;
 }
 
 __global__ void k_force_stop(InstState *st, int count)
@@ -2291,7 +2334,7 @@ void launch_pass(const PassArgs<V> &p, int fmt, int dir, int ept, int jw, bool c
             else bpart_fmt<V, V>(p, fmt, ept, jw, 0, s);
         }
         if (p.nlong > 0) {
-            const int nb = (p.nlong + 255) / 256;
+            const int nb = (p.nlong + COMB_ROWS - 1) / COMB_ROWS;
             if (check) hipLaunchKernelGGL((k_bseg<V, double>), dim3(nb), dim3(256), 0, s, p, jw, 1);
             else hipLaunchKernelGGL((k_bseg<V, V>), dim3(nb), dim3(256), 0, s, p, jw, 0);
         }
@@ -2320,7 +2363,7 @@ void launch_pass(const PassArgs<V> &p, int fmt, int dir, int ept, int jw, bool c
         }
     }
     if (p.nlong > 0) {
-        const int nb = (p.nlong + 255) / 256;
+        const int nb = (p.nlong + COMB_ROWS - 1) / COMB_ROWS;
         if (check) {
             if (dir == DIR_COL) hipLaunchKernelGGL((k_combine_check<V, DIR_COL>), dim3(nb), dim3(256), 0, s, p);
             else hipLaunchKernelGGL((k_combine_check<V, DIR_ROW>), dim3(nb), dim3(256), 0, s, p);
@@ -2424,14 +2467,20 @@ void launch_step(const StepArgs &a, int count, hipStream_t s)
 
 void launch_decide(const DecideArgs &d, int count, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_decide, dim3(count), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(k_decide, dim3(count), dim3(DECIDE_NT), 0, s, d);
 }
 
 template <class V>
-void launch_take_avg(InstState *st, const InstInfo *info, V *x, V *y, const V *xa, const V *ya, double *ax,
-                     const double *axa, int count, hipStream_t s)
+void launch_take_avg(const InstState *st, const InstInfo *info, V *x, V *y, const V *xa, const V *ya, double *ax,
+                     const double *axa, int count, int longest, hipStream_t s)
 {
-    if (count > 0) hipLaunchKernelGGL(k_take_avg<V>, dim3(count), dim3(256), 0, s, st, info, x, y, xa, ya, ax, axa);
+    // about 2048 columns a workgroup, at most 256 workgroups an instance (a
+    // workgroup for each of a 5k x 10k instance took 7 us)
+    int blocks = (longest + 2047) / 2048;
+    if (blocks < 1) blocks = 1;
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(k_take_avg<V>, dim3((unsigned)(count * blocks)), dim3(256), 0, s, st, info, x, y, xa, ya, ax, axa,
+                       blocks);
 }
 
 void launch_force_stop(InstState *st, int count, hipStream_t s)
@@ -2526,8 +2575,8 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
     template void launch_combine<V>(const PassArgs<V> &, int, int, hipStream_t);                       \
     template void launch_direct<V>(const PassArgs<V> &, int, int, int, int, size_t, hipStream_t, bool); \
     template void launch_finish_diag<V>(const double *, V *, int, hipStream_t);                        \
-    template void launch_take_avg<V>(InstState *, const InstInfo *, V *, V *, const V *, const V *,      \
-                                     double *, const double *, int, hipStream_t);                       \
+    template void launch_take_avg<V>(const InstState *, const InstInfo *, V *, V *, const V *, const V *, \
+                                     double *, const double *, int, int, hipStream_t);                      \
     template void launch_begin<V>(const BeginArgs<V> &, hipStream_t);                                  \
     template void launch_cast<V>(const double *, V *, int, hipStream_t);                               \
     template void launch_project<V>(V *, const V *, const V *, int, int, V *, const uint8_t *, int, int, \

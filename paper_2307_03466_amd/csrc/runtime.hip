@@ -572,7 +572,7 @@ void enqueue_check(scylla_batch *h, int32_t R, hipStream_t s)
     if (h->avg_on)
         launch_take_avg<V>(h->st.as<InstState>(), h->info.as<InstInfo>(), h->x.as<V>(), h->y.as<V>(),
                            h->xavg.as<V>(), h->yavg.as<V>(), h->adaptive ? h->ax.as<double>() : nullptr,
-                           h->adaptive ? h->axavg.as<double>() : nullptr, h->count, s);
+                           h->adaptive ? h->axavg.as<double>() : nullptr, h->count, h->longest, s);
 }
 
 // The first n iterations after a check.
@@ -1258,6 +1258,8 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     set_plan(h, h->orow, 0, 8);
     set_plan(h, h->ocol, 0, 8);
     refresh_info(h);
+    for (int32_t q = 0; q < h->count; ++q)
+        h->longest = std::max({h->longest, h->row_off[q + 1] - h->row_off[q], h->col_off[q + 1] - h->col_off[q]});
     for (int32_t q = 0; q < h->count; ++q)
         h->norm_slots = std::max(h->norm_slots, norm_blocks(h->row_off[q + 1] - h->row_off[q],
                                                             h->col_off[q + 1] - h->col_off[q]));
