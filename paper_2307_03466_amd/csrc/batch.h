@@ -188,6 +188,12 @@ struct scylla_batch {
     DevMem ibnd;            // [2 * count] (l, u) shared by all columns of an
                             // instance, NaN where they differ
     DevMem start_flag;      // validation flag of a device warm start
+    // pinned staging of small updates (objectives, rounding bits, weights):
+    // copied from without waiting, reused from the start once the stream has
+    // drained
+    char *stage = nullptr;
+    size_t stage_at = 0;
+    int *start_host = nullptr;  // pinned copy of start_flag
     DevMem q64, qv;         // diagonal Hessian (QP objectives), once set
     DevMem xp, yp, axp, atyp;  // previous check's point and products
     bool has_q = false;
@@ -240,6 +246,8 @@ struct scylla_batch {
         if (pinned) (void)hipHostFree(pinned);
         if (cstage) (void)hipHostFree(cstage);
         if (limits) (void)hipHostFree(limits);
+        if (stage) (void)hipHostFree(stage);
+        if (start_host) (void)hipHostFree(start_host);
         if (ev) (void)hipEventDestroy(ev);
         if (cap) (void)hipStreamDestroy(cap);
         if (side) (void)hipStreamDestroy(side);
@@ -290,6 +298,10 @@ void cast_q(scylla_batch *h, int32_t lo, int32_t hi);
 // Norms and cold-start weights of the instances [q0, q1) for their current
 // objective (rows: and right-hand side).
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows = false);
+NormArgs norm_args(scylla_batch *h, int32_t q0);
+// Pump objective and partial norms of instance inst from device-readable
+// rounding and integer bits; launch_norm_final must follow.
+void blend_instance(scylla_batch *h, int32_t inst, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa);
 
 // ---- defined in fixprop_dev.hip
 // Batched fix-and-propagate of every wanted instance on the device.

@@ -209,16 +209,29 @@ template <class V>
 void launch_begin(const BeginArgs<V> &a, hipStream_t s);
 void launch_decide(const DecideArgs &d, int count, hipStream_t s);
 void launch_force_stop(InstState *st, int count, hipStream_t s);
-// flag |= 1 if x[0, n) holds a NaN, |= 2 if y[0, m) holds a non-finite value
-// (either pointer may be null; *flag must start at 0).
-void launch_start_check(const double *x, int n, const double *y, int m, int *flag, hipStream_t s);
+// Warm start of all instances from device memory: x0 [n] / y0 [m] (null:
+// keep the iterate), omega [count] (null, or <= 0: keep), checked first and
+// written only if valid; *host_flag (pinned) gets 1: a NaN in x0, 2: a
+// non-finite y0.  *flag must be 0 and is 0 again afterwards.
+template <class V>
+struct StartArgs {
+    const double *x0, *y0, *omega;
+    V *x, *y;
+    const V *l, *u;
+    const uint8_t *sense;
+    InstState *st;
+    int *flag;
+    int32_t n, m, count;
+};
+template <class V>
+void launch_start(const StartArgs<V> &a, int *host_flag, hipStream_t s);
 void launch_scale_reduce(const MatView &M, int fmt, int rows, const double *drow, const double *dcol,
                          double *out, int mode, hipStream_t s);
 void launch_scale_apply(double *d, const double *r, int len, hipStream_t s);
 // Norms of the instances [q0, q1) after their objective (and, with rows set,
 // their right-hand side) was written; part holds 4 doubles per instance and
 // slot, slots = the most pieces of any instance of the handle.
-constexpr int NORM_CHUNK = 8192, NORM_MAX_BLOCKS = 256;
+constexpr int NORM_CHUNK = 2048, NORM_MAX_BLOCKS = 1024;
 __host__ __device__ inline int norm_blocks(int m, int n)
 {
     const int64_t nb = ((int64_t)m + n + NORM_CHUNK - 1) / NORM_CHUNK;
@@ -226,11 +239,26 @@ __host__ __device__ inline int norm_blocks(int m, int n)
 }
 struct NormArgs {
     const InstInfo *info;
-    const double *b, *c, *dr, *dc;
+    const double *b;
+    double *c;  // (written by launch_blend only)
+    const double *dr, *dc;
     InstState *st;
     double *part;
     int32_t slots, q0, rows;
 };
+// Pump objective of instance q0: original objective, rounding bits and integer
+// bits of its columns (null: all integer), weights, path-precision copy.
+struct BlendArgs {
+    const double *c_orig;
+    const uint8_t *xbits, *ibits;
+    double a, kappa;
+    void *cv;
+};
+// Objective and partial norms of instance a.q0; launch_norm_final over the
+// instances must follow (launch_norms does both for objectives in place).
+template <class V>
+void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s);
+void launch_norm_final(const NormArgs &a, int q1, hipStream_t s);
 void launch_norms(const NormArgs &a, int q1, hipStream_t s);
 template <class V>
 void launch_finish_diag(const double *d, V *d2, int len, hipStream_t s);
@@ -239,12 +267,9 @@ void launch_cast(const double *src, V *dst, int len, hipStream_t s);
 template <class V>
 void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const uint8_t *sense, int rlo,
                     int rhi, int zero, hipStream_t s);
-template <class V>
-void launch_blend(const double *c_orig, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa,
-                  double *c64, V *cv, int lo, int hi, hipStream_t s);
 // MIP-feasibility of x per instance (rows within tol (1 + |b_i|), bounds
 // and integrality within tol): rbad [m], cbad [n] scratch flags,
-// feasible [count] = 1 / 0.
+// feasible [count] = 1 / 0; is_int null: all integer.
 template <class V>
 void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const InstInfo *info, const V *x,
                       const double *b, const uint8_t *sense, const double *l, const double *u,

@@ -1947,11 +1947,12 @@ __global__ void k_scale_apply(double *d, const double *r, int len)
 // One workgroup per instance read a 300k x 600k LP's 14 MB in 1.05 ms and a
 // 20k x 40k instance's in 75 us (latency of one CU's loads), so an instance
 // is cut into norm_blocks() pieces of about NORM_CHUNK entries, one workgroup
-// each, whose partial sums a second kernel adds in piece order.  With that,
+// each, whose partial sums a second kernel adds in a fixed order.  With that,
 // and the sums of the instances that changed only, a new objective and a warm
 // re-solve of 64 iterations of the 300k x 600k LP went from 4.80 to 3.73 ms,
 // 64 objective updates and a re-solve of 64 20k x 40k instances from 11.5 to
-// 7.4 ms.  The pieces depend on the instance alone, so a batch and a single
+// 7.4 ms (pieces of 8192; at 2048, with the pump's objective made in the same
+// launch, the latter's update kernels take 0.4 ms less again).  The pieces depend on the instance alone, so a batch and a single
 // solve agree bit for bit.  An instance of one piece is finished by its only
 // workgroup.
 __device__ __forceinline__ void norm_finish(InstState &S, const double s[4], bool rows)
@@ -1985,11 +1986,47 @@ __device__ __forceinline__ void norm_sums(const double *v, const double *d, int 
     }
 }
 
+// The same over columns whose objective is the pump's (Algorithm 1, objective
+// update), written on the way: c_hat_j = a kappa c_j + (1 - a) g_j, g_j = +1 /
+// -1 from the rounding bit, 0 for continuous columns; bits count from j0.
+template <class V>
+__device__ __forceinline__ void blend_sums(const BlendArgs &B, double *c, const double *d, int j0, int lo, int hi,
+                                           double &s, double &t)
+{
+    for (int i0 = lo + (int)threadIdx.x; i0 < hi; i0 += 4 * 256) {
+        double w[4], co[4];
+        bool up[4], in[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = i0 + u * 256, q = j - j0;
+            const bool on = j < hi;
+            w[u] = on ? d[j] : 0.0;
+            co[u] = on ? B.c_orig[j] : 0.0;
+            up[u] = on && ((B.xbits[q >> 3] >> (q & 7)) & 1);
+            in[u] = on && (!B.ibits || ((B.ibits[q >> 3] >> (q & 7)) & 1));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = i0 + u * 256;
+            if (j >= hi) continue;
+            const double g = in[u] ? (up[u] ? -1.0 : 1.0) : 0.0;
+            const double v = B.a * B.kappa * co[u] + (1.0 - B.a) * g;
+            c[j] = v;
+            ((V *)B.cv)[j] = (V)v;
+            const double x = w[u] * v;
+            s += v * v;
+            t += x * x;
+        }
+    }
+}
+
 // Workgroup slots * i + piece: one piece of instance q0 + i, partial sums to
 // part[4 (slots q + piece)], or the norms themselves when it is the only one.
-__global__ __launch_bounds__(256) void k_norm_part(const NormArgs a)
+// BLEND: the objective is written first (V: path precision).
+template <class V, bool BLEND>
+__global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const BlendArgs B)
 {
-    __shared__ double red[4];
+    __shared__ double red[4 * 4], sum[4];
     const int q = a.q0 + (int)(blockIdx.x / a.slots), blk = (int)(blockIdx.x % a.slots);
     const InstInfo &I = a.info[q];
     const int m = I.row1 - I.row0, n = I.col1 - I.col0;
@@ -1999,20 +2036,13 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a)
     if (a.rows)
         norm_sums(a.b, a.dr, I.row0 + (int)((int64_t)m * blk / nb), I.row0 + (int)((int64_t)m * (blk + 1) / nb),
                   acc[0], acc[1]);
-    norm_sums(a.c, a.dc, I.col0 + (int)((int64_t)n * blk / nb), I.col0 + (int)((int64_t)n * (blk + 1) / nb), acc[2],
-              acc[3]);
-    double s[4];
-    for (int k = 0; k < 4; ++k) {
-        s[k] = block_sum<double, 256>(acc[k], red);
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
-    if (nb == 1) {
-        norm_finish(a.st[q], s, a.rows != 0);
-    } else {
-        double *p = a.part + 4 * ((size_t)a.slots * q + blk);
-        for (int k = 0; k < 4; ++k) p[k] = s[k];
-    }
+    const int lo = I.col0 + (int)((int64_t)n * blk / nb), hi = I.col0 + (int)((int64_t)n * (blk + 1) / nb);
+    if constexpr (BLEND) blend_sums<V>(B, a.c, a.dc, I.col0, lo, hi, acc[2], acc[3]);
+    else norm_sums(a.c, a.dc, lo, hi, acc[2], acc[3]);
+    block_sums<256, 4>(acc, red, nb == 1 ? sum : a.part + 4 * ((size_t)a.slots * q + blk));
+    if (nb > 1) return;
+    __syncthreads();
+    if (threadIdx.x == 0) norm_finish(a.st[q], sum, a.rows != 0);
 }
 
 // One wave per instance of more than one piece: adds the partial sums.
@@ -2027,7 +2057,7 @@ __global__ __launch_bounds__(64) void k_norm_final(const NormArgs a)
         const double *p = a.part + 4 * ((size_t)a.slots * q + b);
         for (int k = 0; k < 4; ++k) s[k] += p[k];
     }
-    for (int k = 0; k < 4; ++k) s[k] = wave_sum_width(s[k], 64);
+    for (int k = 0; k < 4; ++k) s[k] = group_sum(s[k], 64);
     if (threadIdx.x == 0) norm_finish(a.st[q], s, a.rows != 0);
 }
 
@@ -2129,21 +2159,57 @@ void launch_begin(const BeginArgs<V> &a, hipStream_t s)
     hipLaunchKernelGGL(k_begin<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, a);
 }
 
-// flag |= 1 if some x[j] is NaN, |= 2 if some y[i] is not finite (a warm
-// start read from device memory is checked before anything is written).
-__global__ void k_start_check(const double *x, int n, const double *y, int m, int *flag)
+// Warm start from device memory, in three launches and one wait: the values
+// are checked (flag |= 1: a NaN in x, |= 2: a non-finite y), then written only
+// if the flag stayed clear, then the flag goes to the host and is cleared for
+// the next call.
+__global__ __launch_bounds__(256) void k_start_check(const double *x, int n, const double *y, int m, int *flag)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int k = blockIdx.x * 256 + threadIdx.x;
     int bad = 0;
     if (x && k < n && isnan(x[k])) bad |= 1;
     if (y && k < m && !isfinite(y[k])) bad |= 2;
     if (bad) atomicOr(flag, bad);
 }
 
-void launch_start_check(const double *x, int n, const double *y, int m, int *flag, hipStream_t s)
+template <class V>
+__global__ __launch_bounds__(256) void k_start_set(const StartArgs<V> a)
 {
-    const int nx = x ? n : 0, ny = y ? m : 0, len = nx > ny ? nx : ny;
-    if (len > 0) hipLaunchKernelGGL(k_start_check, dim3((len + 255) / 256), dim3(256), 0, s, x, n, y, m, flag);
+    if (*a.flag) return;
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < a.n) {
+        V v = a.x0 ? (V)a.x0[k] : a.x[k];
+        v = v < a.l[k] ? a.l[k] : v;
+        v = v > a.u[k] ? a.u[k] : v;
+        a.x[k] = v;
+    }
+    if (k < a.m) {
+        V v = a.y0 ? (V)a.y0[k] : a.y[k];
+        const uint8_t sn = a.sense[k];
+        if (sn == 'G') v = v > (V)0 ? v : (V)0;
+        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
+        a.y[k] = v;
+    }
+    if (a.omega && k < a.count && a.omega[k] > 0.0) a.st[k].omega = a.omega[k];
+}
+
+__global__ void k_start_flag(int *flag, int *host)
+{
+    *host = *flag;
+    *flag = 0;
+}
+
+template <class V>
+void launch_start(const StartArgs<V> &a, int *host_flag, hipStream_t s)
+{
+    const int nx = a.x0 ? a.n : 0, ny = a.y0 ? a.m : 0, given = nx > ny ? nx : ny;
+    if (given > 0)
+        hipLaunchKernelGGL(k_start_check, dim3((unsigned)((given + 255) / 256)), dim3(256), 0, s, a.x0, nx, a.y0, ny,
+                           a.flag);
+    int len = a.n > a.m ? a.n : a.m;
+    if (a.count > len) len = a.count;
+    hipLaunchKernelGGL(k_start_set<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_start_flag, dim3(1), dim3(1), 0, s, a.flag, host_flag);
 }
 
 template <class V>
@@ -2158,50 +2224,50 @@ __global__ void k_project_dual(V *y, const uint8_t *sense, int lo, int hi, int z
     y[i] = v;
 }
 
-// Pump objective (Algorithm 1, objective update) on columns [lo, hi):
-// c_hat_j = a kappa c_j + (1 - a) g_j, g_j = +1 / -1 from the rounding bit,
-// 0 for continuous columns.
-template <class V>
-__global__ void k_blend(const double *c_orig, const uint8_t *xbits, const uint8_t *ibits, double a,
-                        double kappa, double *c64, V *cv, int lo, int hi)
-{
-    const int j = lo + blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= hi) return;
-    const int q = j - lo;
-    const bool integer = ibits ? ((ibits[q >> 3] >> (q & 7)) & 1) : true;
-    const bool up = (xbits[q >> 3] >> (q & 7)) & 1;
-    const double g = integer ? (up ? -1.0 : 1.0) : 0.0;
-    const double v = a * kappa * c_orig[j] + (1.0 - a) * g;
-    c64[j] = v;
-    cv[j] = (V)v;
-}
-
 // ------------------------------------------------ MIP feasibility
 // Algorithm 1 tests the PDHG point itself before rounding it: x is
 // MIP-feasible when every row holds within tol (1 + |b_i|), every x_j lies
 // within tol of [l_j, u_j] and every integer x_j within tol of an integer.
-// Row activities are FP64 sums of a_ij x_j (16 lanes per row); a
+// Row activities are FP64 sums of a_ij x_j (MIP_L lanes per row, MIP_U entries
+// a lane at a time: at 16 lanes a row of 11 nonzeros left a load in flight a
+// lane, 115 us for 64 20k x 40k instances against 31 us for a pass); a
 // non-finite value counts as a violation.  Flags: 1 = violated.
+constexpr int MIP_L = 4, MIP_U = 4;
+
 template <class V, int FMT>
 __global__ __launch_bounds__(256) void k_mip_rows(const MatView M, int rows, const V *__restrict__ x,
                                                   const double *__restrict__ b, const uint8_t *__restrict__ sense,
                                                   double tol, uint8_t *__restrict__ bad)
 {
-    const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
-    const int lane = threadIdx.x & 15;
-    // whole 16-lane groups leave together, so the shuffles below only
-    // involve lanes that are still running
+    const int row = blockIdx.x * (256 / MIP_L) + threadIdx.x / MIP_L;
+    const int lane = threadIdx.x & (MIP_L - 1);
+    // whole lane groups leave together, so the sums below only involve lanes
+    // that are still running
     if (row >= rows) return;
     const int e1 = M.ptr[row + 1];
     double acc = 0.0;
-    for (int e = M.ptr[row] + lane; e < e1; e += 16) {
-        uint32_t w;
-        double a;
-        load_entry<FMT, double>(M, e, w, a);
-        const int j = decode_entry<FMT, double>(M, w, a);
-        acc += a * (double)x[j];
+    for (int e0 = M.ptr[row] + lane; e0 < e1; e0 += MIP_L * MIP_U) {
+        uint32_t w[MIP_U];
+        double a[MIP_U];
+        int j[MIP_U];
+        V g[MIP_U];
+#pragma unroll
+        for (int u = 0; u < MIP_U; ++u) {
+            const int e = e0 + u * MIP_L;
+            w[u] = 0;
+            a[u] = 0.0;
+            if (e < e1) load_entry<FMT, double>(M, e, w[u], a[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < MIP_U; ++u) {
+            j[u] = decode_entry<FMT, double>(M, w[u], a[u]);
+            if (e0 + u * MIP_L < e1) g[u] = x[j[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < MIP_U; ++u)
+            if (e0 + u * MIP_L < e1) acc += a[u] * (double)g[u];
     }
-    for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
+    acc = group_sum(acc, MIP_L);
     if (lane == 0) {
         const double bi = b[row], t = tol * (1.0 + fabs(bi));
         const uint8_t sn = sense[row];
@@ -2212,6 +2278,7 @@ __global__ __launch_bounds__(256) void k_mip_rows(const MatView M, int rows, con
     }
 }
 
+// is_int null: every column is integer.
 template <class V>
 __global__ void k_mip_cols(const V *__restrict__ x, const double *__restrict__ l, const double *__restrict__ u,
                            const uint8_t *__restrict__ is_int, double tol, int n, uint8_t *__restrict__ bad)
@@ -2220,20 +2287,36 @@ __global__ void k_mip_cols(const V *__restrict__ x, const double *__restrict__ l
     if (j >= n) return;
     const double v = (double)x[j];
     bool ok = v >= l[j] - tol && v <= u[j] + tol;
-    if (is_int[j]) ok = ok && fabs(v - rint(v)) <= tol;
+    if (!is_int || is_int[j]) ok = ok && fabs(v - rint(v)) <= tol;
     bad[j] = ok ? 0 : 1;
+}
+
+// Whether one of the flags [lo, hi) is set, as this thread sees them: aligned
+// words of 16 flags, the ends flag by flag (flag by flag throughout, one
+// workgroup took 60 us for 60k flags an instance).
+__device__ __forceinline__ uint32_t any_flag(const uint8_t *__restrict__ f, int lo, int hi)
+{
+    uint32_t any = 0;
+    const int a = (int)(((uintptr_t)(f + lo) + 15) / 16 * 16 - (uintptr_t)(f + lo));
+    const int first = lo + a < hi ? lo + a : hi, words = (hi - first) / 16, last = first + 16 * words;
+    for (int i = lo + (int)threadIdx.x; i < first; i += 256) any |= f[i];
+    const uint4 *w = reinterpret_cast<const uint4 *>(f + first);
+    for (int i = threadIdx.x; i < words; i += 256) {
+        const uint4 v = w[i];
+        any |= v.x | v.y | v.z | v.w;
+    }
+    for (int i = last + (int)threadIdx.x; i < hi; i += 256) any |= f[i];
+    return any;
 }
 
 // One workgroup per instance: feasible[inst] = no violated row or column.
 __global__ __launch_bounds__(256) void k_mip_reduce(const InstInfo *__restrict__ info, const uint8_t *__restrict__ rbad,
                                                     const uint8_t *__restrict__ cbad, uint8_t *__restrict__ feasible)
 {
-    const InstInfo I = info[blockIdx.x];
-    int any = 0;
-    for (int i = I.row0 + threadIdx.x; i < I.row1; i += 256) any |= rbad[i];
-    for (int j = I.col0 + threadIdx.x; j < I.col1; j += 256) any |= cbad[j];
-    any = __syncthreads_or(any);
-    if (threadIdx.x == 0) feasible[blockIdx.x] = any ? 0 : 1;
+    const InstInfo &I = info[blockIdx.x];
+    const uint32_t any = any_flag(rbad, I.row0, I.row1) | any_flag(cbad, I.col0, I.col1);
+    const int bad = __syncthreads_or(any != 0);
+    if (threadIdx.x == 0) feasible[blockIdx.x] = bad ? 0 : 1;
 }
 
 // ------------------------------------------------------ host launchers
@@ -2509,9 +2592,21 @@ void launch_scale_apply(double *d, const double *r, int len, hipStream_t s)
 void launch_norms(const NormArgs &a, int q1, hipStream_t s)
 {
     if (q1 <= a.q0) return;
-    const unsigned nq = (unsigned)(q1 - a.q0);
-    hipLaunchKernelGGL(k_norm_part, dim3((unsigned)a.slots * nq), dim3(256), 0, s, a);
-    if (a.slots > 1) hipLaunchKernelGGL(k_norm_final, dim3(nq), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_norm_part<double, false>), dim3((unsigned)a.slots * (unsigned)(q1 - a.q0)), dim3(256), 0, s, a,
+                       BlendArgs{});
+    launch_norm_final(a, q1, s);
+}
+
+template <class V>
+void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_norm_part<V, true>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+}
+
+void launch_norm_final(const NormArgs &a, int q1, hipStream_t s)
+{
+    if (a.slots > 1 && q1 > a.q0)
+        hipLaunchKernelGGL(k_norm_final, dim3((unsigned)(q1 - a.q0)), dim3(64), 0, s, a);
 }
 
 template <class V>
@@ -2537,22 +2632,13 @@ void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const 
 }
 
 template <class V>
-void launch_blend(const double *c_orig, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa,
-                  double *c64, V *cv, int lo, int hi, hipStream_t s)
-{
-    if (hi > lo)
-        hipLaunchKernelGGL(k_blend<V>, dim3((hi - lo + 255) / 256), dim3(256), 0, s, c_orig, xbits, ibits, a,
-                           kappa, c64, cv, lo, hi);
-}
-
-template <class V>
 void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const InstInfo *info, const V *x,
                       const double *b, const uint8_t *sense, const double *l, const double *u,
                       const uint8_t *is_int, double tol, uint8_t *rbad, uint8_t *cbad, uint8_t *feasible,
                       hipStream_t s)
 {
     if (m > 0) {
-        dim3 g((m + 15) / 16), bl(256);
+        dim3 g((m + 256 / MIP_L - 1) / (256 / MIP_L)), bl(256);
         if constexpr (sizeof(V) == 8) {
             hipLaunchKernelGGL((k_mip_rows<V, FMT_F64>), g, bl, 0, s, M, m, x, b, sense, tol, rbad);
         } else {
@@ -2578,11 +2664,11 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
     template void launch_take_avg<V>(const InstState *, const InstInfo *, V *, V *, const V *, const V *, \
                                      double *, const double *, int, int, hipStream_t);                      \
     template void launch_begin<V>(const BeginArgs<V> &, hipStream_t);                                  \
+    template void launch_start<V>(const StartArgs<V> &, int *, hipStream_t);                           \
     template void launch_cast<V>(const double *, V *, int, hipStream_t);                               \
     template void launch_project<V>(V *, const V *, const V *, int, int, V *, const uint8_t *, int, int, \
                                     int, hipStream_t);                                                 \
-    template void launch_blend<V>(const double *, const uint8_t *, const uint8_t *, double, double,    \
-                                  double *, V *, int, int, hipStream_t);                               \
+    template void launch_blend<V>(const NormArgs &, const BlendArgs &, hipStream_t);                   \
     template void launch_mip_check<V>(const MatView &, int, int, int, int, const InstInfo *, const V *, \
                                       const double *, const uint8_t *, const double *, const double *, \
                                       const uint8_t *, double, uint8_t *, uint8_t *, uint8_t *, hipStream_t);

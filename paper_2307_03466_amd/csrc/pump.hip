@@ -7,18 +7,20 @@
 
 namespace {
 
-// Integer flags [N] of the MIP-feasibility check (NULL: all integer).
+// Integer flags [N] of the MIP-feasibility check (NULL: all integer, which
+// needs no flags).
 void set_mip_isint(scylla_batch *h, const uint8_t *is_int)
 {
     const size_t N = (size_t)std::max(h->N, 1);
-    if (h->mip_isint.bytes < N) h->mip_isint.alloc(N);
     if (h->mip_rbad.bytes < (size_t)std::max(h->M, 1)) h->mip_rbad.alloc((size_t)std::max(h->M, 1));
     if (h->mip_cbad.bytes < N) h->mip_cbad.alloc(N);
     if (h->mip_ok.bytes < (size_t)h->count) h->mip_ok.alloc((size_t)h->count);
-    std::vector<uint8_t> ii(N, 1);
-    if (is_int)
-        for (int32_t j = 0; j < h->N; ++j) ii[j] = is_int[j] ? 1 : 0;
-    HIPC(hipMemcpyAsync(h->mip_isint.p, ii.data(), N, hipMemcpyHostToDevice, h->stream));
+    if (!is_int) {
+        h->mip_isint.release();
+        return;
+    }
+    if (h->mip_isint.bytes < N) h->mip_isint.alloc(N);
+    HIPC(hipMemcpyAsync(h->mip_isint.p, is_int, (size_t)h->N, hipMemcpyHostToDevice, h->stream));
     HIPC(hipStreamSynchronize(h->stream));
 }
 
@@ -425,6 +427,7 @@ int pump_impl(scylla_batch *h, const scylla_params *p, const uint8_t *is_int, co
                                 hipMemcpyHostToDevice, h->stream));
             cast_c(h, c0, c1);
             cast_q(h, c0, c1);
+            refresh_norms(h, g.q0, g.q1);
         } else if (g.K < o.rounds && any) {
             const double a = pow(o.alpha, (double)g.K);
             const size_t b0 = boff[g.q0], b1 = boff[g.q1];
@@ -432,19 +435,12 @@ int pump_impl(scylla_batch *h, const scylla_params *p, const uint8_t *is_int, co
                                 h->stream));
             for (int32_t q = g.q0; q < g.q1; ++q) {
                 if (!active[q]) continue;
-                const int lo = h->col_off[q], hi = h->col_off[q + 1];
-                const uint8_t *xb = h->bits_tmp.as<uint8_t>() + boff[q];
-                const uint8_t *ib = h->ibits_tmp.as<uint8_t>() + boff[q];
-                if (h->vbytes == 4)
-                    launch_blend<float>(h->corig64.as<double>(), xb, ib, a, kappa[q], h->c64.as<double>(),
-                                        h->cv.as<float>(), lo, hi, h->stream);
-                else
-                    launch_blend<double>(h->corig64.as<double>(), xb, ib, a, kappa[q], h->c64.as<double>(),
-                                         h->cv.as<double>(), lo, hi, h->stream);
+                blend_instance(h, q, h->bits_tmp.as<uint8_t>() + boff[q], h->ibits_tmp.as<uint8_t>() + boff[q], a,
+                               kappa[q]);
             }
+            launch_norm_final(norm_args(h, g.q0), g.q1, h->stream);
         }
         if (g.K < o.rounds && any) {
-            refresh_norms(h, g.q0, g.q1);
             HIPC(hipGetLastError());
             HIPC(hipStreamSynchronize(h->stream));
         }

@@ -1326,13 +1326,12 @@ void project_start(scylla_batch *h, int32_t inst, int zero)
                       h->sense.as<uint8_t>(), rlo, rhi, zero, h->stream);
 }
 
-// Projects (after zeroing, when `zero`) the start points of instances
-// [q0, q1), which occupy contiguous column and row ranges.
 template <class V>
-void project_range(scylla_batch *h, int32_t q0, int32_t q1, int zero)
+void start_device(scylla_batch *h, const double *x0, const double *y0, const double *omega)
 {
-    launch_project<V>(h->x.as<V>(), h->lv.as<V>(), h->uv.as<V>(), h->col_off[q0], h->col_off[q1], h->y.as<V>(),
-                      h->sense.as<uint8_t>(), h->row_off[q0], h->row_off[q1], zero, h->stream);
+    const StartArgs<V> a{x0, y0, omega, h->x.as<V>(), h->y.as<V>(), h->lv.as<V>(), h->uv.as<V>(),
+                         h->sense.as<uint8_t>(), h->st.as<InstState>(), h->start_flag.as<int>(), h->N, h->M, h->count};
+    launch_start<V>(a, h->start_host, h->stream);
 }
 
 // States of a solve from its parameters, start points of instances [q0, q1).
@@ -1571,12 +1570,24 @@ static void cast_range(scylla_batch *h, const DevMem &src, DevMem &dst, int32_t 
 void cast_c(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->c64, h->cv, lo, hi); }
 void cast_q(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->q64, h->qv, lo, hi); }
 
+NormArgs norm_args(scylla_batch *h, int32_t q0)
+{
+    return {h->info.as<InstInfo>(), h->b64.as<double>(),   h->c64.as<double>(),       h->dr64.as<double>(),
+            h->dc64.as<double>(),   h->st.as<InstState>(), h->norm_part.as<double>(), h->norm_slots, q0, 0};
+}
+
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows)
 {
-    const NormArgs a{h->info.as<InstInfo>(), h->b64.as<double>(), h->c64.as<double>(), h->dr64.as<double>(),
-                     h->dc64.as<double>(), h->st.as<InstState>(), h->norm_part.as<double>(), h->norm_slots, q0,
-                     rows ? 1 : 0};
+    NormArgs a = norm_args(h, q0);
+    a.rows = rows ? 1 : 0;
     launch_norms(a, q1, h->stream);
+}
+
+void blend_instance(scylla_batch *h, int32_t inst, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa)
+{
+    const BlendArgs b{h->corig64.as<double>(), xbits, ibits, a, kappa, h->cv.p};
+    if (h->vbytes == 4) launch_blend<float>(norm_args(h, inst), b, h->stream);
+    else launch_blend<double>(norm_args(h, inst), b, h->stream);
 }
 
 }  // namespace scy
@@ -1738,14 +1749,8 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         if (int_bits && h->ibits_tmp.bytes < nb) h->ibits_tmp.alloc(nb);
         HIPC(hipMemcpyAsync(h->bits_tmp.p, xhat_bits, nb, hipMemcpyHostToDevice, h->stream));
         if (int_bits) HIPC(hipMemcpyAsync(h->ibits_tmp.p, int_bits, nb, hipMemcpyHostToDevice, h->stream));
-        const uint8_t *ib = int_bits ? h->ibits_tmp.as<uint8_t>() : nullptr;
-        if (h->vbytes == 4)
-            launch_blend<float>(h->corig64.as<double>(), h->bits_tmp.as<uint8_t>(), ib, a, kappa,
-                                h->c64.as<double>(), h->cv.as<float>(), lo, hi, h->stream);
-        else
-            launch_blend<double>(h->corig64.as<double>(), h->bits_tmp.as<uint8_t>(), ib, a, kappa,
-                                 h->c64.as<double>(), h->cv.as<double>(), lo, hi, h->stream);
-        refresh_norms(h, inst, inst + 1);
+        blend_instance(h, inst, h->bits_tmp.as<uint8_t>(), int_bits ? h->ibits_tmp.as<uint8_t>() : nullptr, a, kappa);
+        launch_norm_final(norm_args(h, inst), inst + 1, h->stream);
         HIPC(hipGetLastError());
         HIPC(hipStreamSynchronize(h->stream));
         return 0;
@@ -1795,36 +1800,22 @@ int scylla_batch_set_start_device(scylla_batch *h, const double *x0_dev, const d
             for (int32_t q = 0; q < h->count; ++q)
                 if (!(omega0[q] <= 0.0 || isfinite(omega0[q]))) throw_err(-EINVAL, "non-finite omega0");
         // validated on the device before anything is written
-        if (x0_dev || y0_dev) {
-            if (h->start_flag.bytes < sizeof(int)) h->start_flag.alloc(sizeof(int));
+        if (!h->start_flag.p) {
+            h->start_flag.alloc(sizeof(int));
             HIPC(hipMemsetAsync(h->start_flag.p, 0, sizeof(int), h->stream));
-            launch_start_check(x0_dev, h->N, y0_dev, h->M, h->start_flag.as<int>(), h->stream);
-            HIPC(hipGetLastError());
-            int bad = 0;
-            HIPC(hipMemcpyAsync(&bad, h->start_flag.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-            HIPC(hipStreamSynchronize(h->stream));
-            if (bad & 1) throw_err(-EINVAL, "NaN in x0");
-            if (bad & 2) throw_err(-EINVAL, "non-finite y0");
         }
-        if (h->vbytes == 4) {
-            if (x0_dev) launch_cast<float>(x0_dev, h->x.as<float>(), h->N, h->stream);
-            if (y0_dev) launch_cast<float>(y0_dev, h->y.as<float>(), h->M, h->stream);
-            project_range<float>(h, 0, h->count, 0);
-        } else {
-            if (x0_dev) launch_cast<double>(x0_dev, h->x.as<double>(), h->N, h->stream);
-            if (y0_dev) launch_cast<double>(y0_dev, h->y.as<double>(), h->M, h->stream);
-            project_range<double>(h, 0, h->count, 0);
-        }
-        if (omega0) {
-            std::vector<InstState> st;
-            read_states(h, st);
-            for (int32_t q = 0; q < h->count; ++q)
-                if (omega0[q] > 0.0) st[q].omega = omega0[q];
-            HIPC(hipMemcpyAsync(h->st.p, st.data(), sizeof(InstState) * h->count, hipMemcpyHostToDevice,
-                                h->stream));
-        }
+        // pinned: the flag, then the weights
+        if (!h->start_host)
+            HIPC(hipHostMalloc((void **)&h->start_host, 8 + 8 * (size_t)h->count, hipHostMallocCoherent));
+        double *om = reinterpret_cast<double *>(h->start_host + 2);
+        if (omega0) memcpy(om, omega0, sizeof(double) * (size_t)h->count);
+        if (h->vbytes == 4) start_device<float>(h, x0_dev, y0_dev, omega0 ? om : nullptr);
+        else start_device<double>(h, x0_dev, y0_dev, omega0 ? om : nullptr);
         HIPC(hipGetLastError());
         HIPC(hipStreamSynchronize(h->stream));
+        const int bad = *h->start_host;
+        if (bad & 1) throw_err(-EINVAL, "NaN in x0");
+        if (bad & 2) throw_err(-EINVAL, "non-finite y0");
         return 0;
     });
 }

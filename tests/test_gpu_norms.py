@@ -1,5 +1,5 @@
 """Norms and cold-start weight of an instance, at the edges of the pieces
-they are summed in (8192 entries a piece, at most 256 pieces), after setup
+they are summed in (2048 entries a piece, at most 1024 pieces), after setup
 and after one instance of a batch got a new objective."""
 import numpy as np
 import pytest
@@ -38,7 +38,7 @@ def _expect(lp, c):
     return omega, oracle.kkt(lp, np.zeros(lp.n), np.zeros(lp.m), c=c)["rel"]
 
 
-@pytest.mark.parametrize("total", [M + 270, 8191, 8192, 8193, 16385, 2_097_153, 2_200_001])
+@pytest.mark.parametrize("total", [M + 270, 2047, 2048, 2049, 8193, 2_097_153, 2_200_001])
 def test_norms_at_piece_edges(total):
     lps = [_lp(500, 1), _lp(total - M, 2), _lp(8193 - M, 3)]
     c2 = np.random.default_rng(4).normal(size=lps[1].n) * 3.0
@@ -52,3 +52,45 @@ def test_norms_at_piece_edges(total):
                 assert r["iterations"] == 0
                 assert abs(r["omega"] - omega) <= tol * omega
                 assert abs(r["rel_kkt"] - rel) <= tol * rel
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("total", [2048, 2049, 5000])
+def test_blended_objective_at_piece_edges(prec, total):
+    """The pump's objective and its norms are made in one pass over a piece;
+    bits that end inside a byte, with and without continuous columns."""
+    lps = [_lp(500, 1), _lp(total - M, 2), _lp(1000, 3)]
+    lp = lps[1]
+    rng = np.random.default_rng(5)
+    up, ii = rng.random(lp.n) < 0.4, rng.random(lp.n) < 0.7
+    a, kappa = 0.81, 1.7
+    tol = 2 * total * np.finfo(float).eps + 1e-12
+    with pdhg.Batch(lps, precision=prec) as b:
+        for flags in (None, ii):
+            b.set_blend(1, up, a, kappa, is_int=flags)
+            c = a * kappa * lp.c + (1.0 - a) * np.where(ii if flags is not None else True, np.where(up, -1.0, 1.0), 0.0)
+            for q, r in enumerate(b.solve(tol=1e-300, iter_limit=0, autotune=0)):
+                omega, rel = _expect(lps[q], c if q == 1 else lps[q].c)
+                assert abs(r["omega"] - omega) <= tol * omega
+                assert abs(r["rel_kkt"] - rel) <= tol * rel
+
+
+@pytest.mark.parametrize("m", [1, 15, 16, 17, 33, 4096, 4101])
+def test_feasibility_flags_at_word_edges(m):
+    """One violated row or column anywhere must show: the flags are read in
+    words of 16 that need not start where an instance does."""
+    def lp(m, bad):
+        x = np.ones(m)
+        b = np.ones(m)
+        if bad is not None:
+            b[bad] = 2.0  # row bad: x_bad >= 2, bounds hold x at 1
+        return I.LP(m=m, n=m, row_ptr=np.arange(m + 1), col_idx=np.arange(m, dtype=np.int32), val=np.ones(m),
+                    c=np.ones(m), b=b, senses=np.full(m, ord("G"), dtype=np.uint8), l=np.ones(m), u=x,
+                    is_int=np.ones(m, dtype=np.uint8))
+    at = sorted({0, m // 2, m - 1, max(0, m - 2), min(m - 1, 15), min(m - 1, 16)})
+    lps = [lp(m, None)] + [v for k in at for v in (lp(m, k), lp(m, None))]
+    with pdhg.Batch(lps) as b:
+        b.solve(tol=-1.0, iter_limit=0, autotune=0)  # x = proj(0) = 1
+        want = [1] + [v for _ in at for v in (0, 1)]
+        assert b.mip_feasible().tolist() == want
+        assert b.mip_feasible(is_int=np.zeros(m * len(lps), dtype=np.uint8)).tolist() == want
