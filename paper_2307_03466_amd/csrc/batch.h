@@ -101,6 +101,7 @@ struct OrientRT {
     DevMem ptr, ent, val;
     MatView mat{};
     TilePlan plan;
+    int32_t normal_chunk = 0;  // tile size plan and its buffers are made for
     int32_t ept = 8;
     // gather-blocked layout (when chosen)
     bool blocked = false;

@@ -169,8 +169,10 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
         o.seg64.alloc(std::max<size_t>(1, o.bplan.nslots) * 8);
         o.part.alloc(std::max<size_t>(1, o.bplan.ctiles.size() / 4) * CHK * 8);
         o.lpart.alloc(8 * CHK);
-    } else {
+    } else if (o.blocked || o.normal_chunk != chunk) {
+        // (the staged and direct candidates of the tuner share this plan)
         o.blocked = false;
+        o.normal_chunk = chunk;
         plan_tiles(o.host.ptr, off, chunk, 1024, o.plan);
         seal_tiles(o.host.ptr, o.plan.tiles);
         upload(o.tiles, o.plan.tiles, h->stream);
@@ -1538,6 +1540,7 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
         }
     }
     HIPC(hipStreamSynchronize(h->stream));
+    h->stage_at = 0;
     const double solve_s = now_s() - t0;
     for (int32_t q = 0; q < h->count; ++q) {
         fill_result(h->pinned[q], results[q], solve_s, h->setup_seconds);
@@ -1569,6 +1572,34 @@ static void cast_range(scylla_batch *h, const DevMem &src, DevMem &dst, int32_t 
 
 void cast_c(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->c64, h->cv, lo, hi); }
 void cast_q(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->q64, h->qv, lo, hi); }
+
+// Host data for a copy queued on the stream: small data is copied into the
+// pinned staging buffer, so that the caller's memory is free at once and
+// nothing waits; returns where it lies (readable by the device too), or NULL
+// when it is larger than the buffer (the caller then copies and waits).
+static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
+{
+    // one buffer a handle, made by its first update
+    constexpr size_t STAGE_BYTES = (size_t)1 << 20;
+    if (bytes > STAGE_BYTES) return nullptr;
+    if (!h->stage) HIPC(hipHostMalloc((void **)&h->stage, STAGE_BYTES, hipHostMallocCoherent));
+    if (h->stage_at + bytes > STAGE_BYTES) {
+        HIPC(hipStreamSynchronize(h->stream));
+        h->stage_at = 0;
+    }
+    char *at = h->stage + h->stage_at;
+    memcpy(at, src, bytes);
+    h->stage_at += (bytes + 255) & ~(size_t)255;
+    return at;
+}
+
+// Device dst <- host src; false: src is still being read, wait for the stream.
+static bool put_staged(scylla_batch *h, void *dst, const void *src, size_t bytes)
+{
+    const char *at = stage_data(h, src, bytes);
+    HIPC(hipMemcpyAsync(dst, at ? at : src, bytes, hipMemcpyHostToDevice, h->stream));
+    return at != nullptr;
+}
 
 NormArgs norm_args(scylla_batch *h, int32_t q0)
 {
@@ -1704,11 +1735,11 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
         const int32_t lo = h->col_off[inst], len = h->col_off[inst + 1] - lo;
         for (int32_t j = 0; j < len; ++j)
             if (!isfinite(c_hat[j])) throw_err(-EINVAL, "non-finite objective");
-        HIPC(hipMemcpyAsync(h->c64.as<double>() + lo, c_hat, sizeof(double) * len, hipMemcpyHostToDevice, h->stream));
+        const bool staged = put_staged(h, h->c64.as<double>() + lo, c_hat, sizeof(double) * (size_t)len);
         cast_c(h, lo, lo + len);
         refresh_norms(h, inst, inst + 1);
         HIPC(hipGetLastError());
-        HIPC(hipStreamSynchronize(h->stream));
+        if (!staged) HIPC(hipStreamSynchronize(h->stream));
         return 0;
     });
 }
@@ -1723,15 +1754,15 @@ int scylla_batch_set_quadratic(scylla_batch *h, int32_t inst, const double *q)
                 if (!(q[j] >= 0.0) || !isfinite(q[j])) throw_err(-EINVAL, "q must be finite and >= 0");
         if (!q && !h->has_q) return 0;
         ensure_q(h);
+        bool staged = true;
         if (q) {
-            HIPC(hipMemcpyAsync(h->q64.as<double>() + lo, q, sizeof(double) * len, hipMemcpyHostToDevice,
-                                h->stream));
+            staged = put_staged(h, h->q64.as<double>() + lo, q, sizeof(double) * (size_t)len);
         } else {
             HIPC(hipMemsetAsync(h->q64.as<double>() + lo, 0, sizeof(double) * len, h->stream));
         }
         cast_q(h, lo, lo + len);
         HIPC(hipGetLastError());
-        HIPC(hipStreamSynchronize(h->stream));
+        if (!staged) HIPC(hipStreamSynchronize(h->stream));
         return 0;
     });
 }
@@ -1745,14 +1776,20 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         if (!isfinite(a) || !isfinite(kappa)) throw_err(-EINVAL, "a and kappa must be finite");
         const int32_t lo = h->col_off[inst], hi = h->col_off[inst + 1];
         const size_t nb = (size_t)(hi - lo + 7) / 8;
-        if (h->bits_tmp.bytes < nb) h->bits_tmp.alloc(nb);
-        if (int_bits && h->ibits_tmp.bytes < nb) h->ibits_tmp.alloc(nb);
-        HIPC(hipMemcpyAsync(h->bits_tmp.p, xhat_bits, nb, hipMemcpyHostToDevice, h->stream));
-        if (int_bits) HIPC(hipMemcpyAsync(h->ibits_tmp.p, int_bits, nb, hipMemcpyHostToDevice, h->stream));
-        blend_instance(h, inst, h->bits_tmp.as<uint8_t>(), int_bits ? h->ibits_tmp.as<uint8_t>() : nullptr, a, kappa);
+        // bits of up to 128k columns are read by the kernel where they are
+        // staged (5 KB for 40k columns: less than a copy's launch)
+        const bool in_place = nb <= 16384;
+        auto put = [&](DevMem &d, const uint8_t *src) -> const uint8_t * {
+            if (in_place) return reinterpret_cast<const uint8_t *>(stage_data(h, src, nb));
+            if (d.bytes < nb) d.alloc(nb);
+            HIPC(hipMemcpyAsync(d.p, src, nb, hipMemcpyHostToDevice, h->stream));
+            return d.as<uint8_t>();
+        };
+        const uint8_t *xb = put(h->bits_tmp, xhat_bits), *ib = int_bits ? put(h->ibits_tmp, int_bits) : nullptr;
+        blend_instance(h, inst, xb, ib, a, kappa);
         launch_norm_final(norm_args(h, inst), inst + 1, h->stream);
         HIPC(hipGetLastError());
-        HIPC(hipStreamSynchronize(h->stream));
+        if (!in_place) HIPC(hipStreamSynchronize(h->stream));
         return 0;
     });
 }

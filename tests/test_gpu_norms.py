@@ -94,3 +94,30 @@ def test_feasibility_flags_at_word_edges(m):
         want = [1] + [v for _ in at for v in (0, 1)]
         assert b.mip_feasible().tolist() == want
         assert b.mip_feasible(is_int=np.zeros(m * len(lps), dtype=np.uint8)).tolist() == want
+
+
+def test_updates_beyond_the_staging_buffer():
+    """Updates are staged in a 1 MiB buffer that starts over once the stream
+    has drained; larger ones are copied directly.  The last value of every
+    instance counts, whatever was staged around it."""
+    rng = np.random.default_rng(6)
+    lps = [_lp(5000, 1), _lp(140_000, 2), _lp(700, 3)]
+    with pdhg.Batch(lps, precision=pdhg.FP64) as b:
+        want = [None] * 3
+        for k in range(60):  # 60 x 40 KB
+            for q in ([0, 2] if k else [0, 1, 2]):
+                want[q] = rng.normal(size=lps[q].n)  # instance 1: 1.1 MB
+                b.set_objective(q, want[q])
+                want[q] = want[q].copy()
+        for q, r in enumerate(b.solve(tol=1e-300, iter_limit=0, autotune=0)):
+            omega, rel = _expect(lps[q], want[q])
+            assert abs(r["omega"] - omega) <= 1e-9 * omega and abs(r["rel_kkt"] - rel) <= 1e-9 * rel
+        a, kappa = 0.5, 2.0
+        for k in range(120):  # 120 x 2 x (0.6 + 0.1) KB in place, 17.5 KB bits copied
+            for q in ([0, 2] if k % 40 else [0, 1, 2]):
+                up, ii = rng.random(lps[q].n) < 0.5, rng.random(lps[q].n) < 0.5
+                b.set_blend(q, up, a, kappa, is_int=ii)
+                want[q] = a * kappa * lps[q].c + (1 - a) * np.where(ii, np.where(up, -1.0, 1.0), 0.0)
+        for q, r in enumerate(b.solve(tol=1e-300, iter_limit=0, autotune=0)):
+            omega, rel = _expect(lps[q], want[q])
+            assert abs(r["omega"] - omega) <= 1e-9 * omega and abs(r["rel_kkt"] - rel) <= 1e-9 * rel
