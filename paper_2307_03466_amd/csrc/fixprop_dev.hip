@@ -85,21 +85,91 @@ struct RowAct {
     int ni, xi;     // infinite contributions to each
 };
 
-// Activity bounds of row i over the current domains, nonzeros in row order.
-__device__ RowAct fpb_activity(const FPBArgs &a, int i)
+// A row belongs to FPL lanes, one nonzero each at a time (a DPP row, so that
+// a lane's value reaches the others as an operand modifier).  Their loads and
+// derived bounds run side by side; the sums are added lane by lane, in row
+// order, so that they round like a sequential evaluation.  Bound by the latency
+// of the chain of batches and rounds.  One lane a row waited for every
+// nonzero's loads in turn, three times over: 70 us a batch of 16 fixings on 2k
+// x 4k instances (17.7 ms a rounding of 16), now 12 us (3.2 ms); 64 20k x 40k
+// instances one fixing at a time 1.35 -> 0.23 s, 64 at a time 126 -> 32 ms.
+constexpr int FPL = 16;
+
+template <int K>
+__device__ __forceinline__ double fpb_bcast(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xf, 0xf, true);  // row_newbcast:K
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// acc + the values of lanes 0, 1, ... of the group, in that order.
+__device__ __forceinline__ double fpb_ordered_add(double acc, double v)
+{
+    acc += fpb_bcast<0>(v);
+    acc += fpb_bcast<1>(v);
+    acc += fpb_bcast<2>(v);
+    acc += fpb_bcast<3>(v);
+    acc += fpb_bcast<4>(v);
+    acc += fpb_bcast<5>(v);
+    acc += fpb_bcast<6>(v);
+    acc += fpb_bcast<7>(v);
+    acc += fpb_bcast<8>(v);
+    acc += fpb_bcast<9>(v);
+    acc += fpb_bcast<10>(v);
+    acc += fpb_bcast<11>(v);
+    acc += fpb_bcast<12>(v);
+    acc += fpb_bcast<13>(v);
+    acc += fpb_bcast<14>(v);
+    acc += fpb_bcast<15>(v);
+    return acc;
+}
+
+// Lanes of the group for which p holds, as a mask.
+__device__ __forceinline__ unsigned fpb_group_mask(bool p)
+{
+    return (unsigned)(__ballot(p) >> (threadIdx.x & 48)) & 0xffffu;
+}
+
+// This lane's nonzero of a row: value (0: none), column, domain.
+struct Ent {
+    double v, lo, hi;
+    int j;
+    bool ii;
+};
+
+__device__ __forceinline__ Ent fpb_ent(const FPBArgs &a, int e, int e1)
+{
+    Ent t{0.0, 0.0, 0.0, 0, false};
+    if (e < e1) {
+        t.v = a.val[e];
+        t.j = a.col[e];
+        t.lo = a.L[t.j];
+        t.hi = a.U[t.j];
+        t.ii = a.isint[t.j] != 0;
+    }
+    return t;
+}
+
+// Adds FPL nonzeros to the activity bounds (a term that does not count adds 0,
+// which changes no sum).
+__device__ __forceinline__ void fpb_add(RowAct &r, const Ent &t)
+{
+    const double lo = t.v > 0 ? t.lo : t.hi, hi = t.v > 0 ? t.hi : t.lo;
+    const bool on = t.v != 0.0, li = on && isinf(lo), hf = on && isinf(hi);
+    r.ni += __popc(fpb_group_mask(li));
+    r.xi += __popc(fpb_group_mask(hf));
+    r.mn = fpb_ordered_add(r.mn, on && !li ? t.v * lo : 0.0);
+    r.mx = fpb_ordered_add(r.mx, on && !hf ? t.v * hi : 0.0);
+}
+
+// Activity bounds of the row [e0, e1) over the current domains, nonzeros in
+// row order; t: the lane's nonzero of the first FPL.
+__device__ __forceinline__ RowAct fpb_activity(const FPBArgs &a, int e0, int e1, const Ent &t, int lane)
 {
     RowAct r{0.0, 0.0, 0, 0};
-    for (int e = a.rptr[i]; e < a.rptr[i + 1]; ++e) {
-        const double v = a.val[e];
-        if (v == 0.0) continue;
-        const int j = a.col[e];
-        const double lo = v > 0 ? a.L[j] : a.U[j];
-        const double hi = v > 0 ? a.U[j] : a.L[j];
-        if (isinf(lo)) r.ni++;
-        else r.mn += v * lo;
-        if (isinf(hi)) r.xi++;
-        else r.mx += v * hi;
-    }
+    fpb_add(r, t);
+    for (int e = e0 + FPL; e < e1; e += FPL) fpb_add(r, fpb_ent(a, e + lane, e1));
     return r;
 }
 
@@ -148,77 +218,92 @@ __device__ __forceinline__ bool fpb_upper_changes(bool isint, double hi, double 
     return nu < hi - 1e-9 * (1.0 + fabs(hi)) || (isinf(hi) && isfinite(nu));
 }
 
-// True if row i must be ignored against the current domains; r receives its
-// activity bounds.
-__device__ bool fpb_row_fails(const FPBArgs &a, int i, RowAct &r)
+// Folds the bounds [nl, nu] that a row derives for its nonzero t and that would
+// change the variable into the combined bounds; lists each such variable once
+// per fold stamp.
+__device__ __forceinline__ void fpb_fold(const FPBArgs &a, const Ent &t, double nl, double nu, int stamp,
+                                         int32_t *touched, int *ntouched)
 {
-    r = fpb_activity(a, i);
-    const char sn = (char)a.sense[i];
-    const double bi = a.b[i];
-    const double feas_tol = 1e-9 * (1.0 + fabs(bi));
-    if ((sn == 'G' || sn == 'E') && r.xi == 0 && r.mx < bi - feas_tol) return true;
-    if ((sn == 'L' || sn == 'E') && r.ni == 0 && r.mn > bi + feas_tol) return true;
-    for (int e = a.rptr[i]; e < a.rptr[i + 1]; ++e) {
-        const double v = a.val[e];
-        if (v == 0.0) continue;
-        const int j = a.col[e];
-        double nl, nu;
-        fpb_derive(sn, bi, r, v, a.L[j], a.U[j], a.isint[j] != 0, nl, nu);
-        if (nl > nu + 1e-9 * (1.0 + fabs(nu))) return true;
-    }
-    return false;
+    const bool tl = fpb_lower_changes(t.ii, t.lo, nl), tu = fpb_upper_changes(t.ii, t.hi, nu);
+    if (!tl && !tu) return;
+    if (tl) atomicMax(&a.cL[t.j], fpb_enc(nl));
+    if (tu) atomicMin(&a.cU[t.j], fpb_enc(nu));
+    if (atomicExch(&a.vstamp[t.j], stamp) != stamp) touched[atomicAdd(ntouched, 1)] = t.j;
 }
 
-// Folds the bounds row i derives that would change a variable into the
-// combined bounds; lists each such variable once per fold stamp.
-__device__ void fpb_fold(const FPBArgs &a, int i, const RowAct &r, int stamp, int32_t *touched, int *ntouched)
+// One active row i by its FPL lanes: ignored (for good) if it excludes b or
+// empties a domain against the current domains, else folded.
+__device__ __forceinline__ void fpb_row(const FPBArgs &a, int i, int lane, int stamp, int32_t *touched, int *ntouched,
+                                        bool test)
 {
+    const int e0 = a.rptr[i], e1 = a.rptr[i + 1];
     const char sn = (char)a.sense[i];
     const double bi = a.b[i];
-    for (int e = a.rptr[i]; e < a.rptr[i + 1]; ++e) {
-        const double v = a.val[e];
-        if (v == 0.0) continue;
-        const int j = a.col[e];
-        const double lo = a.L[j], hi = a.U[j];
-        const bool ii = a.isint[j] != 0;
-        double nl, nu;
-        fpb_derive(sn, bi, r, v, lo, hi, ii, nl, nu);
-        const bool tl = fpb_lower_changes(ii, lo, nl), tu = fpb_upper_changes(ii, hi, nu);
-        if (!tl && !tu) continue;
-        if (atomicExch(&a.vstamp[j], stamp) != stamp) touched[atomicAdd(ntouched, 1)] = j;
-        if (tl) atomicMax(&a.cL[j], fpb_enc(nl));
-        if (tu) atomicMin(&a.cU[j], fpb_enc(nu));
+    const Ent t = fpb_ent(a, e0 + lane, e1);
+    const RowAct r = fpb_activity(a, e0, e1, t, lane);
+    double nl, nu;
+    fpb_derive(sn, bi, r, t.v, t.lo, t.hi, t.ii, nl, nu);
+    if (test) {
+        const double feas_tol = 1e-9 * (1.0 + fabs(bi));
+        bool fails = (sn == 'G' || sn == 'E') && r.xi == 0 && r.mx < bi - feas_tol;
+        fails = fails || ((sn == 'L' || sn == 'E') && r.ni == 0 && r.mn > bi + feas_tol);
+        fails = fails || (t.v != 0.0 && nl > nu + 1e-9 * (1.0 + fabs(nu)));
+        for (int e = e0 + FPL; e < e1; e += FPL) {
+            const Ent q = fpb_ent(a, e + lane, e1);
+            double ql, qu;
+            fpb_derive(sn, bi, r, q.v, q.lo, q.hi, q.ii, ql, qu);
+            fails = fails || (q.v != 0.0 && ql > qu + 1e-9 * (1.0 + fabs(qu)));
+        }
+        if (fpb_group_mask(fails)) {
+            if (lane == 0) a.ign[i] = 1;
+            return;
+        }
+    }
+    if (t.v != 0.0) fpb_fold(a, t, nl, nu, stamp, touched, ntouched);
+    for (int e = e0 + FPL; e < e1; e += FPL) {
+        const Ent q = fpb_ent(a, e + lane, e1);
+        if (q.v == 0.0) continue;
+        fpb_derive(sn, bi, r, q.v, q.lo, q.hi, q.ii, nl, nu);
+        fpb_fold(a, q, nl, nu, stamp, touched, ntouched);
     }
 }
 
-// True if row i would change a variable whose combined domain is empty.
-__device__ bool fpb_conflicts(const FPBArgs &a, int i, const RowAct &r)
+// True (in every lane) if row i would change a variable whose combined domain
+// is empty.
+__device__ __forceinline__ bool fpb_conflicts(const FPBArgs &a, int i, int lane)
 {
+    const int e0 = a.rptr[i], e1 = a.rptr[i + 1];
     const char sn = (char)a.sense[i];
     const double bi = a.b[i];
-    for (int e = a.rptr[i]; e < a.rptr[i + 1]; ++e) {
-        const double v = a.val[e];
-        if (v == 0.0) continue;
-        const int j = a.col[e];
-        const double NL = fpb_dec(fpb_load(&a.cL[j])), NU = fpb_dec(fpb_load(&a.cU[j]));
+    const Ent first = fpb_ent(a, e0 + lane, e1);
+    const RowAct r = fpb_activity(a, e0, e1, first, lane);
+    bool hit = false;
+    for (int e = e0; e < e1; e += FPL) {
+        const Ent t = e == e0 ? first : fpb_ent(a, e + lane, e1);
+        if (t.v == 0.0) continue;
+        const double NL = fpb_dec(fpb_load(&a.cL[t.j])), NU = fpb_dec(fpb_load(&a.cU[t.j]));
         if (!(NL > NU + 1e-9 * (1.0 + fabs(NU)))) continue;
-        const double lo = a.L[j], hi = a.U[j];
-        const bool ii = a.isint[j] != 0;
         double nl, nu;
-        fpb_derive(sn, bi, r, v, lo, hi, ii, nl, nu);
-        if (fpb_lower_changes(ii, lo, nl) || fpb_upper_changes(ii, hi, nu)) return true;
+        fpb_derive(sn, bi, r, t.v, t.lo, t.hi, t.ii, nl, nu);
+        hit = hit || fpb_lower_changes(t.ii, t.lo, nl) || fpb_upper_changes(t.ii, t.hi, nu);
     }
-    return false;
+    return fpb_group_mask(hit) != 0;
 }
 
-// Activates the non-ignored rows of column j (once per stamp).
-__device__ __forceinline__ void fpb_activate(const FPBArgs &a, int j, int stamp, int32_t *list, int *n)
+// Activates the non-ignored rows of column j (once per stamp): entry `lane`
+// of every FPC, by FPC lanes.
+constexpr int FPC = 8;
+
+__device__ __forceinline__ void fpb_activate(const FPBArgs &a, int j, int lane, int stamp, int32_t *list, int *n)
 {
-    for (int e = a.cptr[j]; e < a.cptr[j + 1]; ++e) {
+    const int e1 = a.cptr[j + 1];
+    for (int e = a.cptr[j] + lane; e < e1; e += FPC) {
         const int i = a.crow[e];
         if (!a.ign[i] && atomicExch(&a.rstamp[i], stamp) != stamp) list[atomicAdd(n, 1)] = i;
     }
 }
+
+constexpr int FP_NT = 1024;
 
 // One workgroup per instance.  Every loop is bounded: a batch consumes at
 // least one entry of the order, a batch runs at most max_rounds rounds, the
@@ -231,9 +316,12 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
     constexpr int NW = NT / 64;
     __shared__ int s_wtot[NW];
     __shared__ int s_newp, s_nact, s_nnext, s_ntouched, s_conflict, s_bad, s_nign;
+    __shared__ int s_fixed[NT];  // columns fixed in a turn of the selection
     const int q = blockIdx.x;
     if (a.want && !a.want[q]) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int rl = tid & (FPL - 1), rg = tid / FPL, RG = NT / FPL;  // lane and group of a row
+    const int cl = tid & (FPC - 1), cg = tid / FPC, CG = NT / FPC;  // of a column
     const int r0 = a.row_off[q], r1 = a.row_off[q + 1], c0 = a.col_off[q], c1 = a.col_off[q + 1];
     const int nint = a.nint[q];
     for (int j = c0 + tid; j < c1; j += NT) {
@@ -294,10 +382,12 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
                 a.U[j] = v;
                 fpb_store(&a.cL[j], fpb_enc(v));
                 fpb_store(&a.cU[j], fpb_enc(v));
-                fpb_activate(a, j, fix_stamp, act, &s_nact);
+                s_fixed[rank] = j;
                 if (rank == need - 1) s_newp = idx + 1;
             }
             __syncthreads();
+            for (int k = cg, nk = min(total, need); k < nk; k += CG)
+                fpb_activate(a, s_fixed[k], cl, fix_stamp, act, &s_nact);
             if (total >= need) {
                 nsel = a.K;
                 p = s_newp;
@@ -319,15 +409,7 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
                 s_nnext = 0;
             }
             __syncthreads();
-            for (int t = tid; t < nact; t += NT) {
-                const int i = act[t];
-                RowAct r;
-                if (fpb_row_fails(a, i, r)) {
-                    a.ign[i] = 1;
-                    continue;
-                }
-                fpb_fold(a, i, r, fold1, touched, &s_ntouched);
-            }
+            for (int t = rg; t < nact; t += RG) fpb_row(a, act[t], rl, fold1, touched, &s_ntouched, true);
             __syncthreads();
             // is any combined domain empty?  (rare: only then are the rows
             // behind it looked for)
@@ -338,11 +420,10 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
             }
             __syncthreads();
             if (s_conflict) {
-                for (int t = tid; t < nact; t += NT) {
+                for (int t = rg; t < nact; t += RG) {
                     const int i = act[t];
                     if (a.ign[i]) continue;
-                    const RowAct r = fpb_activity(a, i);
-                    if (fpb_conflicts(a, i, r)) a.bad[i] = 1;
+                    if (fpb_conflicts(a, i, rl) && rl == 0) a.bad[i] = 1;
                 }
                 __syncthreads();
                 const int nt = s_ntouched;
@@ -363,27 +444,28 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
                 __syncthreads();
                 if (tid == 0) s_ntouched = 0;
                 __syncthreads();
-                for (int t = tid; t < nact; t += NT) {
+                for (int t = rg; t < nact; t += RG) {
                     const int i = act[t];
-                    if (a.ign[i]) continue;
-                    const RowAct r = fpb_activity(a, i);
-                    fpb_fold(a, i, r, fold2, touched, &s_ntouched);
+                    if (!a.ign[i]) fpb_row(a, i, rl, fold2, touched, &s_ntouched, false);
                 }
                 __syncthreads();
             }
             ++stamp;
             const int push = stamp;
             const int nt = s_ntouched;
-            for (int t = tid; t < nt; t += NT) {
+            for (int t = cg; t < nt; t += CG) {
                 const int j = touched[t];
                 const double lo = a.L[j], hi = a.U[j];
                 double nl = fpb_dec(fpb_load(&a.cL[j])), nu = fpb_dec(fpb_load(&a.cU[j]));
                 if (nl > nu) nl = nu = fmax(nu, lo);
-                a.L[j] = nl;
-                a.U[j] = nu;
-                fpb_store(&a.cL[j], fpb_enc(nl));
-                fpb_store(&a.cU[j], fpb_enc(nu));
-                if (nl != lo || nu != hi) fpb_activate(a, j, push, nxt, &s_nnext);
+                // (the column's lanes are of one wave: all have read by now)
+                if (cl == 0) {
+                    a.L[j] = nl;
+                    a.U[j] = nu;
+                    fpb_store(&a.cL[j], fpb_enc(nl));
+                    fpb_store(&a.cU[j], fpb_enc(nu));
+                }
+                if (nl != lo || nu != hi) fpb_activate(a, j, cl, push, nxt, &s_nnext);
             }
             __syncthreads();
             nact = s_nnext;
@@ -410,10 +492,13 @@ __global__ __launch_bounds__(NT) void k_fp_batched(const FPBArgs a)
     }
     __syncthreads();
     int nign = 0, bad = 0;
-    for (int i = r0 + tid; i < r1; i += NT) {
-        nign += a.ign[i];
+    for (int i = r0 + rg; i < r1; i += RG) {
+        const int e0 = a.rptr[i], e1 = a.rptr[i + 1];
         double s = 0.0;
-        for (int e = a.rptr[i]; e < a.rptr[i + 1]; ++e) s += a.val[e] * a.xhat[a.col[e]];
+        for (int e = e0; e < e1; e += FPL)
+            s = fpb_ordered_add(s, e + rl < e1 ? a.val[e + rl] * a.xhat[a.col[e + rl]] : 0.0);
+        if (rl != 0) continue;
+        nign += a.ign[i];
         const double bi = a.b[i], tol = 1e-6 * (1.0 + fabs(bi));
         const char sn = (char)a.sense[i];
         if (!isfinite(s)) bad = 1;  // a non-finite activity satisfies no row
@@ -567,7 +652,7 @@ void fp_batched(scylla_batch *h, const uint8_t *is_int, const double *xbar, int3
     a.K = K;
     a.max_rounds = max_rounds;
     if (count > 0) {
-        k_fp_batched<256><<<dim3((unsigned)count), dim3(256), 0, s>>>(a);
+        k_fp_batched<FP_NT><<<dim3((unsigned)count), dim3(FP_NT), 0, s>>>(a);
         HIPC(hipGetLastError());
     }
     std::vector<double> hx((size_t)N);
