@@ -103,6 +103,11 @@ struct OrientRT {
     TilePlan plan;
     int32_t normal_chunk = 0;  // tile size plan and its buffers are made for
     int32_t ept = 8;
+    // normal tiles with sorted entries (when chosen): a copy of the entries in
+    // the order of the tiles of normal_chunk nonzeros
+    bool sorted = false;
+    DevMem sent, sval, spos;
+    MatView smat{};
     // gather-blocked layout (when chosen)
     bool blocked = false;
     BlockedHost bh;  // host copy of the block pointers (entries dropped after upload)

@@ -16,6 +16,7 @@ struct MatView {
     const void *val;      // [nnz] values (format dependent) or null
     int32_t shift;        // packed: value = (int32)word >> shift
     uint32_t mask;        // packed: index = word & mask
+    const uint16_t *pos;  // [nnz] place of an entry in its tile (FMT_SORTED)
 };
 
 // Arguments of one pass (row pass = dual step over the CSR, column pass =
@@ -173,6 +174,10 @@ struct DecideArgs {
 template <class V>
 void launch_pass(const PassArgs<V> &p, int fmt, int dir, int ept, int jw, bool check, bool blocked,
                  hipStream_t s);
+// Sorted copy of the entries of normal tiles of at most 1024 * ept nonzeros:
+// every tile's entries by gathered index, ties in row order.
+void launch_sort_tiles(const MatView &M, int fmt, const int4 *tiles, int ntiles, int ept, uint32_t *ent, void *val,
+                       uint16_t *pos, hipStream_t s);
 // LDS-staged pass over staged tiles {sub0, sub1, inst, -1} (ranges of
 // sub-tiles); shmem = product buffer + largest staged vector, in bytes.  prepare = true only raises the
 // kernel's dynamic-LDS limit (call once before launching or capturing).

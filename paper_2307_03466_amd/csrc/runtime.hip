@@ -30,7 +30,7 @@ template <class V>
 PassArgs<V> orient_args(scylla_batch *h, OrientRT &o, bool check)
 {
     PassArgs<V> p{};
-    p.M = o.blocked ? o.bmat : o.mat;
+    p.M = o.blocked ? o.bmat : (o.sorted ? o.smat : o.mat);
     p.tiles = o.tiles.as<int4>();
     p.ntiles = o.ntiles();
     p.longs = o.longs.as<int4>();
@@ -137,6 +137,7 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
     const std::vector<int32_t> &off = o.row ? h->row_off : h->col_off;
     const size_t vb = (size_t)h->vbytes;
     o.ept = ept;
+    o.sorted = false;
     o.staged = false;
     o.sliced = false;
     o.direct = false;
@@ -173,7 +174,8 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
         // (the staged and direct candidates of the tuner share this plan)
         o.blocked = false;
         o.normal_chunk = chunk;
-        plan_tiles(o.host.ptr, off, chunk, 1024, o.plan);
+        // (columns are short: more of them fill a tile of 8192 nonzeros)
+        plan_tiles(o.host.ptr, off, chunk, chunk > 4096 ? (1 << TILE_ROW_BITS) - 1 : 1024, o.plan);
         seal_tiles(o.host.ptr, o.plan.tiles);
         upload(o.tiles, o.plan.tiles, h->stream);
         upload(o.longs, o.plan.longs, h->stream);
@@ -184,6 +186,40 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
     }
     ip_layout(o);
     HIPC(hipStreamSynchronize(h->stream));
+}
+
+// Whether this handle's entries can be sorted by tile: FP64, or packed words.
+bool can_sort(const scylla_batch *h, const OrientRT &o)
+{
+    return (h->fmt == FMT_F64 || h->fmt == FMT_PACKED) && o.rows > 0 && h->NNZ > 0;
+}
+
+void drop_sorted(OrientRT &o)
+{
+    o.sorted = false;
+    o.sent.release();
+    o.sval.release();
+    o.spos.release();
+}
+
+// Normal tiles with sorted entries; ept -16 / -32: 4096 / 8192 nonzeros a
+// tile, 1024 threads.
+void set_sorted(scylla_batch *h, OrientRT &o, int32_t ept)
+{
+    set_plan(h, o, 0, ept);
+    const size_t nnz = (size_t)h->NNZ;
+    if (o.sent.bytes < 4 * nnz) o.sent.alloc(4 * nnz);
+    if (o.spos.bytes < 2 * nnz) o.spos.alloc(2 * nnz);
+    if (h->fmt == FMT_F64 && o.sval.bytes < 8 * nnz) o.sval.alloc(8 * nnz);
+    launch_sort_tiles(o.mat, h->fmt, o.tiles.as<int4>(), o.ntiles(), -ept / 4, o.sent.as<uint32_t>(), o.sval.p,
+                      o.spos.as<uint16_t>(), h->stream);
+    HIPC(hipGetLastError());
+    HIPC(hipStreamSynchronize(h->stream));
+    o.smat = o.mat;
+    o.smat.ent = o.sent.as<uint32_t>();
+    if (h->fmt == FMT_F64) o.smat.val = o.sval.p;
+    o.smat.pos = o.spos.as<uint16_t>();
+    o.sorted = true;
 }
 
 // LDS-staged layout: the normal plan (used by the check) with `ept`, plus
@@ -429,7 +465,7 @@ void launch_orient(scylla_batch *h, OrientRT &o, const PassArgs<V> &p, int jw, b
     const int dir = o.row ? DIR_ROW : DIR_COL;
     // the iteration passes read the matrix with the orientation's load
     // policy (the checks, once per window, stream it)
-    const int ifmt = h->fmt | (o.cached && h->vbytes == 4 ? (int)FMT_CACHED : 0);
+    const int ifmt = h->fmt | (o.cached && h->vbytes == 4 ? (int)FMT_CACHED : 0) | (o.sorted ? (int)FMT_SORTED : 0);
     // iteration launches take the compacted tile lists when there are any
     const bool cmp = o.cmp && !check;
     auto n4 = [](const std::vector<int32_t> &v) { return (int32_t)(v.size() / 4); };
@@ -970,7 +1006,11 @@ void tune_store(const std::string &key, const TuneChoice &c)
 void apply_choice(scylla_batch *h, OrientRT &o, const int32_t *v)
 {
     const int32_t v3 = v[3] & ~64;  // bit 64: plain (cacheable) matrix loads
-    if (v[0] == -2) {
+    if (v[0] == 0 && (v3 & 128) != 0 && (v[1] == -16 || v[1] == -32) && can_sort(h, o)) {  // bit 128: sorted tiles
+        set_sorted(h, o, v[1]);
+        drop_blocked(o);
+        release_sliced(o);
+    } else if (v[0] == -2) {
         set_direct(h, o, v[1], v[2], v3);
         drop_blocked(o);
         release_sliced(o);
@@ -978,7 +1018,8 @@ void apply_choice(scylla_batch *h, OrientRT &o, const int32_t *v)
         set_staged(h, o, v[1], v[2], v3 & 3, (v3 >> 2) & 1, (v3 >> 3) & 1);
         drop_blocked(o);
     } else {
-        set_plan(h, o, v[0], v[1]);
+        // (only sorted tiles come in 8192 nonzeros)
+        set_plan(h, o, v[0], v[1] < -16 ? -16 : v[1]);
         if (v[0] == 0) drop_blocked(o);
     }
     o.cached = (v[3] & 64) != 0 && h->vbytes == 4;
@@ -995,6 +1036,7 @@ TuneChoice current_choice(scylla_batch *h)
         v[2] = o.direct ? o.dnnz : (o.staged ? o.staged_nnz : 0);
         v[3] = o.direct ? o.dlanes
                         : (o.staged ? (o.svariant | (o.sliced ? 4 : 0) | (o.shalf ? 8 : 0)) : 0);
+        if (o.sorted) v[3] = 128;
         if (o.cached) v[3] |= 64;
     }
     return c;
@@ -1061,6 +1103,30 @@ void autotune(scylla_batch *h)
                 }
             }
         }
+        // Sorted tiles, where there are enough nonzeros for the gathers to
+        // bound a pass (below, its launch does).  They cost 2 bytes more a
+        // nonzero and win where a tile's gathers share cache lines: the
+        // shorter the vector, the more.  Their 8192-nonzero tiles are not
+        // offered unsorted (slower than 4096 ones).
+        bool best_sorted = false;
+        const int plain_ept = best_ept;
+        if (can_sort(h, o) && h->NNZ >= 262144) {
+            for (int ept : {-16, -32}) {
+                const double tp = now_s();
+                set_sorted(h, o, ept);
+                const double tt = now_s();
+                const double ms = timer.time(o, 10);
+                if (trace)
+                    fprintf(stderr, "tune %s sorted ept=%d plan %.1f ms run %.3f ms (timing %.1f ms)\n",
+                            o.row ? "row" : "col", ept, (tt - tp) * 1e3, ms, (now_s() - tt) * 1e3);
+                if (ms < 0.99 * best) {
+                    best = ms;
+                    best_B = 0;
+                    best_ept = ept;
+                    best_sorted = true;
+                }
+            }
+        }
         // LDS-staged candidates when some instance's gathered vector fits,
         // whole or in up to four slices
         const std::vector<int32_t> &g = o.row ? h->col_off : h->row_off;
@@ -1077,7 +1143,7 @@ void autotune(scylla_batch *h)
                     for (int var = 0; var < 4; ++var)
                         for (int nnz : {16384, 32768, 65536, 131072}) {
                             const double tp = now_s();
-                            set_staged(h, o, best_ept, nnz, var, slice, half);
+                            set_staged(h, o, plain_ept, nnz, var, slice, half);
                             const double tt = now_s();
                             if (!o.staged || (slice && !o.sliced)) continue;
                             const double ms = timer.time(o, 10);
@@ -1109,7 +1175,7 @@ void autotune(scylla_batch *h)
             for (int lanes : {2, 4, 8, 16})
                 for (int nnz : {32768, 65536}) {
                     const double tp = now_s();
-                    set_direct(h, o, best_ept, nnz, lanes);
+                    set_direct(h, o, plain_ept, nnz, lanes);
                     const double tt = now_s();
                     if (!o.direct) continue;
                     const double ms = timer.time(o, 10);
@@ -1125,15 +1191,22 @@ void autotune(scylla_batch *h)
                 }
         }
         if (best_B == -2) {
-            set_direct(h, o, best_ept, best_dnnz, best_dl);
+            set_direct(h, o, plain_ept, best_dnnz, best_dl);
             drop_blocked(o);
+            drop_sorted(o);
             release_sliced(o);
         } else if (best_B < 0) {
-            set_staged(h, o, best_ept, best_nnz, best_var, best_slice, best_half);
+            set_staged(h, o, plain_ept, best_nnz, best_var, best_slice, best_half);
             drop_blocked(o);
+            drop_sorted(o);
+        } else if (best_sorted) {
+            set_sorted(h, o, best_ept);
+            drop_blocked(o);
+            release_sliced(o);
         } else {
             set_plan(h, o, best_B, best_ept);
             if (best_B == 0) drop_blocked(o);
+            drop_sorted(o);
             release_sliced(o);
         }
     }
@@ -1993,6 +2066,7 @@ int scylla_batch_set_layout(scylla_batch *h, int32_t row_blocks, int32_t row_ept
             o.cached = false;  // non-temporal matrix loads unless set otherwise
             int32_t B = d == 0 ? row_blocks : col_blocks, ept = d == 0 ? row_ept : col_ept;
             if (o.rows == 0 && B > 0) B = 0;
+            drop_sorted(o);
             if (B <= -6) {
                 // at least 1, 4 or 8 lanes per row (8, 4 or 2 nonzeros per lane and round)
                 set_direct(h, o, ept, 32768, B == -6 ? 1 : (B == -7 ? 4 : 8));
