@@ -1476,20 +1476,22 @@ __device__ __forceinline__ TinyLds<V> tiny_carve(unsigned char *base, int m, int
 }
 
 // A lane's share of one row (column) of the fused window, in registers: its
-// entries lane, lane + L, ... of the row, at most K, as value and 16-bit
-// element index of what they gather, counted from the start of the dynamic
-// LDS.  Slots beyond the lane's entries gather element 0, which holds zero
-// (so the sums need no masks, and 0 * 0 is added, never 0 * inf).
+// entries lane, lane + L, ... of the row, at most K, as value and byte offset
+// of what they gather in the dynamic LDS (the address of the read, so that an
+// entry costs one LDS read and one multiplication; as 16-bit element indices
+// the unpacking took most of a pass's instructions).  Slots beyond the lane's
+// entries gather offset 0, which holds zero (so the sums need no masks, and
+// 0 * 0 is added, never 0 * inf).
 template <class V, int K>
 struct LaneRow {
-    uint32_t idx[K / 2];  // two indices a word
+    uint32_t off[K];
     V val[K];
-    int wcnt;             // the most entries of any lane of the wave
+    int wcnt;  // the most entries of any lane of the wave
 };
 
 template <class V, int K>
-__device__ __forceinline__ void lane_row_load(LaneRow<V, K> &r, const int *ptr, const int *col, const V *val, int vec0,
-                                              int row, bool on, int lane, int L)
+__device__ __forceinline__ void lane_row_load(LaneRow<V, K> &r, const int *ptr, const int *col, const V *val,
+                                              uint32_t vec0, int row, bool on, int lane, int L)
 {
     const int e0 = on ? ptr[row] + lane : 0, e1 = on ? ptr[row + 1] : 0;
     int cnt = e0 < e1 ? (e1 - e0 + L - 1) / L : 0;
@@ -1497,20 +1499,19 @@ __device__ __forceinline__ void lane_row_load(LaneRow<V, K> &r, const int *ptr, 
     for (int k = 0; k < K; ++k) {
         const bool in = k < cnt;
         const int e = in ? e0 + k * L : 0;  // (element 0 is read in any case)
-        const int j = col[e];
+        const uint32_t j = (uint32_t)col[e];
         const V v = val[e];
-        const uint32_t c = in ? (uint32_t)(vec0 + j) : 0;
-        r.idx[k / 2] = k % 2 ? r.idx[k / 2] | c << 16 : c;
+        r.off[k] = in ? vec0 + j * (uint32_t)sizeof(V) : 0;
         r.val[k] = in ? v : (V)0;
     }
     for (int off = 32; off > 0; off >>= 1) cnt = max(cnt, __shfl_xor(cnt, off, 64));
     r.wcnt = __builtin_amdgcn_readfirstlane(cnt);
 }
 
-// sum of val * lds[idx] over the row's lanes; the gathers of four slots go
-// out before the first product waits.
+// sum of val * (what lds + off holds) over the row's lanes; the gathers of
+// four slots go out before the first product waits.
 template <class V, int K>
-__device__ __forceinline__ V lane_row_dot(const LaneRow<V, K> &r, const V *lds, int L)
+__device__ __forceinline__ V lane_row_dot(const LaneRow<V, K> &r, const unsigned char *lds, int L)
 {
     V s = 0;
 #pragma unroll
@@ -1518,7 +1519,7 @@ __device__ __forceinline__ V lane_row_dot(const LaneRow<V, K> &r, const V *lds, 
         if (k0 < r.wcnt) {
             V g[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) g[k] = lds[(r.idx[(k0 + k) / 2] >> (16 * (k % 2))) & 0xffff];
+            for (int k = 0; k < 4; ++k) g[k] = *reinterpret_cast<const V *>(lds + r.off[k0 + k]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) s += r.val[k0 + k] * g[k];
         }
@@ -1539,16 +1540,31 @@ __device__ __attribute__((noinline)) void tiny_adapt(InstState *S, double nx, do
 
 constexpr int TINY_NT = 1024;
 // Entries of a row that a lane can hold in registers (of the 128 a thread of
-// a 1024-thread workgroup has, an entry takes 1.5 in FP32 and 2.5 in FP64).
+// a 1024-thread workgroup has, an entry takes 2 in FP32 and 3 in FP64).
 template <class V>
 constexpr int TINY_K = sizeof(V) == 8 ? 8 : 16;
+
+// Lanes of a row (column) of the fused window, of `rows` with at most `longest`
+// entries.  A pass is bound by instruction issue: its update costs a wave
+// about as much as 20 entries, so the rows take five eighths of the threads at
+// most (two or three waves a SIMD) rather than all of them, and more lanes only
+// where their entries would not fit the registers.  (An iteration of a 200 x
+// 500 set cover with all threads 0.82 us in either precision, now 0.76 us in
+// FP64 and 0.68 us in FP32.)
+template <class V>
+__device__ __forceinline__ int tiny_lanes(int rows, int longest)
+{
+    int L = lanes_per_row<TINY_NT / 8 * 5>(rows);
+    while (L < 64 && longest > TINY_K<V> * L && rows * (L << 1) <= TINY_NT) L <<= 1;
+    return L;
+}
 
 // Scratch of the fused window in static LDS (its dynamic LDS leaves 1024 B).
 struct TinyShared {
     InstState S;
     double red[4 * TINY_NT / 64];
     double tot[NTOT + 2];
-    int nrun, restart;
+    int nrun, restart, longest[2];
     double t, s;
 };
 
@@ -1584,16 +1600,18 @@ __device__ __forceinline__ void tiny_totals(double (&acc)[NTOT], TinyShared &sh)
 // iterations) 740 us a solve; now 0.7 us and 430 us.
 template <class V, int K, bool ADAPT>
 __device__ __forceinline__ void tiny_iters_reg(const TinyArgs<V> &a, const TinyLds<V> &L, TinyShared &sh, int tid, int m,
-                                               int n)
+                                               int n, int Lc, int Lr)
 {
     constexpr int NT = TINY_NT;
-    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     const int j = tid / Lc, i = tid / Lr;
     const bool jon = j < n, ion = i < m;
+    // waves without a column (row) go straight to the barrier
+    const bool jwave = __any(jon), iwave = __any(ion);
     const bool jw = jon && (tid & (Lc - 1)) == 0, iw = ion && (tid & (Lr - 1)) == 0;
     LaneRow<V, K> C, R;
-    lane_row_load<V, K>(C, L.cptr, L.ccol, L.cval, (int)(L.y - L.zero), j, jon, tid & (Lc - 1), Lc);
-    lane_row_load<V, K>(R, L.rptr, L.rcol, L.rval, (int)(L.xb - L.zero), i, ion, tid & (Lr - 1), Lr);
+    lane_row_load<V, K>(C, L.cptr, L.ccol, L.cval, (uint32_t)((L.y - L.zero) * sizeof(V)), j, jon, tid & (Lc - 1), Lc);
+    lane_row_load<V, K>(R, L.rptr, L.rcol, L.rval, (uint32_t)((L.xb - L.zero) * sizeof(V)), i, ion, tid & (Lr - 1), Lr);
     V x = 0, c = 0, lo = 0, hi = 0, dc2 = 0, q = 0, y = 0, b = 0, dr2 = 0;
     double ax = 0.0;
     uint8_t sn = 'E';
@@ -1620,34 +1638,38 @@ __device__ __forceinline__ void tiny_iters_reg(const TinyArgs<V> &a, const TinyL
     V t = (V)sh.t, sd = (V)sh.s;
     for (int it = 0; it < nrun; ++it) {
         double nx = 0.0, ny = 0.0, inter = 0.0;
-        const V aty = lane_row_dot<V, K>(C, L.zero, Lc);
-        V xn = x + t * dc2 * (aty - c);
-        if (a.q) xn /= (V)1 + t * dc2 * q;
-        xn = xn < lo ? lo : xn;
-        xn = xn > hi ? hi : xn;
-        if (jw) L.xb[j] = ADAPT ? xn - x : (V)2 * xn - x;  // adaptive: the move dx
-        if (ADAPT && jw) {
-            const double d = (double)xn - (double)x;
-            nx = d * d / (double)dc2;
-        }
-        x = xn;
-        __syncthreads();
-        const V axb = lane_row_dot<V, K>(R, L.zero, Lr);
-        // adaptive: axb = (A dx)_i and (A x_bar)_i = (A x)_i + 2 (A dx)_i
-        const V res = ADAPT ? (V)((double)b - (ax + 2.0 * (double)axb)) : b - axb;
-        V v = y + sd * dr2 * res;
-        if (sn == 'G') v = v > (V)0 ? v : (V)0;
-        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
-        if (iw) L.y[i] = v;
-        if (ADAPT) {
-            if (iw) {
-                const double dy = (double)v - (double)y;
-                ny = dy * dy / (double)dr2;
-                inter = dy * (double)axb;
+        if (jwave) {
+            const V aty = lane_row_dot<V, K>(C, lds_raw, Lc);
+            V xn = x + t * dc2 * (aty - c);
+            if (a.q) xn /= (V)1 + t * dc2 * q;
+            xn = xn < lo ? lo : xn;
+            xn = xn > hi ? hi : xn;
+            if (jw) L.xb[j] = ADAPT ? xn - x : (V)2 * xn - x;  // adaptive: the move dx
+            if (ADAPT && jw) {
+                const double d = (double)xn - (double)x;
+                nx = d * d / (double)dc2;
             }
-            ax += (double)axb;
+            x = xn;
         }
-        y = v;
+        __syncthreads();
+        if (iwave) {
+            const V axb = lane_row_dot<V, K>(R, lds_raw, Lr);
+            // adaptive: axb = (A dx)_i and (A x_bar)_i = (A x)_i + 2 (A dx)_i
+            const V res = ADAPT ? (V)((double)b - (ax + 2.0 * (double)axb)) : b - axb;
+            V v = y + sd * dr2 * res;
+            if (sn == 'G') v = v > (V)0 ? v : (V)0;
+            else if (sn == 'L') v = v < (V)0 ? v : (V)0;
+            if (iw) L.y[i] = v;
+            if (ADAPT) {
+                if (iw) {
+                    const double dy = (double)v - (double)y;
+                    ny = dy * dy / (double)dr2;
+                    inter = dy * (double)axb;
+                }
+                ax += (double)axb;
+            }
+            y = v;
+        }
         __syncthreads();
         if (ADAPT) {
             double zero = 0.0;
@@ -1797,15 +1819,13 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
     }
     __syncthreads();
     // lanes per column and row, and whether every lane's share fits registers
-    const int Lc = lanes_per_row<NT>(n), Lr = lanes_per_row<NT>(m);
-    bool wide = n > NT || m > NT;
-    if (tid < n) wide |= L.cptr[tid + 1] - L.cptr[tid] > K * Lc;
-    if (tid < m) wide |= L.rptr[tid + 1] - L.rptr[tid] > K * Lr;
-    if (tid == 0) sh.nrun = 0;
+    if (tid < 2) sh.longest[tid] = 0;
     __syncthreads();
-    if (wide) sh.nrun = 1;
+    for (int j = tid; j < n; j += NT) atomicMax(&sh.longest[0], L.cptr[j + 1] - L.cptr[j]);
+    for (int i = tid; i < m; i += NT) atomicMax(&sh.longest[1], L.rptr[i + 1] - L.rptr[i]);
     __syncthreads();
-    const bool regs = sh.nrun == 0;
+    const int Lc = tiny_lanes<V>(n, sh.longest[0]), Lr = tiny_lanes<V>(m, sh.longest[1]);
+    const bool regs = n <= NT && m <= NT && sh.longest[0] <= K * Lc && sh.longest[1] <= K * Lr;
     int win = 0;
     for (; win < nwin; ++win) {
         // the thread index behind a barrier for the optimiser: addresses made
@@ -1817,27 +1837,30 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
         // ---- FP64 KKT check of the current point (Section 2.2)
         double acc[NTOT] = {};
         for (int i = tid / Lr; i < m; i += NT / Lr) {
+            // (operands in global memory first: they load during the sum)
+            const int gi = I.row0 + i;
+            const bool head = lr == 0;
+            const double bb = head ? a.b64[gi] : 0.0, drow = head ? a.dr64[gi] : 1.0;
+            const double yprev = head ? (double)a.yp[gi] : 0.0, axprev = head ? a.axp[gi] : 0.0;
             double ax = 0.0;
             for (int e = L.rptr[i] + lr; e < L.rptr[i + 1]; e += Lr) ax += (double)L.rval[e] * (double)L.x[L.rcol[e]];
             ax = group_sum(ax, Lr);
-            if (lr != 0) continue;
-            const double bb = a.b64[I.row0 + i];
+            if (!head) continue;
             const uint8_t sn = L.sense[i];
             double r;
             if (sn == 'G') r = fmax(bb - ax, 0.0);
             else if (sn == 'L') r = fmax(ax - bb, 0.0);
             else r = bb - ax;
             const double yy = (double)L.y[i];
-            const double dy = (yy - (double)L.yr[i]) / a.dr64[I.row0 + i];
+            const double dy = (yy - (double)L.yr[i]) / drow;
             L.ax[i] = ax;  // A x of the current point in FP64 (adaptive steps)
             acc[0] += r * r;
             acc[1] += bb * yy;
             acc[2] += dy * dy;
             // moves since the previous check (infeasibility certificates)
-            const int gi = I.row0 + i;
-            const double v = yy - (double)a.yp[gi];
+            const double v = yy - yprev;
             const double vp = sn == 'G' ? fmax(v, 0.0) : (sn == 'L' ? fmin(v, 0.0) : v);
-            const double ad = ax - a.axp[gi];
+            const double ad = ax - axprev;
             const double viol = sn == 'G' ? fmax(-ad, 0.0) : (sn == 'L' ? fmax(ad, 0.0) : ad);
             acc[7] += bb * v;
             acc[8] += (v - vp) * (v - vp);
@@ -1846,14 +1869,17 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
             a.axp[gi] = ax;
         }
         for (int j = tid / Lc; j < n; j += NT / Lc) {
+            const int g = I.col0 + j;
+            const bool head = lc == 0;
+            const double cc = head ? a.c64[g] : 0.0, lo = head ? a.l64[g] : 0.0, hi = head ? a.u64[g] : 0.0;
+            const double dcol = head ? a.dc64[g] : 1.0, qj = head && a.q64 ? a.q64[g] : 0.0;
+            const double xprev = head ? (double)a.xp[g] : 0.0, atyprev = head ? a.atyp[g] : 0.0;
             double aty = 0.0;
             for (int e = L.cptr[j] + lc; e < L.cptr[j + 1]; e += Lc) aty += (double)L.cval[e] * (double)L.y[L.ccol[e]];
             aty = group_sum(aty, Lc);
-            if (lc != 0) continue;
-            const int g = I.col0 + j;
-            const double cc = a.c64[g], lo = a.l64[g], hi = a.u64[g];
+            if (!head) continue;
             const double xq = (double)L.x[j];
-            const double qx = a.q64 ? a.q64[g] * xq : 0.0;
+            const double qx = a.q64 ? qj * xq : 0.0;
             const double gr = cc + qx - aty;
             const bool lf = isfinite(lo), uf = isfinite(hi);
             double lam;
@@ -1862,14 +1888,14 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
             else if (uf) lam = fmin(gr, 0.0);
             else lam = 0.0;
             const double rd = gr - lam;
-            const double dx = (xq - (double)L.xr[j]) / a.dc64[g];
+            const double dx = (xq - (double)L.xr[j]) / dcol;
             acc[3] += rd * rd;
             acc[4] += cc * xq + 0.5 * qx * xq;
             if (lf && lam > 0.0) acc[5] += lo * lam;
             if (uf && lam < 0.0) acc[5] += hi * lam;
             acc[5] -= 0.5 * qx * xq;
             acc[6] += dx * dx;
-            const double w = aty - a.atyp[g];
+            const double w = aty - atyprev;
             double rl;
             if (lf && uf) rl = -w;
             else if (lf) rl = fmax(-w, 0.0);
@@ -1878,7 +1904,7 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
             acc[10] += (w + rl) * (w + rl);
             if (lf && rl > 0.0) acc[11] += lo * rl;
             if (uf && rl < 0.0) acc[11] += hi * rl;
-            const double d = xq - (double)a.xp[g];
+            const double d = xq - xprev;
             acc[12] += cc * d;
             double bv;
             if (lf && uf) bv = d;
@@ -1886,7 +1912,7 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
             else if (uf) bv = fmax(d, 0.0);
             else bv = 0.0;
             acc[13] += bv * bv;
-            if (a.q64) acc[13] += (a.q64[g] * d) * (a.q64[g] * d);
+            if (a.q64) acc[13] += (qj * d) * (qj * d);
             a.xp[g] = L.x[j];
             a.atyp[g] = aty;
         }
@@ -1901,8 +1927,8 @@ __global__ __launch_bounds__(TINY_NT) void k_tiny(const TinyArgs<V> a, const int
         __syncthreads();
         if (sh.nrun == 0) break;
         if (!regs) tiny_iters_lds<V>(a, L, sh, tid, m, n);
-        else if (a.adapt) tiny_iters_reg<V, K, true>(a, L, sh, tid, m, n);
-        else tiny_iters_reg<V, K, false>(a, L, sh, tid, m, n);
+        else if (a.adapt) tiny_iters_reg<V, K, true>(a, L, sh, tid, m, n, Lc, Lr);
+        else tiny_iters_reg<V, K, false>(a, L, sh, tid, m, n, Lc, Lr);
     }
     if (tid == 0) {
         a.st[inst] = sh.S;
