@@ -230,9 +230,26 @@ struct StartArgs {
 };
 template <class V>
 void launch_start(const StartArgs<V> &a, int *host_flag, hipStream_t s);
-void launch_scale_reduce(const MatView &M, int fmt, int rows, const double *drow, const double *dcol,
-                         double *out, int mode, hipStream_t s);
-void launch_scale_apply(double *d, const double *r, int len, hipStream_t s);
+// One preconditioner round over both orientations (dr, dc: last round's, null:
+// ones; LR / LC: 16 or 64 lanes a row / column).
+struct ScaleArgs {
+    MatView R, C;
+    const double *dr, *dc;
+    double *dr_new, *dc_new;
+    int32_t M, N, LR, LC, mode, rblocks;
+};
+void launch_scale_round(ScaleArgs a, int fmt, hipStream_t s);
+// Vectors of a new handle from its FP64 data and preconditioner.
+template <class V>
+struct SetupArgs {
+    const double *c64, *l64, *u64, *b64, *dc64, *dr64;
+    V *c, *l, *u, *b, *dc2, *dr2;
+    V *x, *xbar, *xr, *xp, *y, *yr, *yp;  // cleared
+    double *ax, *axp, *atyp;              // cleared
+    int32_t M, N;
+};
+template <class V>
+void launch_setup_vectors(const SetupArgs<V> &a, hipStream_t s);
 // Norms of the instances [q0, q1) after their objective (and, with rows set,
 // their right-hand side) was written; part holds 4 doubles per instance and
 // slot, slots = the most pieces of any instance of the handle.
@@ -265,8 +282,6 @@ template <class V>
 void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s);
 void launch_norm_final(const NormArgs &a, int q1, hipStream_t s);
 void launch_norms(const NormArgs &a, int q1, hipStream_t s);
-template <class V>
-void launch_finish_diag(const double *d, V *d2, int len, hipStream_t s);
 template <class V>
 void launch_cast(const double *src, V *dst, int len, hipStream_t s);
 template <class V>

@@ -1286,13 +1286,6 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     h->xp.alloc((size_t)std::max(N, 1) * vb);
     h->axp.alloc((size_t)std::max(M, 1) * 8);
     h->atyp.alloc((size_t)std::max(N, 1) * 8);
-    for (DevMem *d : {&h->xp, &h->yp, &h->axp, &h->atyp}) HIPC(hipMemsetAsync(d->p, 0, d->bytes, s));
-    for (DevMem *d : {&h->x, &h->xbar, &h->xr}) HIPC(hipMemsetAsync(d->p, 0, d->bytes, s));
-    for (DevMem *d : {&h->y, &h->yr, &h->ax}) HIPC(hipMemsetAsync(d->p, 0, d->bytes, s));
-    launch_cast<V>(h->c64.as<double>(), h->cv.as<V>(), N, s);
-    launch_cast<V>(h->l64.as<double>(), h->lv.as<V>(), N, s);
-    launch_cast<V>(h->u64.as<double>(), h->uv.as<V>(), N, s);
-    launch_cast<V>(h->b64.as<double>(), h->b_v.as<V>(), M, s);
     // bounds shared by every column of an instance (binary problems): the
     // column pass then reads them once per workgroup, not per column
     {
@@ -1310,21 +1303,35 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     }
     // preconditioner: 10 Ruiz rounds (infinity norm) + one Pock-Chambolle
     // round (alpha = 1), FP64; A itself stays unscaled
-    std::vector<double> ones_m(M, 1.0), ones_n(N, 1.0);
-    upload(h->dr64, ones_m, s);
-    upload(h->dc64, ones_n, s);
     DevMem rt, ct;
-    rt.alloc((size_t)std::max(M, 1) * 8);
-    ct.alloc((size_t)std::max(N, 1) * 8);
-    for (int it = 0; it < 11; ++it) {
-        const int mode = it < 10 ? 0 : 1;
-        launch_scale_reduce(h->orow.mat, h->fmt, M, h->dr64.as<double>(), h->dc64.as<double>(), rt.as<double>(), mode, s);
-        launch_scale_reduce(h->ocol.mat, h->fmt, N, h->dc64.as<double>(), h->dr64.as<double>(), ct.as<double>(), mode, s);
-        launch_scale_apply(h->dr64.as<double>(), rt.as<double>(), M, s);
-        launch_scale_apply(h->dc64.as<double>(), ct.as<double>(), N, s);
+    for (DevMem *d : {&h->dr64, &rt}) d->alloc((size_t)std::max(M, 1) * 8);
+    for (DevMem *d : {&h->dc64, &ct}) d->alloc((size_t)std::max(N, 1) * 8);
+    auto lanes = [](const std::vector<int32_t> &ptr) {  // a long row wants a whole wave
+        int32_t longest = 0;
+        for (size_t i = 0; i + 1 < ptr.size(); ++i) longest = std::max(longest, ptr[i + 1] - ptr[i]);
+        return longest > 256 ? 64 : 16;
+    };
+    ScaleArgs sc{};
+    sc.R = h->orow.mat;
+    sc.C = h->ocol.mat;
+    sc.M = M;
+    sc.N = N;
+    sc.LR = lanes(h->orow.host.ptr);
+    sc.LC = lanes(h->ocol.host.ptr);
+    for (int it = 0; it < 11; ++it) {  // the last of an odd number of rounds writes the handle's vectors
+        sc.dr_new = it % 2 == 0 ? h->dr64.as<double>() : rt.as<double>();
+        sc.dc_new = it % 2 == 0 ? h->dc64.as<double>() : ct.as<double>();
+        sc.mode = it < 10 ? 0 : 1;
+        launch_scale_round(sc, h->fmt, s);
+        sc.dr = sc.dr_new;
+        sc.dc = sc.dc_new;
     }
-    launch_finish_diag<V>(h->dr64.as<double>(), h->dr2.as<V>(), M, s);
-    launch_finish_diag<V>(h->dc64.as<double>(), h->dc2.as<V>(), N, s);
+    const SetupArgs<V> sv{h->c64.as<double>(), h->l64.as<double>(), h->u64.as<double>(), h->b64.as<double>(),
+                          h->dc64.as<double>(), h->dr64.as<double>(), h->cv.as<V>(), h->lv.as<V>(), h->uv.as<V>(),
+                          h->b_v.as<V>(), h->dc2.as<V>(), h->dr2.as<V>(), h->x.as<V>(), h->xbar.as<V>(),
+                          h->xr.as<V>(), h->xp.as<V>(), h->y.as<V>(), h->yr.as<V>(), h->yp.as<V>(),
+                          h->ax.as<double>(), h->axp.as<double>(), h->atyp.as<double>(), M, N};
+    launch_setup_vectors<V>(sv, s);
     // states and norms
     std::vector<InstState> st(h->count);
     memset(st.data(), 0, sizeof(InstState) * st.size());
