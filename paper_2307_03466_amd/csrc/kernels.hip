@@ -1369,14 +1369,15 @@ __global__ __launch_bounds__(DECIDE_NT) void k_decide(const DecideArgs d)
 // without retries): eta_bar = (omega |dx~|^2 + |dy~|^2 / omega) / (2 |dy^T A dx|),
 // eta <- min((1 - (k+1)^-0.3) eta_bar, (1 + (k+1)^-0.6) eta); eta_bar is
 // infinite when the interaction is 0, and eta is kept when the move is 0.
-__device__ __forceinline__ void adapt_step(InstState &S, double nx, double ny, double inter, int64_t k)
+// p6, p3: (k+1)^-0.6 and (k+1)^-0.3.
+__device__ __forceinline__ void adapt_step(InstState &S, double nx, double ny, double inter, double p6, double p3)
 {
     if (!(nx + ny > 0.0)) return;
-    const double grow = (1.0 + pow((double)k + 1.0, -0.6)) * S.eta;
+    const double grow = (1.0 + p6) * S.eta;
     double eta = grow;
     if (inter != 0.0) {
         const double ebar = (S.omega * nx + ny / S.omega) / (2.0 * fabs(inter));
-        const double shrink = (1.0 - pow((double)k + 1.0, -0.3)) * ebar;
+        const double shrink = (1.0 - p3) * ebar;
         eta = shrink < grow ? shrink : grow;
     }
     S.eta = eta;
@@ -1385,42 +1386,51 @@ __device__ __forceinline__ void adapt_step(InstState &S, double nx, double ny, d
 }
 
 // One workgroup per instance: fixed-order FP64 sums of the iteration
-// partials of both passes (slot ranges in InstInfo::ir), then the rule.
-// Each thread issues its loads in groups of STEP_U before adding them, so
-// an instance with thousands of tiles is not bound by load latency.
-constexpr int STEP_NT = 1024, STEP_U = 8;
-
-__device__ __forceinline__ void step_sum(const double *ip, int lo, int hi, int comp, double &acc)
-{
-    for (int q0 = lo + (int)threadIdx.x; q0 < hi; q0 += STEP_NT * STEP_U) {
-        double v[STEP_U];
-#pragma unroll
-        for (int u = 0; u < STEP_U; ++u) {
-            const int q = q0 + u * STEP_NT;
-            v[u] = q < hi ? ip[2 * q + comp] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < STEP_U; ++u) acc += v[u];
-    }
-}
+// partials of both passes (slot ranges in InstInfo::ir), then the rule.  A
+// launch an iteration, bound by its latency: the partials of both passes load
+// together, STEP_U of each a thread at a time, the last wave forms the rule's
+// powers meanwhile, and the three sums share a barrier (one sum after the
+// other and the powers behind them: 6.5 us an iteration of a 5k x 10k LP).
+constexpr int STEP_NT = 1024, STEP_SUM = STEP_NT - 64, STEP_U = 4;
 
 __global__ __launch_bounds__(STEP_NT) void k_step(const StepArgs a)
 {
-    __shared__ double red2[2 * STEP_NT / 64];
-    const int inst = blockIdx.x;
+    __shared__ double red[3 * STEP_NT / 64], tot[3], pw[2];
+    const int inst = blockIdx.x, tid = threadIdx.x;
     InstState &S = a.st[inst];
     if (S.status != ST_RUN || a.jw >= S.nrun) return;
-    const InstInfo I = a.info[inst];
-    double nx = 0.0, ny = 0.0, inter = 0.0;
-    for (int r = 0; r < 3; ++r) {
-        step_sum(a.cip, I.ir[1][r][0], I.ir[1][r][1], 0, nx);
-        step_sum(a.rip, I.ir[0][r][0], I.ir[0][r][1], 0, ny);
-        step_sum(a.rip, I.ir[0][r][0], I.ir[0][r][1], 1, inter);
+    const InstInfo &I = a.info[inst];
+    double acc[3] = {};
+    if (tid >= STEP_SUM) {
+        if (tid < STEP_SUM + 2) {
+            const double k1 = (double)(S.k + a.jw + 1) + 1.0;
+            pw[tid - STEP_SUM] = pow(k1, tid == STEP_SUM ? -0.6 : -0.3);
+        }
+    } else {
+        const double2 *cip = reinterpret_cast<const double2 *>(a.cip), *rip = reinterpret_cast<const double2 *>(a.rip);
+        for (int r = 0; r < 3; ++r) {
+            const int c0 = I.ir[1][r][0], c1 = I.ir[1][r][1], r0 = I.ir[0][r][0], r1 = I.ir[0][r][1];
+            const int len = max(c1 - c0, r1 - r0);
+            for (int q0 = tid; q0 < len; q0 += STEP_SUM * STEP_U) {
+                double2 c[STEP_U], v[STEP_U];
+#pragma unroll
+                for (int u = 0; u < STEP_U; ++u) {
+                    const int q = q0 + u * STEP_SUM;
+                    c[u] = c0 + q < c1 ? cip[c0 + q] : double2{0.0, 0.0};
+                    v[u] = r0 + q < r1 ? rip[r0 + q] : double2{0.0, 0.0};
+                }
+#pragma unroll
+                for (int u = 0; u < STEP_U; ++u) {
+                    acc[0] += c[u].x;
+                    acc[1] += v[u].x;
+                    acc[2] += v[u].y;
+                }
+            }
+        }
     }
-    double zero = 0.0;
-    block_sum2<STEP_NT>(nx, zero, red2);
-    block_sum2<STEP_NT>(ny, inter, red2);
-    if (threadIdx.x == 0) adapt_step(S, nx, ny, inter, S.k + a.jw + 1);
+    block_sums<STEP_NT, 3>(acc, red, tot);
+    __syncthreads();
+    if (tid == 0) adapt_step(S, tot[0], tot[1], tot[2], pw[0], pw[1]);
 }
 
 // --------------------------------------------- fused window (tiny instances)
@@ -1535,7 +1545,7 @@ __device__ __attribute__((noinline)) void tiny_decide(InstState *S, const double
 
 __device__ __attribute__((noinline)) void tiny_adapt(InstState *S, double nx, double ny, double inter, int64_t k)
 {
-    adapt_step(*S, nx, ny, inter, k);
+    adapt_step(*S, nx, ny, inter, pow((double)k + 1.0, -0.6), pow((double)k + 1.0, -0.3));
 }
 
 constexpr int TINY_NT = 1024;
@@ -2456,6 +2466,9 @@ static void dispatch_pass(const PassArgs<V> &p, int ept, int jw, bool check, hip
         break;
     case -16:
         check ? launch_check_t<V, FMT, DIR, 1024, 4>(p, s) : launch_pass_t<V, FMT, DIR, 1024, 4>(p, jw, s);
+        break;
+    case 1:
+        check ? launch_check_t<V, FMT, DIR, 256, 1>(p, s) : launch_pass_t<V, FMT, DIR, 256, 1>(p, jw, s);
         break;
     case 2:
         check ? launch_check_t<V, FMT, DIR, 256, 2>(p, s) : launch_pass_t<V, FMT, DIR, 256, 2>(p, jw, s);

@@ -1059,7 +1059,7 @@ void autotune(scylla_batch *h)
         h->tuned = true;
         return;
     }
-    const int epts[6] = {2, 4, 8, 16, -8, -16};
+    const int epts[7] = {1, 2, 4, 8, 16, -8, -16};
     // The matrix load policy first, on the initial layout (both passes
     // timed together): whether an iteration's data fits the device's
     // last-level cache hardly depends on the layout, and the layouts are
@@ -1089,6 +1089,8 @@ void autotune(scylla_batch *h)
         }
         for (int B : Bs) {
             for (int ept : epts) {
+                // 256-nonzero tiles where larger ones leave compute units idle
+                if (ept == 1 && (B > 0 || h->NNZ > 262144)) continue;
                 const double tp = now_s();
                 set_plan(h, o, B, ept);
                 const double tt = now_s();

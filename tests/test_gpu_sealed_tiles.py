@@ -34,3 +34,20 @@ def test_tiles_at_their_limits(ept, prec):
             b.solve(tol=-1.0, iter_limit=100, restarts=0, fused_window=0, autotune=0)
             for k, q in enumerate(part):
                 assert parity_err(*b.solution(k), refs[q].x, refs[q].y) <= bar
+
+
+# step-size partials of about 980 and 3910 tiles: beyond one turn of the 960
+# summing threads, and beyond one round of four turns
+@pytest.mark.parametrize("m", [50_000, 200_000])
+def test_step_sums_beyond_a_round(m):
+    from paper_2307_03466_amd import instances as I
+    lp = I.general_lp(m, 2 * m, seed=m)
+    ref = oracle.pdhg(lp, tol=-1.0, iter_limit=3, restarts=False, adaptive=True)
+    with pdhg.Batch([lp], precision=0) as b:
+        b.set_layout(0, 2, 0, 2)
+        b.solve(tol=-1.0, iter_limit=3, restarts=0, adaptive=1, autotune=0)
+        x, y = b.solution(0)
+        b.solve(tol=-1.0, iter_limit=3, restarts=0, adaptive=1, autotune=0)
+        x2, y2 = b.solution(0)
+    assert parity_err(x, y, ref.x, ref.y) <= 1e-10  # the sums of the first steps, before they amplify rounding
+    assert (x == x2).all() and (y == y2).all()

@@ -1,5 +1,5 @@
 """Normal tiles with their entries sorted by what they gather (4096 or 8192
-nonzeros): pinned through the tuning cache file, since the layout call offers
+nonzeros), and those of 256 nonzeros: pinned through the tuning cache file, since the layout call offers
 the unsorted ones only.  The products keep their places, so 4096-nonzero
 sorted tiles give the unsorted ones' bits; both are checked against the
 oracle, at tile edges, with long rows, empty rows, one instance and a batch,
@@ -45,7 +45,7 @@ for lps in BATCHES:
         with pdhg.Batch(lps, precision=prec) as b:
             b.solve(**KW)
             info = b.info()
-            chunk = 8192 if want == -32 else 4096
+            chunk = {-32: 8192, 1: 256}.get(want, 4096)
             assert info["row_chunk"] == info["col_chunk"] == chunk, info
             got = [b.solution(q) for q in range(len(lps))]
         for q in range(len(lps)):
@@ -78,9 +78,10 @@ def keys(tmp_path_factory):
 
 
 # ept, flags of a sorted choice (128), with plain loads (64); -32 without the
-# flag is no choice: its passes run 4096-nonzero tiles
+# flag is no choice: its passes run 4096-nonzero tiles; 1: the 256-nonzero
+# tiles of small LPs, which the layout call does not offer either
 @pytest.mark.parametrize("ept,flags,want", [(-16, 128, -16), (-32, 128, -32), (-16, 192, -16), (-32, 192, -32),
-                                            (-32, 0, -16)])
+                                            (-32, 0, -16), (1, 0, 1), (1, 64, 1)])
 def test_sorted_tiles(keys, tmp_path, ept, flags, want):
     path = tmp_path / "second.txt"
     path.write_text("".join(f"{k} 0 {ept} 0 {flags} 0 {ept} 0 {flags}\n" for k in keys))
