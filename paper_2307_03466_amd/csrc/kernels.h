@@ -262,7 +262,7 @@ __host__ __device__ inline int norm_blocks(int m, int n)
 struct NormArgs {
     const InstInfo *info;
     const double *b;
-    double *c;  // (written by launch_blend only)
+    double *c;  // (written by launch_blend and launch_objective only)
     const double *dr, *dc;
     InstState *st;
     double *part;
@@ -280,7 +280,13 @@ struct BlendArgs {
 // instances must follow (launch_norms does both for objectives in place).
 template <class V>
 void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s);
+// The same for an objective read from device-readable memory.
+template <class V>
+void launch_objective(const NormArgs &a, const double *src, V *cv, hipStream_t s);
 void launch_norm_final(const NormArgs &a, int q1, hipStream_t s);
+// dst = src and its copy in the path precision.
+template <class V>
+void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s);
 void launch_norms(const NormArgs &a, int q1, hipStream_t s);
 template <class V>
 void launch_cast(const double *src, V *dst, int len, hipStream_t s);

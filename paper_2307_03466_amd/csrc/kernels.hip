@@ -2147,10 +2147,40 @@ __device__ __forceinline__ void blend_sums(const BlendArgs &B, double *c, const 
     }
 }
 
+// The same over a new objective, read where the host staged it (src counts
+// from j0) and written on the way: a copy, a cast and the sums in one launch.
+template <class V>
+__device__ __forceinline__ void staged_sums(const double *src, double *c, V *cv, const double *d, int j0, int lo, int hi,
+                                            double &s, double &t)
+{
+    for (int i0 = lo + (int)threadIdx.x; i0 < hi; i0 += 4 * 256) {
+        double v[4], w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = i0 + u * 256;
+            v[u] = j < hi ? src[j - j0] : 0.0;
+            w[u] = j < hi ? d[j] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = i0 + u * 256;
+            if (j >= hi) continue;
+            c[j] = v[u];
+            cv[j] = (V)v[u];
+            const double x = w[u] * v[u];
+            s += v[u] * v[u];
+            t += x * x;
+        }
+    }
+}
+
+// How a norm launch gets the objective.
+enum { NORM_KEEP = 0, NORM_BLEND = 1, NORM_STAGED = 2 };
+
 // Workgroup slots * i + piece: one piece of instance q0 + i, partial sums to
 // part[4 (slots q + piece)], or the norms themselves when it is the only one.
-// BLEND: the objective is written first (V: path precision).
-template <class V, bool BLEND>
+// NORM_BLEND / NORM_STAGED: the objective is written first (V: path precision).
+template <class V, int SRC>
 __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const BlendArgs B)
 {
     __shared__ double red[4 * 4], sum[4];
@@ -2164,7 +2194,9 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
         norm_sums(a.b, a.dr, I.row0 + (int)((int64_t)m * blk / nb), I.row0 + (int)((int64_t)m * (blk + 1) / nb),
                   acc[0], acc[1]);
     const int lo = I.col0 + (int)((int64_t)n * blk / nb), hi = I.col0 + (int)((int64_t)n * (blk + 1) / nb);
-    if constexpr (BLEND) blend_sums<V>(B, a.c, a.dc, I.col0, lo, hi, acc[2], acc[3]);
+    if constexpr (SRC == NORM_BLEND) blend_sums<V>(B, a.c, a.dc, I.col0, lo, hi, acc[2], acc[3]);
+    else if constexpr (SRC == NORM_STAGED)
+        staged_sums<V>(B.c_orig, a.c, (V *)B.cv, a.dc, I.col0, lo, hi, acc[2], acc[3]);
     else norm_sums(a.c, a.dc, lo, hi, acc[2], acc[3]);
     block_sums<256, 4>(acc, red, nb == 1 ? sum : a.part + 4 * ((size_t)a.slots * q + blk));
     if (nb > 1) return;
@@ -2757,7 +2789,7 @@ void launch_setup_vectors(const SetupArgs<V> &a, hipStream_t s)
 void launch_norms(const NormArgs &a, int q1, hipStream_t s)
 {
     if (q1 <= a.q0) return;
-    hipLaunchKernelGGL((k_norm_part<double, false>), dim3((unsigned)a.slots * (unsigned)(q1 - a.q0)), dim3(256), 0, s, a,
+    hipLaunchKernelGGL((k_norm_part<double, NORM_KEEP>), dim3((unsigned)a.slots * (unsigned)(q1 - a.q0)), dim3(256), 0, s, a,
                        BlendArgs{});
     launch_norm_final(a, q1, s);
 }
@@ -2765,7 +2797,34 @@ void launch_norms(const NormArgs &a, int q1, hipStream_t s)
 template <class V>
 void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_norm_part<V, true>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+    hipLaunchKernelGGL((k_norm_part<V, NORM_BLEND>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+}
+
+template <class V>
+void launch_objective(const NormArgs &a, const double *src, V *cv, hipStream_t s)
+{
+    BlendArgs b{};
+    b.c_orig = src;
+    b.cv = cv;
+    hipLaunchKernelGGL((k_norm_part<V, NORM_STAGED>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+}
+
+// dst = src, dst_v = src in the path precision.
+template <class V>
+__global__ __launch_bounds__(256) void k_put(const double *src, double *dst, V *dst_v, int len)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= len) return;
+    const double v = src[i];
+    dst[i] = v;
+    dst_v[i] = (V)v;
+}
+
+template <class V>
+void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s)
+{
+    if (len > 0)
+        hipLaunchKernelGGL(k_put<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, src, dst, dst_v, len);
 }
 
 void launch_norm_final(const NormArgs &a, int q1, hipStream_t s)
@@ -2828,6 +2887,8 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
     template void launch_project<V>(V *, const V *, const V *, int, int, V *, const uint8_t *, int, int, \
                                     int, hipStream_t);                                                 \
     template void launch_blend<V>(const NormArgs &, const BlendArgs &, hipStream_t);                   \
+    template void launch_objective<V>(const NormArgs &, const double *, V *, hipStream_t);             \
+    template void launch_put<V>(const double *, double *, V *, int, hipStream_t);                      \
     template void launch_mip_check<V>(const MatView &, int, int, int, int, const InstInfo *, const V *, \
                                       const double *, const uint8_t *, const double *, const double *, \
                                       const uint8_t *, double, uint8_t *, uint8_t *, uint8_t *, hipStream_t);

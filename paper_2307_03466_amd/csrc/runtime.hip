@@ -1675,14 +1675,6 @@ static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
     return at;
 }
 
-// Device dst <- host src; false: src is still being read, wait for the stream.
-static bool put_staged(scylla_batch *h, void *dst, const void *src, size_t bytes)
-{
-    const char *at = stage_data(h, src, bytes);
-    HIPC(hipMemcpyAsync(dst, at ? at : src, bytes, hipMemcpyHostToDevice, h->stream));
-    return at != nullptr;
-}
-
 NormArgs norm_args(scylla_batch *h, int32_t q0)
 {
     return {h->info.as<InstInfo>(), h->b64.as<double>(),   h->c64.as<double>(),       h->dr64.as<double>(),
@@ -1817,11 +1809,22 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
         const int32_t lo = h->col_off[inst], len = h->col_off[inst + 1] - lo;
         for (int32_t j = 0; j < len; ++j)
             if (!isfinite(c_hat[j])) throw_err(-EINVAL, "non-finite objective");
-        const bool staged = put_staged(h, h->c64.as<double>() + lo, c_hat, sizeof(double) * (size_t)len);
-        cast_c(h, lo, lo + len);
-        refresh_norms(h, inst, inst + 1);
+        // read by the kernel where it is staged (16 objectives and Hessians
+        // of 10k columns with copies and casts of their own: 0.18 ms more)
+        const char *at = stage_data(h, c_hat, sizeof(double) * (size_t)len);
+        if (at) {
+            const double *src = reinterpret_cast<const double *>(at);
+            if (h->vbytes == 4) launch_objective<float>(norm_args(h, inst), src, h->cv.as<float>(), h->stream);
+            else launch_objective<double>(norm_args(h, inst), src, h->cv.as<double>(), h->stream);
+            launch_norm_final(norm_args(h, inst), inst + 1, h->stream);
+        } else {
+            HIPC(hipMemcpyAsync(h->c64.as<double>() + lo, c_hat, sizeof(double) * (size_t)len, hipMemcpyHostToDevice,
+                                h->stream));
+            cast_c(h, lo, lo + len);
+            refresh_norms(h, inst, inst + 1);
+        }
         HIPC(hipGetLastError());
-        if (!staged) HIPC(hipStreamSynchronize(h->stream));
+        if (!at) HIPC(hipStreamSynchronize(h->stream));
         return 0;
     });
 }
@@ -1836,15 +1839,22 @@ int scylla_batch_set_quadratic(scylla_batch *h, int32_t inst, const double *q)
                 if (!(q[j] >= 0.0) || !isfinite(q[j])) throw_err(-EINVAL, "q must be finite and >= 0");
         if (!q && !h->has_q) return 0;
         ensure_q(h);
-        bool staged = true;
-        if (q) {
-            staged = put_staged(h, h->q64.as<double>() + lo, q, sizeof(double) * (size_t)len);
+        const char *at = q ? stage_data(h, q, sizeof(double) * (size_t)len) : nullptr;
+        if (at) {
+            const double *src = reinterpret_cast<const double *>(at);
+            if (h->vbytes == 4)
+                launch_put<float>(src, h->q64.as<double>() + lo, h->qv.as<float>() + lo, len, h->stream);
+            else
+                launch_put<double>(src, h->q64.as<double>() + lo, h->qv.as<double>() + lo, len, h->stream);
         } else {
-            HIPC(hipMemsetAsync(h->q64.as<double>() + lo, 0, sizeof(double) * len, h->stream));
+            if (q)
+                HIPC(hipMemcpyAsync(h->q64.as<double>() + lo, q, sizeof(double) * (size_t)len, hipMemcpyHostToDevice,
+                                    h->stream));
+            else HIPC(hipMemsetAsync(h->q64.as<double>() + lo, 0, sizeof(double) * (size_t)len, h->stream));
+            cast_q(h, lo, lo + len);
         }
-        cast_q(h, lo, lo + len);
         HIPC(hipGetLastError());
-        if (!staged) HIPC(hipStreamSynchronize(h->stream));
+        if (q && !at) HIPC(hipStreamSynchronize(h->stream));
         return 0;
     });
 }
