@@ -2618,8 +2618,15 @@ void launch_pass(const PassArgs<V> &p, int fmt, int dir, int ept, int jw, bool c
         if (fmt & FMT_SORTED) {
             // (packed words in FP32, or FP64: the formats that are sorted)
             if constexpr (sizeof(V) == 8) {
-                if (dir == DIR_COL) dispatch_sorted<V, FMT_F64 | FMT_SORTED, DIR_COL>(p, ept, jw, check, s);
-                else dispatch_sorted<V, FMT_F64 | FMT_SORTED, DIR_ROW>(p, ept, jw, check, s);
+                if (fmt & FMT_CACHED) {
+                    constexpr int F = FMT_F64 | FMT_CACHED | FMT_SORTED;
+                    if (dir == DIR_COL) dispatch_sorted<V, F, DIR_COL>(p, ept, jw, check, s);
+                    else dispatch_sorted<V, F, DIR_ROW>(p, ept, jw, check, s);
+                } else {
+                    constexpr int F = FMT_F64 | FMT_SORTED;
+                    if (dir == DIR_COL) dispatch_sorted<V, F, DIR_COL>(p, ept, jw, check, s);
+                    else dispatch_sorted<V, F, DIR_ROW>(p, ept, jw, check, s);
+                }
             } else if (fmt & FMT_CACHED) {
                 constexpr int F = FMT_PACKED | FMT_CACHED | FMT_SORTED;
                 if (dir == DIR_COL) dispatch_sorted<V, F, DIR_COL>(p, ept, jw, check, s);
@@ -2630,8 +2637,14 @@ void launch_pass(const PassArgs<V> &p, int fmt, int dir, int ept, int jw, bool c
                 else dispatch_sorted<V, F, DIR_ROW>(p, ept, jw, check, s);
             }
         } else if constexpr (sizeof(V) == 8) {
-            if (dir == DIR_COL) dispatch_pass<V, FMT_F64, DIR_COL>(p, ept, jw, check, s);
-            else dispatch_pass<V, FMT_F64, DIR_ROW>(p, ept, jw, check, s);
+            if (fmt & FMT_CACHED) {
+                constexpr int F = FMT_F64 | FMT_CACHED;
+                if (dir == DIR_COL) dispatch_pass<V, F, DIR_COL>(p, ept, jw, check, s);
+                else dispatch_pass<V, F, DIR_ROW>(p, ept, jw, check, s);
+            } else {
+                if (dir == DIR_COL) dispatch_pass<V, FMT_F64, DIR_COL>(p, ept, jw, check, s);
+                else dispatch_pass<V, FMT_F64, DIR_ROW>(p, ept, jw, check, s);
+            }
         } else {
             fp32_format(fmt, [&](auto fc) {
                 constexpr int F = decltype(fc)::value;
