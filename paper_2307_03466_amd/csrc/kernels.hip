@@ -258,6 +258,7 @@ __device__ __forceinline__ void stage_products(const MatView &M, const GV *__res
 template <class V>
 struct RowOps {
     V own, rhs, diag2, lo, hi, q;
+    V avg;      // running mean (restart to the average)
     double ax;  // running A x (adaptive steps)
     uint8_t sense;
 };
@@ -288,6 +289,7 @@ __device__ __forceinline__ void load_ops(const PassArgs<V> &p, int i, RowOps<V> 
     o.own = p.own[i];
     o.rhs = p.rhs[i];
     o.diag2 = p.diag2[i];
+    if (p.avg) o.avg = p.avg[i];
     if (DIR == DIR_COL) {
         if (ib.uni) {
             o.lo = ib.lo;
@@ -321,9 +323,9 @@ __device__ __forceinline__ V avg_count(const PassArgs<V> &p, const InstState &S,
 // Folds the new iterate value v of entry i into the running mean (the first
 // iterate after a restart starts it).
 template <class V>
-__device__ __forceinline__ void fold_avg(const PassArgs<V> &p, int i, V v, V acnt)
+__device__ __forceinline__ void fold_avg(const PassArgs<V> &p, int i, V v, V avg, V acnt)
 {
-    if (acnt > (V)0) p.avg[i] = acnt == (V)1 ? v : p.avg[i] + (v - p.avg[i]) / acnt;
+    if (acnt > (V)0) p.avg[i] = acnt == (V)1 ? v : avg + (v - avg) / acnt;
 }
 
 template <class V, int DIR>
@@ -338,7 +340,7 @@ __device__ __forceinline__ void apply_ops(const PassArgs<V> &p, int i, V sum, V 
         if (copy_ref) p.own_ref[i] = o.own;
         p.bar[i] = p.adapt ? xn - o.own : (V)2 * xn - o.own;
         p.own[i] = xn;
-        fold_avg(p, i, xn, acnt);
+        fold_avg(p, i, xn, o.avg, acnt);
         if (p.adapt) {
             const double d = (double)xn - (double)o.own;
             ip[0] += d * d / (double)o.diag2;
@@ -351,7 +353,7 @@ __device__ __forceinline__ void apply_ops(const PassArgs<V> &p, int i, V sum, V 
         else if (o.sense == 'L') v = v < (V)0 ? v : (V)0;
         if (copy_ref) p.own_ref[i] = o.own;
         p.own[i] = v;
-        fold_avg(p, i, v, acnt);
+        fold_avg(p, i, v, o.avg, acnt);
         if (p.adapt) {
             const double dy = (double)v - (double)o.own;
             ip[0] += dy * dy / (double)o.diag2;
