@@ -203,14 +203,22 @@ void drop_sorted(OrientRT &o)
 }
 
 // Normal tiles with sorted entries; ept -16 / -32: 4096 / 8192 nonzeros a
-// tile, 1024 threads.
-void set_sorted(scylla_batch *h, OrientRT &o, int32_t ept)
+// tile, 1024 threads.  False (and nothing set) when the device has no room for
+// the second copy of the entries, which a handle works without.
+bool set_sorted(scylla_batch *h, OrientRT &o, int32_t ept)
 {
-    set_plan(h, o, 0, ept);
     const size_t nnz = (size_t)h->NNZ;
-    if (o.sent.bytes < 4 * nnz) o.sent.alloc(4 * nnz);
-    if (o.spos.bytes < 2 * nnz) o.spos.alloc(2 * nnz);
-    if (h->fmt == FMT_F64 && o.sval.bytes < 8 * nnz) o.sval.alloc(8 * nnz);
+    try {
+        if (o.sent.bytes < 4 * nnz) o.sent.alloc(4 * nnz);
+        if (o.spos.bytes < 2 * nnz) o.spos.alloc(2 * nnz);
+        if (h->fmt == FMT_F64 && o.sval.bytes < 8 * nnz) o.sval.alloc(8 * nnz);
+    } catch (const Err &e) {
+        if (e.code != -ENOMEM) throw;
+        (void)hipGetLastError();
+        drop_sorted(o);
+        return false;
+    }
+    set_plan(h, o, 0, ept);
     launch_sort_tiles(o.mat, h->fmt, o.tiles.as<int4>(), o.ntiles(), -ept / 4, o.sent.as<uint32_t>(), o.sval.p,
                       o.spos.as<uint16_t>(), h->stream);
     HIPC(hipGetLastError());
@@ -220,6 +228,7 @@ void set_sorted(scylla_batch *h, OrientRT &o, int32_t ept)
     if (h->fmt == FMT_F64) o.smat.val = o.sval.p;
     o.smat.pos = o.spos.as<uint16_t>();
     o.sorted = true;
+    return true;
 }
 
 // LDS-staged layout: the normal plan (used by the check) with `ept`, plus
@@ -1009,8 +1018,8 @@ void tune_store(const std::string &key, const TuneChoice &c)
 void apply_choice(scylla_batch *h, OrientRT &o, const int32_t *v)
 {
     const int32_t v3 = v[3] & ~64;  // bit 64: plain (cacheable) matrix loads
-    if (v[0] == 0 && (v3 & 128) != 0 && (v[1] == -16 || v[1] == -32) && can_sort(h, o)) {  // bit 128: sorted tiles
-        set_sorted(h, o, v[1]);
+    // bit 128: sorted tiles
+    if (v[0] == 0 && (v3 & 128) != 0 && (v[1] == -16 || v[1] == -32) && can_sort(h, o) && set_sorted(h, o, v[1])) {
         drop_blocked(o);
         release_sliced(o);
     } else if (v[0] == -2) {
@@ -1118,7 +1127,7 @@ void autotune(scylla_batch *h)
         if (can_sort(h, o) && h->NNZ >= 262144) {
             for (int ept : {-16, -32}) {
                 const double tp = now_s();
-                set_sorted(h, o, ept);
+                if (!set_sorted(h, o, ept)) break;
                 const double tt = now_s();
                 const double ms = timer.time(o, 10);
                 if (trace)
@@ -1577,7 +1586,8 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
         // 200 x 500 set cover): the host's turn between launches then costs
         // under 1 %, and the GPU is not held for long.  With a time limit one
         // window, so that it is seen after each.
-        const int64_t per = p->time_limit_s > 0.0 ? 1 : std::max(1, 4096 / R), checks = (lim + R - 1) / R + 1;
+        const int64_t per = p->time_limit_s > 0.0 ? 1 : std::max(1, 4096 / R);
+        const int64_t checks = lim / R + (lim % R != 0 ? 2 : 1);
         for (int64_t w = 0; w < checks; w += per) {
             launch_windows_tiny(h, R, (int32_t)std::min(per, checks - w));
             HIPC(hipGetLastError());

@@ -40,3 +40,13 @@ def test_limits_around_windows(limit, fused):
 @pytest.mark.parametrize("limit", [4095, 4096, 4097, 4161])
 def test_limits_around_fused_launches(limit):
     _check(I.set_cover(30, 70, seed=6), limit, 1)
+
+
+@pytest.mark.parametrize("fused", [0, 1])
+def test_largest_iteration_limit(fused):
+    """No limit, as large as the parameter holds: ends at its tolerance."""
+    lp = I.set_cover(30, 70, seed=6)
+    with pdhg.Batch([lp], precision=pdhg.FP64) as b:
+        r = b.solve(tol=1e-4, iter_limit=2**63 - 1, fused_window=fused, autotune=0)[0]
+        x, y = b.solution(0)
+    assert r["status"] == pdhg.OPTIMAL and oracle.kkt(lp, x, y)["rel"] <= 1e-4 * (1 + 1e-6)
