@@ -333,7 +333,8 @@ int scylla_batch_get_info(scylla_batch *h, scylla_batch_info *info);
  * 0): 1 = plain loads, which the device's last-level (Infinity) cache
  * keeps across iterations when an iteration's data fits in it, 0 =
  * non-temporal loads that stream past the caches.  Results do not depend
- * on it.  Call after scylla_batch_set_layout (which resets it).  Returns 0,
+ * on it.  (For FP64 handles this call keeps non-temporal loads; the tuner may
+ * choose plain ones for normal tiles.)  Call after scylla_batch_set_layout (which resets it).  Returns 0,
  * or -EINVAL (NULL handle, flags not 0 or 1). */
 int scylla_batch_set_cached_loads(scylla_batch *h, int32_t row_cached, int32_t col_cached);
 
