@@ -189,6 +189,7 @@ struct scylla_batch {
     DevMem c64, corig64, l64, u64, b64, dr64, dc64;
     DevMem st, info;
     DevMem norm_part;       // partial sums of the norms
+    DevMem norm_done;       // pieces summed so far, per instance
     int32_t norm_slots = 1; // most pieces of an instance's norms
     DevMem ax;              // running A x of the row pass (adaptive steps)
     DevMem ibnd;            // [2 * count] (l, u) shared by all columns of an
@@ -305,8 +306,8 @@ void cast_q(scylla_batch *h, int32_t lo, int32_t hi);
 // objective (rows: and right-hand side).
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows = false);
 NormArgs norm_args(scylla_batch *h, int32_t q0);
-// Pump objective and partial norms of instance inst from device-readable
-// rounding and integer bits; launch_norm_final must follow.
+// Pump objective and norms of instance inst from device-readable rounding and
+// integer bits.
 void blend_instance(scylla_batch *h, int32_t inst, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa);
 
 // ---- defined in fixprop_dev.hip

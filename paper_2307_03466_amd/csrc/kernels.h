@@ -266,6 +266,7 @@ struct NormArgs {
     const double *dr, *dc;
     InstState *st;
     double *part;
+    int32_t *done;  // [count] pieces finished, 0 between launches
     int32_t slots, q0, rows;
 };
 // Pump objective of instance q0: original objective, rounding bits and integer
@@ -276,14 +277,12 @@ struct BlendArgs {
     double a, kappa;
     void *cv;
 };
-// Objective and partial norms of instance a.q0; launch_norm_final over the
-// instances must follow (launch_norms does both for objectives in place).
+// Objective and norms of instance a.q0.
 template <class V>
 void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s);
 // The same for an objective read from device-readable memory.
 template <class V>
 void launch_objective(const NormArgs &a, const double *src, V *cv, hipStream_t s);
-void launch_norm_final(const NormArgs &a, int q1, hipStream_t s);
 // dst = src and its copy in the path precision.
 template <class V>
 void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s);

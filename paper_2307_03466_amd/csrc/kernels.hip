@@ -2083,14 +2083,16 @@ __global__ __launch_bounds__(256) void k_setup_vectors(const SetupArgs<V> a)
 // One workgroup per instance read a 300k x 600k LP's 14 MB in 1.05 ms and a
 // 20k x 40k instance's in 75 us (latency of one CU's loads), so an instance
 // is cut into norm_blocks() pieces of about NORM_CHUNK entries, one workgroup
-// each, whose partial sums a second kernel adds in a fixed order.  With that,
+// each, and the last of them adds the partial sums in a fixed order.  With that,
 // and the sums of the instances that changed only, a new objective and a warm
 // re-solve of 64 iterations of the 300k x 600k LP went from 4.80 to 3.73 ms,
 // 64 objective updates and a re-solve of 64 20k x 40k instances from 11.5 to
 // 7.4 ms (pieces of 8192; at 2048, with the pump's objective made in the same
-// launch, the latter's update kernels take 0.4 ms less again).  The pieces depend on the instance alone, so a batch and a single
-// solve agree bit for bit.  An instance of one piece is finished by its only
-// workgroup.
+// launch, the latter's update kernels take 0.4 ms less again; without a second
+// launch for the sum of the pieces 4.80 -> 4.68 ms, and 32 updates and a
+// re-solve of 16 5k x 10k instances 1.155 -> 1.106 ms).  The pieces depend on
+// the instance alone, so a batch and a single solve agree bit for bit.  An
+// instance of one piece is finished by its only workgroup.
 __device__ __forceinline__ void norm_finish(InstState &S, const double s[4], bool rows)
 {
     if (rows) {
@@ -2188,11 +2190,15 @@ enum { NORM_KEEP = 0, NORM_BLEND = 1, NORM_STAGED = 2 };
 
 // Workgroup slots * i + piece: one piece of instance q0 + i, partial sums to
 // part[4 (slots q + piece)], or the norms themselves when it is the only one.
+// The workgroup that counts itself last in done[q] adds the pieces of q and
+// clears the count (nobody waits); the fences order the partial sums before the
+// count across the XCDs' L2s.
 // NORM_BLEND / NORM_STAGED: the objective is written first (V: path precision).
 template <class V, int SRC>
 __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const BlendArgs B)
 {
     __shared__ double red[4 * 4], sum[4];
+    __shared__ int last;
     const int q = a.q0 + (int)(blockIdx.x / a.slots), blk = (int)(blockIdx.x % a.slots);
     const InstInfo &I = a.info[q];
     const int m = I.row1 - I.row0, n = I.col1 - I.col0;
@@ -2208,25 +2214,27 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
         staged_sums<V>(B.c_orig, a.c, (V *)B.cv, a.dc, I.col0, lo, hi, acc[2], acc[3]);
     else norm_sums(a.c, a.dc, lo, hi, acc[2], acc[3]);
     block_sums<256, 4>(acc, red, nb == 1 ? sum : a.part + 4 * ((size_t)a.slots * q + blk));
-    if (nb > 1) return;
+    if (nb == 1) {
+        __syncthreads();
+        if (threadIdx.x == 0) norm_finish(a.st[q], sum, a.rows != 0);
+        return;
+    }
+    if (threadIdx.x < 4) __threadfence();
     __syncthreads();
-    if (threadIdx.x == 0) norm_finish(a.st[q], sum, a.rows != 0);
-}
-
-// One wave per instance of more than one piece: adds the partial sums.
-__global__ __launch_bounds__(64) void k_norm_final(const NormArgs a)
-{
-    const int q = a.q0 + blockIdx.x;
-    const InstInfo &I = a.info[q];
-    const int nb = norm_blocks(I.row1 - I.row0, I.col1 - I.col0);
-    if (nb == 1) return;
+    if (threadIdx.x == 0) last = atomicAdd(a.done + q, 1) == nb - 1;
+    __syncthreads();
+    if (!last || threadIdx.x >= 64) return;
+    __threadfence();
     double s[4] = {};
     for (int b = threadIdx.x; b < nb; b += 64) {
         const double *p = a.part + 4 * ((size_t)a.slots * q + b);
         for (int k = 0; k < 4; ++k) s[k] += p[k];
     }
     for (int k = 0; k < 4; ++k) s[k] = group_sum(s[k], 64);
-    if (threadIdx.x == 0) norm_finish(a.st[q], s, a.rows != 0);
+    if (threadIdx.x == 0) {
+        a.done[q] = 0;
+        norm_finish(a.st[q], s, a.rows != 0);
+    }
 }
 
 template <class V>
@@ -2813,7 +2821,6 @@ void launch_norms(const NormArgs &a, int q1, hipStream_t s)
     if (q1 <= a.q0) return;
     hipLaunchKernelGGL((k_norm_part<double, NORM_KEEP>), dim3((unsigned)a.slots * (unsigned)(q1 - a.q0)), dim3(256), 0, s, a,
                        BlendArgs{});
-    launch_norm_final(a, q1, s);
 }
 
 template <class V>
@@ -2847,12 +2854,6 @@ void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s
 {
     if (len > 0)
         hipLaunchKernelGGL(k_put<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, src, dst, dst_v, len);
-}
-
-void launch_norm_final(const NormArgs &a, int q1, hipStream_t s)
-{
-    if (a.slots > 1 && q1 > a.q0)
-        hipLaunchKernelGGL(k_norm_final, dim3((unsigned)(q1 - a.q0)), dim3(64), 0, s, a);
 }
 
 template <class V>

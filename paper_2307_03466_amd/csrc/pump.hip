@@ -438,7 +438,6 @@ int pump_impl(scylla_batch *h, const scylla_params *p, const uint8_t *is_int, co
                 blend_instance(h, q, h->bits_tmp.as<uint8_t>() + boff[q], h->ibits_tmp.as<uint8_t>() + boff[q], a,
                                kappa[q]);
             }
-            launch_norm_final(norm_args(h, g.q0), g.q1, h->stream);
         }
         if (g.K < o.rounds && any) {
             HIPC(hipGetLastError());

@@ -1359,7 +1359,11 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     for (int32_t q = 0; q < h->count; ++q)
         h->norm_slots = std::max(h->norm_slots, norm_blocks(h->row_off[q + 1] - h->row_off[q],
                                                             h->col_off[q + 1] - h->col_off[q]));
-    if (h->norm_slots > 1) h->norm_part.alloc(32 * (size_t)h->norm_slots * h->count);
+    if (h->norm_slots > 1) {
+        h->norm_part.alloc(32 * (size_t)h->norm_slots * h->count);
+        h->norm_done.alloc(4 * (size_t)h->count);
+        HIPC(hipMemsetAsync(h->norm_done.p, 0, h->norm_done.bytes, s));
+    }
     refresh_norms(h, 0, h->count, true);
     HIPC(hipGetLastError());
     // fused-window eligibility: every instance fits in LDS
@@ -1691,7 +1695,8 @@ static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
 NormArgs norm_args(scylla_batch *h, int32_t q0)
 {
     return {h->info.as<InstInfo>(), h->b64.as<double>(),   h->c64.as<double>(),       h->dr64.as<double>(),
-            h->dc64.as<double>(),   h->st.as<InstState>(), h->norm_part.as<double>(), h->norm_slots, q0, 0};
+            h->dc64.as<double>(),   h->st.as<InstState>(), h->norm_part.as<double>(),
+            h->norm_done.as<int32_t>(), h->norm_slots, q0, 0};
 }
 
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows)
@@ -1829,7 +1834,6 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
             const double *src = reinterpret_cast<const double *>(at);
             if (h->vbytes == 4) launch_objective<float>(norm_args(h, inst), src, h->cv.as<float>(), h->stream);
             else launch_objective<double>(norm_args(h, inst), src, h->cv.as<double>(), h->stream);
-            launch_norm_final(norm_args(h, inst), inst + 1, h->stream);
         } else {
             HIPC(hipMemcpyAsync(h->c64.as<double>() + lo, c_hat, sizeof(double) * (size_t)len, hipMemcpyHostToDevice,
                                 h->stream));
@@ -1892,7 +1896,6 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         };
         const uint8_t *xb = put(h->bits_tmp, xhat_bits), *ib = int_bits ? put(h->ibits_tmp, int_bits) : nullptr;
         blend_instance(h, inst, xb, ib, a, kappa);
-        launch_norm_final(norm_args(h, inst), inst + 1, h->stream);
         HIPC(hipGetLastError());
         if (!in_place) HIPC(hipStreamSynchronize(h->stream));
         return 0;
