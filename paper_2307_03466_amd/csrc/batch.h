@@ -195,9 +195,9 @@ struct scylla_batch {
     DevMem ibnd;            // [2 * count] (l, u) shared by all columns of an
                             // instance, NaN where they differ
     DevMem start_flag;      // validation flag of a device warm start
-    // pinned staging of small updates (objectives, rounding bits, weights):
-    // copied from without waiting, reused from the start once the stream has
-    // drained
+    // pinned staging of small updates (objectives, Hessians, rounding bits),
+    // read by their kernels without waiting; reused from the start once the
+    // stream has drained, and all that one launch reads is reserved together
     char *stage = nullptr;
     size_t stage_at = 0;
     int *start_host = nullptr;  // pinned copy of start_flag

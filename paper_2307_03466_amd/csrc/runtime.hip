@@ -1672,11 +1672,14 @@ static void cast_range(scylla_batch *h, const DevMem &src, DevMem &dst, int32_t 
 void cast_c(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->c64, h->cv, lo, hi); }
 void cast_q(scylla_batch *h, int32_t lo, int32_t hi) { cast_range(h, h->q64, h->qv, lo, hi); }
 
-// Host data for a copy queued on the stream: small data is copied into the
-// pinned staging buffer, so that the caller's memory is free at once and
-// nothing waits; returns where it lies (readable by the device too), or NULL
-// when it is larger than the buffer (the caller then copies and waits).
-static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
+// Room in the pinned staging buffer for all the host data that one launch
+// reads: small data is copied there, so that the caller's memory is free at
+// once and nothing waits (the device reads it where it lies).  Everything
+// reserved earlier belongs to work that is queued by now, so the buffer can
+// start over once the stream has drained; a launch that took its data from two
+// reservations would break that.  NULL when the data is larger than the buffer
+// (the caller then copies and waits).
+static char *stage_room(scylla_batch *h, size_t bytes)
 {
     // one buffer a handle, made by its first update
     constexpr size_t STAGE_BYTES = (size_t)1 << 20;
@@ -1687,8 +1690,14 @@ static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
         h->stage_at = 0;
     }
     char *at = h->stage + h->stage_at;
-    memcpy(at, src, bytes);
     h->stage_at += (bytes + 255) & ~(size_t)255;
+    return at;
+}
+
+static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
+{
+    char *at = stage_room(h, bytes);
+    if (at) memcpy(at, src, bytes);
     return at;
 }
 
@@ -1888,13 +1897,19 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         // bits of up to 128k columns are read by the kernel where they are
         // staged (5 KB for 40k columns: less than a copy's launch)
         const bool in_place = nb <= 16384;
-        auto put = [&](DevMem &d, const uint8_t *src) -> const uint8_t * {
-            if (in_place) return reinterpret_cast<const uint8_t *>(stage_data(h, src, nb));
+        const size_t ib_at = (nb + 255) & ~(size_t)255;
+        char *at = in_place ? stage_room(h, int_bits ? ib_at + nb : nb) : nullptr;
+        auto put = [&](char *to, DevMem &d, const uint8_t *src) -> const uint8_t * {
+            if (in_place) {
+                memcpy(to, src, nb);
+                return reinterpret_cast<const uint8_t *>(to);
+            }
             if (d.bytes < nb) d.alloc(nb);
             HIPC(hipMemcpyAsync(d.p, src, nb, hipMemcpyHostToDevice, h->stream));
             return d.as<uint8_t>();
         };
-        const uint8_t *xb = put(h->bits_tmp, xhat_bits), *ib = int_bits ? put(h->ibits_tmp, int_bits) : nullptr;
+        const uint8_t *xb = put(at, h->bits_tmp, xhat_bits);
+        const uint8_t *ib = int_bits ? put(at + ib_at, h->ibits_tmp, int_bits) : nullptr;
         blend_instance(h, inst, xb, ib, a, kappa);
         HIPC(hipGetLastError());
         if (!in_place) HIPC(hipStreamSynchronize(h->stream));

@@ -1,0 +1,37 @@
+"""The library's host runtime without a GPU: tests/host/runtime_driver.cpp
+replaces the HIP runtime by one that queues work until something waits for it
+and checks what the library launches (sizes, buffers, staged data)."""
+import os
+import subprocess
+import tempfile
+
+import pytest
+
+from paper_2307_03466_amd import pdhg
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def driver():
+    if not os.path.exists(pdhg.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    exe = os.path.join(tempfile.mkdtemp(), "runtime_driver")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-o", exe, os.path.join(ROOT, "tests", "host", "runtime_driver.cpp"), "-rdynamic",
+                           pdhg.LIB_PATH, "-Wl,--allow-shlib-undefined",
+                           "-Wl,-rpath," + os.path.dirname(pdhg.LIB_PATH), "-lpthread"])
+
+    def run(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=110)
+        assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:] + r.stderr[-2000:]
+    return run
+
+
+@pytest.mark.parametrize("n,objectives", [(120000, 0), (131072, 0), (40000, 1), (16384, 1), (17, 1)])
+def test_updates_read_their_own_staged_bits(driver, n, objectives):
+    """Rounding and integer bits of one update are staged together: the
+    buffer starting over between the two would hand the first to later
+    updates while the stream is behind."""
+    driver("blends", n, 400, objectives)
