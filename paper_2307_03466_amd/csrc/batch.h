@@ -188,9 +188,10 @@ struct scylla_batch {
     // FP64 data
     DevMem c64, corig64, l64, u64, b64, dr64, dc64;
     DevMem st, info;
-    DevMem norm_part;       // partial sums of the norms
-    DevMem norm_done;       // pieces summed so far, per instance
-    int32_t norm_slots = 1; // most pieces of an instance's norms
+    // where an instance has more than one piece: partial sums of the norms,
+    // pieces summed so far per instance, first piece of every instance
+    DevMem norm_part, norm_done, norm_off;
+    std::vector<int32_t> hnorm_off;  // host copy of norm_off
     DevMem ax;              // running A x of the row pass (adaptive steps)
     DevMem ibnd;            // [2 * count] (l, u) shared by all columns of an
                             // instance, NaN where they differ
@@ -305,7 +306,7 @@ void cast_q(scylla_batch *h, int32_t lo, int32_t hi);
 // Norms and cold-start weights of the instances [q0, q1) for their current
 // objective (rows: and right-hand side).
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows = false);
-NormArgs norm_args(scylla_batch *h, int32_t q0);
+NormArgs norm_args(scylla_batch *h, int32_t q0, int32_t q1);
 // Pump objective and norms of instance inst from device-readable rounding and
 // integer bits.
 void blend_instance(scylla_batch *h, int32_t inst, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa);

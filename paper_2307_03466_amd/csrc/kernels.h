@@ -251,8 +251,9 @@ struct SetupArgs {
 template <class V>
 void launch_setup_vectors(const SetupArgs<V> &a, hipStream_t s);
 // Norms of the instances [q0, q1) after their objective (and, with rows set,
-// their right-hand side) was written; part holds 4 doubles per instance and
-// slot, slots = the most pieces of any instance of the handle.
+// their right-hand side) was written.  Instance q is summed in the pieces
+// [off[q], off[q + 1]) of the handle, whose partial sums are 4 doubles of part
+// each; off null: one piece an instance.
 constexpr int NORM_CHUNK = 2048, NORM_MAX_BLOCKS = 1024;
 __host__ __device__ inline int norm_blocks(int m, int n)
 {
@@ -266,8 +267,10 @@ struct NormArgs {
     const double *dr, *dc;
     InstState *st;
     double *part;
-    int32_t *done;  // [count] pieces finished, 0 between launches
-    int32_t slots, q0, rows;
+    int32_t *done;       // [count] pieces finished, 0 between launches
+    const int32_t *off;  // [count + 1] first piece of every instance, or null
+    int32_t q0, q1, rows;
+    int32_t pieces;      // of [q0, q1)
 };
 // Pump objective of instance q0: original objective, rounding bits and integer
 // bits of its columns (null: all integer), weights, path-precision copy.
@@ -286,7 +289,7 @@ void launch_objective(const NormArgs &a, const double *src, V *cv, hipStream_t s
 // dst = src and its copy in the path precision.
 template <class V>
 void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s);
-void launch_norms(const NormArgs &a, int q1, hipStream_t s);
+void launch_norms(const NormArgs &a, hipStream_t s);
 template <class V>
 void launch_cast(const double *src, V *dst, int len, hipStream_t s);
 template <class V>

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "scylla_internal.h"
@@ -2188,9 +2189,9 @@ __device__ __forceinline__ void staged_sums(const double *src, double *c, V *cv,
 // How a norm launch gets the objective.
 enum { NORM_KEEP = 0, NORM_BLEND = 1, NORM_STAGED = 2 };
 
-// Workgroup slots * i + piece: one piece of instance q0 + i, partial sums to
-// part[4 (slots q + piece)], or the norms themselves when it is the only one.
-// The workgroup that counts itself last in done[q] adds the pieces of q and
+// One workgroup a piece of the instances [q0, q1), partial sums to its place in
+// part, or the norms themselves when it is an instance's only one.  The
+// workgroup that counts itself last in done[q] adds the pieces of q and
 // clears the count (nobody waits); the fences order the partial sums before the
 // count across the XCDs' L2s.
 // NORM_BLEND / NORM_STAGED: the objective is written first (V: path precision).
@@ -2199,11 +2200,28 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
 {
     __shared__ double red[4 * 4], sum[4];
     __shared__ int last;
-    const int q = a.q0 + (int)(blockIdx.x / a.slots), blk = (int)(blockIdx.x % a.slots);
+    int q = a.q0, piece = (int)blockIdx.x, first = 0;
+    if (!a.off) {
+        q += piece;
+        piece = 0;
+    } else {
+        first = a.off[q];
+        if (a.q1 - a.q0 > 1) {  // the instance that holds the piece
+            const int at = first + piece;
+            for (int hi = a.q1; hi - q > 1;) {
+                const int mid = q + (hi - q) / 2;
+                if (a.off[mid] <= at) q = mid;
+                else hi = mid;
+            }
+            first = a.off[q];
+            piece = at - first;
+        }
+    }
+    const int blk = piece;
     const InstInfo &I = a.info[q];
     const int m = I.row1 - I.row0, n = I.col1 - I.col0;
     const int nb = norm_blocks(m, n);
-    if (blk >= nb) return;
+    double *const part = a.part + 4 * (size_t)first;
     double acc[4] = {};
     if (a.rows)
         norm_sums(a.b, a.dr, I.row0 + (int)((int64_t)m * blk / nb), I.row0 + (int)((int64_t)m * (blk + 1) / nb),
@@ -2213,7 +2231,7 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
     else if constexpr (SRC == NORM_STAGED)
         staged_sums<V>(B.c_orig, a.c, (V *)B.cv, a.dc, I.col0, lo, hi, acc[2], acc[3]);
     else norm_sums(a.c, a.dc, lo, hi, acc[2], acc[3]);
-    block_sums<256, 4>(acc, red, nb == 1 ? sum : a.part + 4 * ((size_t)a.slots * q + blk));
+    block_sums<256, 4>(acc, red, nb == 1 ? sum : part + 4 * (size_t)blk);
     if (nb == 1) {
         __syncthreads();
         if (threadIdx.x == 0) norm_finish(a.st[q], sum, a.rows != 0);
@@ -2227,7 +2245,7 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
     __threadfence();
     double s[4] = {};
     for (int b = threadIdx.x; b < nb; b += 64) {
-        const double *p = a.part + 4 * ((size_t)a.slots * q + b);
+        const double *p = part + 4 * (size_t)b;
         for (int k = 0; k < 4; ++k) s[k] += p[k];
     }
     for (int k = 0; k < 4; ++k) s[k] = group_sum(s[k], 64);
@@ -2783,11 +2801,14 @@ void launch_take_avg(const InstState *st, const InstInfo *info, V *x, V *y, cons
                      const double *axa, int count, int longest, hipStream_t s)
 {
     // about 2048 columns a workgroup, at most 256 workgroups an instance (a
-    // workgroup for each of a 5k x 10k instance took 7 us)
+    // workgroup for each of a 5k x 10k instance took 7 us), and all in all no
+    // more than 2^20 beyond one an instance: a grid is limited to 2^32 threads,
+    // and with that many instances the others fill the chip
+    if (count <= 0) return;
     int blocks = (longest + 2047) / 2048;
+    blocks = std::min({blocks, 256, (1 << 20) / count});
     if (blocks < 1) blocks = 1;
-    if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(k_take_avg<V>, dim3((unsigned)(count * blocks)), dim3(256), 0, s, st, info, x, y, xa, ya, ax, axa,
+    hipLaunchKernelGGL(k_take_avg<V>, dim3((unsigned)count * (unsigned)blocks), dim3(256), 0, s, st, info, x, y, xa, ya, ax, axa,
                        blocks);
 }
 
@@ -2816,17 +2837,16 @@ void launch_setup_vectors(const SetupArgs<V> &a, hipStream_t s)
     if (len > 0) hipLaunchKernelGGL(k_setup_vectors<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, a);
 }
 
-void launch_norms(const NormArgs &a, int q1, hipStream_t s)
+void launch_norms(const NormArgs &a, hipStream_t s)
 {
-    if (q1 <= a.q0) return;
-    hipLaunchKernelGGL((k_norm_part<double, NORM_KEEP>), dim3((unsigned)a.slots * (unsigned)(q1 - a.q0)), dim3(256), 0, s, a,
-                       BlendArgs{});
+    if (a.q1 <= a.q0) return;
+    hipLaunchKernelGGL((k_norm_part<double, NORM_KEEP>), dim3((unsigned)a.pieces), dim3(256), 0, s, a, BlendArgs{});
 }
 
 template <class V>
 void launch_blend(const NormArgs &a, const BlendArgs &b, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_norm_part<V, NORM_BLEND>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+    hipLaunchKernelGGL((k_norm_part<V, NORM_BLEND>), dim3((unsigned)a.pieces), dim3(256), 0, s, a, b);
 }
 
 template <class V>
@@ -2835,7 +2855,7 @@ void launch_objective(const NormArgs &a, const double *src, V *cv, hipStream_t s
     BlendArgs b{};
     b.c_orig = src;
     b.cv = cv;
-    hipLaunchKernelGGL((k_norm_part<V, NORM_STAGED>), dim3((unsigned)a.slots), dim3(256), 0, s, a, b);
+    hipLaunchKernelGGL((k_norm_part<V, NORM_STAGED>), dim3((unsigned)a.pieces), dim3(256), 0, s, a, b);
 }
 
 // dst = src, dst_v = src in the path precision.

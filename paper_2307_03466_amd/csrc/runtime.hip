@@ -1356,13 +1356,15 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     refresh_info(h);
     for (int32_t q = 0; q < h->count; ++q)
         h->longest = std::max({h->longest, h->row_off[q + 1] - h->row_off[q], h->col_off[q + 1] - h->col_off[q]});
+    std::vector<int32_t> off(1, 0);  // pieces of the norms, instance by instance
     for (int32_t q = 0; q < h->count; ++q)
-        h->norm_slots = std::max(h->norm_slots, norm_blocks(h->row_off[q + 1] - h->row_off[q],
-                                                            h->col_off[q + 1] - h->col_off[q]));
-    if (h->norm_slots > 1) {
-        h->norm_part.alloc(32 * (size_t)h->norm_slots * h->count);
+        off.push_back(off.back() + norm_blocks(h->row_off[q + 1] - h->row_off[q], h->col_off[q + 1] - h->col_off[q]));
+    if (off.back() > h->count) {
+        upload(h->norm_off, off, s);
+        h->norm_part.alloc(32 * (size_t)off.back());
         h->norm_done.alloc(4 * (size_t)h->count);
         HIPC(hipMemsetAsync(h->norm_done.p, 0, h->norm_done.bytes, s));
+        h->hnorm_off = std::move(off);
     }
     refresh_norms(h, 0, h->count, true);
     HIPC(hipGetLastError());
@@ -1701,25 +1703,36 @@ static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
     return at;
 }
 
-NormArgs norm_args(scylla_batch *h, int32_t q0)
+NormArgs norm_args(scylla_batch *h, int32_t q0, int32_t q1)
 {
-    return {h->info.as<InstInfo>(), h->b64.as<double>(),   h->c64.as<double>(),       h->dr64.as<double>(),
-            h->dc64.as<double>(),   h->st.as<InstState>(), h->norm_part.as<double>(),
-            h->norm_done.as<int32_t>(), h->norm_slots, q0, 0};
+    NormArgs a{};
+    a.info = h->info.as<InstInfo>();
+    a.b = h->b64.as<double>();
+    a.c = h->c64.as<double>();
+    a.dr = h->dr64.as<double>();
+    a.dc = h->dc64.as<double>();
+    a.st = h->st.as<InstState>();
+    a.part = h->norm_part.as<double>();
+    a.done = h->norm_done.as<int32_t>();
+    a.off = h->norm_off.as<int32_t>();
+    a.q0 = q0;
+    a.q1 = q1;
+    a.pieces = h->hnorm_off.empty() ? q1 - q0 : h->hnorm_off[q1] - h->hnorm_off[q0];
+    return a;
 }
 
 void refresh_norms(scylla_batch *h, int32_t q0, int32_t q1, bool rows)
 {
-    NormArgs a = norm_args(h, q0);
+    NormArgs a = norm_args(h, q0, q1);
     a.rows = rows ? 1 : 0;
-    launch_norms(a, q1, h->stream);
+    launch_norms(a, h->stream);
 }
 
 void blend_instance(scylla_batch *h, int32_t inst, const uint8_t *xbits, const uint8_t *ibits, double a, double kappa)
 {
     const BlendArgs b{h->corig64.as<double>(), xbits, ibits, a, kappa, h->cv.p};
-    if (h->vbytes == 4) launch_blend<float>(norm_args(h, inst), b, h->stream);
-    else launch_blend<double>(norm_args(h, inst), b, h->stream);
+    if (h->vbytes == 4) launch_blend<float>(norm_args(h, inst, inst + 1), b, h->stream);
+    else launch_blend<double>(norm_args(h, inst, inst + 1), b, h->stream);
 }
 
 }  // namespace scy
@@ -1841,8 +1854,8 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
         const char *at = stage_data(h, c_hat, sizeof(double) * (size_t)len);
         if (at) {
             const double *src = reinterpret_cast<const double *>(at);
-            if (h->vbytes == 4) launch_objective<float>(norm_args(h, inst), src, h->cv.as<float>(), h->stream);
-            else launch_objective<double>(norm_args(h, inst), src, h->cv.as<double>(), h->stream);
+            if (h->vbytes == 4) launch_objective<float>(norm_args(h, inst, inst + 1), src, h->cv.as<float>(), h->stream);
+            else launch_objective<double>(norm_args(h, inst, inst + 1), src, h->cv.as<double>(), h->stream);
         } else {
             HIPC(hipMemcpyAsync(h->c64.as<double>() + lo, c_hat, sizeof(double) * (size_t)len, hipMemcpyHostToDevice,
                                 h->stream));

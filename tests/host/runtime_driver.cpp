@@ -32,7 +32,7 @@ std::map<const void *, std::string> &kernels()
     return m;
 }
 std::map<const char *, size_t> g_live;   // device allocations
-size_t g_allocated = 0, g_most = 0;      // bytes now, most of any time
+size_t g_largest = 0;                    // bytes of the largest allocation
 long g_mallocs = 0, g_fail_at = -1;      // hipMalloc calls; the one that fails
 std::vector<std::function<void()>> g_queue;
 hipStream_t g_capturing = nullptr;       // the library's own capture
@@ -201,8 +201,7 @@ hipError_t hipMalloc(void **p, size_t n)
     if (g_mallocs++ == g_fail_at) return hipErrorOutOfMemory;
     *p = calloc(n, 1);
     g_live[(char *)*p] = n;
-    g_allocated += n;
-    g_most = std::max(g_most, g_allocated);
+    g_largest = std::max(g_largest, n);
     return hipSuccess;
 }
 hipError_t hipFree(void *p)
@@ -210,7 +209,6 @@ hipError_t hipFree(void *p)
     drain();
     auto it = g_live.find((char *)p);
     if (it == g_live.end()) return hipErrorInvalidValue;
-    g_allocated -= it->second;
     g_live.erase(it);
     free(p);
     return hipSuccess;
@@ -418,6 +416,24 @@ void blends(int n, int updates, bool objectives)
     scylla_batch_destroy(h);
 }
 
+// One large LP among many small ones: launches and buffers grow with what
+// there is, not with the number of instances times the largest.
+void uneven(int small, int rows, int cols)
+{
+    const Lp big(rows, cols, 2), lp(1, 2, 1);
+    std::vector<scylla_lp> lps(small, lp.view());
+    lps.push_back(big.view());
+    scylla_batch *h = create(lps, SCYLLA_FP32);
+    const size_t bound = 64 * ((size_t)3 * rows + cols) + 1024 * (size_t)lps.size();
+    if (g_largest > bound) fault("an allocation of %zu bytes", g_largest);
+    scylla_params p = solve_params(SCYLLA_FP32);
+    p.restart_avg = 1;
+    std::vector<scylla_result> res(lps.size());
+    if (h) must(scylla_batch_solve(h, &p, 0, res.data()), "solve");
+    if (g_launches["k_take_avg"] == 0 || g_launches["k_norm_part"] != 1) fault("launches");
+    scylla_batch_destroy(h);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -425,6 +441,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     auto arg = [&](int k) { return atoi(argv[k]); };
     if (what == "blends") blends(arg(2), arg(3), arg(4) != 0);
+    else if (what == "uneven") uneven(arg(2), arg(3), arg(4));
     else fault("unknown scenario");
     if (g_faults == 0) printf("ok\n");
     return g_faults == 0 ? 0 : 1;

@@ -35,3 +35,9 @@ def test_updates_read_their_own_staged_bits(driver, n, objectives):
     buffer starting over between the two would hand the first to later
     updates while the stream is behind."""
     driver("blends", n, 400, objectives)
+
+
+@pytest.mark.parametrize("small,rows,cols", [(16384, 1000000, 1100000), (65536, 300000, 530000), (3, 2, 5)])
+def test_one_large_lp_among_many_small_ones(driver, small, rows, cols):
+    """No launch beyond 2^32 threads, no buffer of instances x the largest."""
+    driver("uneven", small, rows, cols)
