@@ -72,8 +72,10 @@ struct DevMem {
     void alloc(size_t b)
     {
         release();
-        bytes = b;
-        HIPC(hipMalloc(&p, b > 0 ? b : 16));
+        void *q = nullptr;
+        HIPC(hipMalloc(&q, b > 0 ? b : 16));
+        p = q;
+        bytes = b;  // (0 after a failure, so that callers which keep a large enough buffer try again)
     }
     template <class T>
     T *as() const { return static_cast<T *>(p); }
@@ -101,7 +103,7 @@ struct OrientRT {
     DevMem ptr, ent, val;
     MatView mat{};
     TilePlan plan;
-    int32_t normal_chunk = 0;  // tile size plan and its buffers are made for
+    int32_t normal_chunk = 0;  // tile size plan and its buffers are made for (0: not normal tiles)
     int32_t ept = 8;
     // normal tiles with sorted entries (when chosen): a copy of the entries in
     // the order of the tiles of normal_chunk nonzeros
@@ -221,6 +223,7 @@ struct scylla_batch {
     size_t cstage_bytes = 0;
     int32_t graph_R = 0;
     bool tuned = false;
+    bool laid_out = false;  // both orientations' plans, buffers and info agree
     int32_t lds_max = 65536;  // dynamic LDS bytes a workgroup may use
     bool tiny_ok = false;     // every instance fits the fused window
     size_t tiny_shmem = 0;

@@ -143,7 +143,9 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
     o.direct = false;
     o.cmp = false;
     if (B > 0) {
+        o.normal_chunk = 0;
         if (!o.blocked || o.bh.B != B) {
+            o.blocked = false;  // until its buffers are there
             build_blocked(o.host, h->fmt, o.gather, B, o.bh);
             upload(o.bptr, o.bh.bptr, h->stream);
             upload(o.bent, o.bh.ent, h->stream);
@@ -170,10 +172,10 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
         o.seg64.alloc(std::max<size_t>(1, o.bplan.nslots) * 8);
         o.part.alloc(std::max<size_t>(1, o.bplan.ctiles.size() / 4) * CHK * 8);
         o.lpart.alloc(8 * CHK);
-    } else if (o.blocked || o.normal_chunk != chunk) {
+    } else if (o.normal_chunk != chunk) {
         // (the staged and direct candidates of the tuner share this plan)
         o.blocked = false;
-        o.normal_chunk = chunk;
+        o.normal_chunk = 0;  // until its buffers are there
         // (columns are short: more of them fill a tile of 8192 nonzeros)
         plan_tiles(o.host.ptr, off, chunk, chunk > 4096 ? (1 << TILE_ROW_BITS) - 1 : 1024, o.plan);
         seal_tiles(o.host.ptr, o.plan.tiles);
@@ -183,6 +185,7 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
         o.seg64.alloc(std::max<size_t>(1, o.plan.nslots) * 8);
         o.part.alloc(std::max<size_t>(1, o.plan.tiles.size() / 4) * CHK * 8);
         o.lpart.alloc(std::max<size_t>(1, o.plan.longs.size() / 4) * CHK * 8);
+        o.normal_chunk = chunk;
     }
     ip_layout(o);
     HIPC(hipStreamSynchronize(h->stream));
@@ -270,8 +273,6 @@ void set_staged(scylla_batch *h, OrientRT &o, int32_t ept, int32_t group_nnz, in
             for (int32_t q = 0; q < h->count; ++q) cand[q] = o.splan.staged[q] ? 0 : 1;
             release_sliced(o);
             build_sliced(o.host, h->fmt, off, gofs, cand, max_vec, 4, chunk, o.xplan);
-            o.x_max_vec = max_vec;
-            o.x_sub = chunk;
             if (o.xplan.S > 0) {
                 upload(o.xsq, o.xplan.Sq, h->stream);
                 upload(o.xptr, o.xplan.bptr, h->stream);
@@ -288,6 +289,8 @@ void set_staged(scylla_batch *h, OrientRT &o, int32_t ept, int32_t group_nnz, in
                 o.xplan.v64.clear();
                 o.xplan.v64.shrink_to_fit();
             }
+            o.x_max_vec = max_vec;  // (its buffers are there)
+            o.x_sub = chunk;
         }
         o.sliced = o.xplan.S > 0;
     } else {
@@ -466,6 +469,30 @@ void invalidate_graph(scylla_batch *h)
     if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
     h->gexec = nullptr;
     h->graph_R = 0;
+}
+
+// End of a layout change: info and graph follow the plans.
+void laid_out(scylla_batch *h)
+{
+    refresh_info(h);
+    invalidate_graph(h);
+    h->laid_out = true;
+}
+
+// A layout change that failed midway (no memory) leaves plans, buffers and
+// info that disagree: before the next launch the layout of a new handle takes
+// its place.
+void ensure_layout(scylla_batch *h)
+{
+    if (h->laid_out) return;
+    for (OrientRT *o : {&h->orow, &h->ocol}) {
+        o->cached = false;
+        drop_sorted(*o);
+        set_plan(h, *o, 0, 8);
+        drop_blocked(*o);
+        release_sliced(*o);
+    }
+    laid_out(h);
 }
 
 template <class V>
@@ -1061,13 +1088,14 @@ TuneChoice current_choice(scylla_batch *h)
 template <class V>
 void autotune(scylla_batch *h)
 {
+    ensure_layout(h);
+    h->laid_out = false;
     const std::string key = tune_key(h);
     TuneChoice cached;
     if (tune_lookup(key, cached)) {
         apply_choice(h, h->orow, cached.v);
         apply_choice(h, h->ocol, cached.v + 4);
-        refresh_info(h);
-        invalidate_graph(h);
+        laid_out(h);
         h->tuned = true;
         return;
     }
@@ -1246,8 +1274,7 @@ void autotune(scylla_batch *h)
         h->orow.cached = (best_c & 1) != 0;
         h->ocol.cached = (best_c & 2) != 0;
     }
-    refresh_info(h);
-    invalidate_graph(h);
+    laid_out(h);
     h->tuned = true;
     tune_store(key, current_choice(h));
 }
@@ -1353,7 +1380,7 @@ void setup_device(scylla_batch *h, const scylla_lp *lps, HostOrient &csr, HostOr
     upload(h->st, st, s);
     set_plan(h, h->orow, 0, 8);
     set_plan(h, h->ocol, 0, 8);
-    refresh_info(h);
+    laid_out(h);
     for (int32_t q = 0; q < h->count; ++q)
         h->longest = std::max({h->longest, h->row_off[q + 1] - h->row_off[q], h->col_off[q + 1] - h->col_off[q]});
     std::vector<int32_t> off(1, 0);  // pieces of the norms, instance by instance
@@ -1527,6 +1554,7 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
         else autotune<double>(h);
         tune_s = now_s() - tt;
     }
+    ensure_layout(h);
     // the largest iteration limit: the check that reaches it stops everything
     int64_t lim = k_limits ? 0 : p->iter_limit;
     if (k_limits) {
@@ -2124,6 +2152,7 @@ int scylla_batch_set_layout(scylla_batch *h, int32_t row_blocks, int32_t row_ept
         if (!okB(row_blocks) || !okB(col_blocks) || !okE(row_ept) || !okE(col_ept))
             throw_err(-EINVAL, "blocks must be -8, -7, -6, -3, -2, -1, 0, 2, 4 or 8 and ept 2, 4, 8, 16, -8 or -16");
         HIPC(hipStreamSynchronize(h->stream));
+        h->laid_out = false;
         for (int d = 0; d < 2; ++d) {
             OrientRT &o = d == 0 ? h->orow : h->ocol;
             o.cached = false;  // non-temporal matrix loads unless set otherwise
@@ -2144,8 +2173,7 @@ int scylla_batch_set_layout(scylla_batch *h, int32_t row_blocks, int32_t row_ept
                 release_sliced(o);
             }
         }
-        refresh_info(h);
-        invalidate_graph(h);
+        laid_out(h);
         h->tuned = true;
         return 0;
     });
@@ -2156,6 +2184,7 @@ int scylla_batch_time_passes(scylla_batch *h, int32_t reps, double *ms_row, doub
     return guarded([&]() {
         if (!h || !ms_row || !ms_col || reps < 1) throw_err(-EINVAL, "bad argument");
         HIPC(hipStreamSynchronize(h->stream));
+        ensure_layout(h);
         if (h->vbytes == 4) {
             PassTimer<float> t(h);
             *ms_row = t.time(h->orow, reps, false);

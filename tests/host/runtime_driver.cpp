@@ -78,25 +78,57 @@ uint64_t byte_sum(const uint8_t *p, size_t n)
     return p ? s : 0;
 }
 
+// What a pass kernel reads and writes is device memory of the sizes it needs.
 template <class V>
 void check_pass(const std::string &name, const PassArgs<V> &p, bool check)
 {
-    if (!on_device(p.tiles, 16 * (size_t)p.ntiles)) fault("%s: tiles", name.c_str());
-    if (check) {
-        if (!on_device(p.part, 8 * CHK * (size_t)p.ntiles)) fault("%s: part", name.c_str());
-    }
-    if (p.nlong > 0) {
-        if (!on_device(p.longs, 16 * (size_t)p.nlong)) fault("%s: longs", name.c_str());
-        // the last long row's descriptor (uploads are queued: read after them)
+    auto is = [&](const char *k) { return name.find(k) != std::string::npos; };
+    auto need = [&](const void *q, size_t bytes, const char *what) {
+        if (!on_device(q, std::max<size_t>(bytes, 1))) fault("%s: %s", name.c_str(), what);
+    };
+    const bool combine = is("9k_combine") || is("15k_combine_check") || is("6k_bseg");
+    const bool rows = is("10k_bcombine") || is("16k_bcombine_check");
+    need(p.st, sizeof(InstState), "states");
+    if (combine) {
+        need(p.longs, 16 * (size_t)p.nlong, "long rows");
+        // the last long row's segments (uploads are queued: read after them)
         const int4 *longs = p.longs;
         const int nlong = p.nlong;
-        const void *seg = check ? (const void *)p.seg64 : (const void *)p.seg, *lpart = p.lpart;
+        const void *seg = check ? (const void *)p.seg64 : (const void *)p.seg;
         const size_t width = check ? 8 : sizeof(V);
-        g_queue.push_back([=] {
+        if (is("15k_combine_check")) need(p.lpart, 8 * CHK * (size_t)nlong, "partials of long rows");
+        if (on_device(longs, 16 * (size_t)nlong)) g_queue.push_back([=] {
             const int4 L = longs[nlong - 1];
             if (!on_device(seg, width * (size_t)(L.y + L.z))) fault("%s: segments", name.c_str());
-            if (check && !on_device(lpart, 8 * CHK * (size_t)nlong)) fault("%s: lpart", name.c_str());
         });
+    } else if (rows) {
+        need(p.ctiles, 16 * (size_t)p.nctiles, "combine tiles");
+        if (check) need(p.P64, 8 * (size_t)p.B * p.rows, "block partials");
+        else need(p.P, sizeof(V) * (size_t)p.B * p.rows, "block partials");
+        if (check) need(p.part, 8 * CHK * (size_t)p.nctiles, "partials");
+    } else if (is("6k_dpass")) {
+        need(p.dtiles, 16 * (size_t)p.ndtiles, "direct tiles");
+        need(p.gofs, 4, "offsets");
+    } else {
+        need(p.tiles, 16 * (size_t)p.ntiles, "tiles");
+        if (is("7k_check")) need(p.part, 8 * CHK * (size_t)p.ntiles, "partials");
+        if (is("7k_bpart")) {
+            need(p.bptr, 4 * (size_t)p.B * (p.rows + 1), "block pointers");
+            need(p.seg, 1, "segments");
+        }
+        if (is("7k_spass")) {
+            need(p.gofs, 4, "offsets");
+            need(p.sub, 0, "sub-tiles");
+            if (p.xS > 0) {
+                need(p.xP, sizeof(V) * (size_t)p.xS * p.rows, "slice partials");
+                need(p.X.ptr, 4 * (size_t)p.xS * (p.rows + 1), "slice pointers");
+                need(p.X.ent, 4, "slice entries");
+                need(p.xsub, 16, "slice sub-tiles");
+                need(p.xSq, 4, "slices");
+            }
+        }
+        need(p.M.ptr, 4, "row pointers");
+        need(p.M.ent, 4, "entries");
     }
 }
 
@@ -134,10 +166,10 @@ void launched_t(const std::string &name, dim3 grid, void **args)
         g_queue.push_back([=] {
             for (int q = 0; q < count; ++q) a.mirror[q].status = ST_ITER;
         });
-    } else if (name.find("k_check") != std::string::npos) {
-        check_pass<V>(name, *(PassArgs<V> *)args[0], true);
-    } else if (name.find("k_pass") != std::string::npos) {
-        check_pass<V>(name, *(PassArgs<V> *)args[0], false);
+    } else if (name.find("8PassArgs") != std::string::npos) {
+        // (k_bpart and k_bseg take the check as an argument)
+        const bool dynamic = name.find("7k_bpart") != std::string::npos || name.find("6k_bseg") != std::string::npos;
+        check_pass<V>(name, *(PassArgs<V> *)args[0], dynamic ? *(int *)args[2] != 0 : name.find("check") != std::string::npos);
     }
 }
 
@@ -187,7 +219,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t, h
     ++g_launches["all"];
     // the limit of a dimension: 2^32 - 1 threads
     if ((uint64_t)g.x * b.x >= (uint64_t)1 << 32 || g.x == 0) fault("%s: grid %u x %u", name.c_str(), g.x, b.x);
-    if (g_capturing) return hipSuccess;
+    // (what a graph launches is checked when it is captured)
+    if (g_capturing && name.find("8PassArgs") == std::string::npos) return hipSuccess;
     // (the precision is the first template argument of every kernel concerned
     // but the decision's, which has none)
     const bool dbl = name.find("IdL") != std::string::npos || name.find("IdE") != std::string::npos;
@@ -434,6 +467,58 @@ void uneven(int small, int rows, int cols)
     scylla_batch_destroy(h);
 }
 
+// Every allocation of a layout change or a solve fails once: the call says so,
+// and whatever follows, the same call again or a solve, launches nothing on
+// buffers that are not there.
+void allocations(const std::string &what, int precision)
+{
+    // long rows (segments), an instance whose vectors fit the LDS, one whose
+    // vectors only fit in slices
+    const Lp one(40, 30000, 9000), two(300, 500, 3), three(100, 90000, 20);
+    const std::vector<scylla_lp> lps = {one.view(), two.view(), three.view()};
+    std::vector<scylla_result> res(lps.size());
+    scylla_params p = solve_params(precision), avg = p;
+    p.fused_window = avg.fused_window = 0;
+    avg.restart_avg = 1;
+    int layout[5] = {};
+    if (sscanf(what.c_str(), "layout:%d,%d,%d,%d", layout, layout + 1, layout + 2, layout + 3) != 4) layout[1] = 0;
+    auto change = [&](scylla_batch *h) {
+        if (layout[1]) return scylla_batch_set_layout(h, layout[0], layout[1], layout[2], layout[3]);
+        return scylla_batch_solve(h, &avg, 0, res.data());
+    };
+    for (int again = 0; again < 2; ++again) {
+        long failed = 0;
+        for (long k = 0;; ++k) {
+            scylla_batch *h = create(lps, precision);
+            if (!h) return;
+            // from another layout with the same and with other tiles
+            must(scylla_batch_set_layout(h, k % 2 ? 2 : 0, layout[1] ? layout[1] : 8, 0, 4), "first layout");
+            g_fail_at = g_mallocs + k;
+            const int rc = change(h);
+            const bool reached = g_mallocs > g_fail_at;
+            g_fail_at = -1;
+            if (reached && rc != -12) fault("allocation %ld fails: %d", k, rc);
+            if (!reached) must(rc, "no allocation fails");
+            if (again) must(change(h), "again");
+            must(scylla_batch_solve(h, &p, 0, res.data()), "solve");
+            if (layout[1]) {
+                double r, c;
+                must(scylla_batch_time_passes(h, 1, &r, &c), "time_passes");
+                must(change(h), "at last");
+                must(scylla_batch_solve(h, &avg, 0, res.data()), "solve to the average");
+            }
+            scylla_batch_destroy(h);
+            if (!reached) break;
+            ++failed;
+            if (g_faults > 0) {
+                printf("(allocation %ld failed first, the call %s)\n", k, again ? "made again" : "not made again");
+                return;
+            }
+        }
+        if (failed == 0) fault("no allocation was reached");
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -442,6 +527,7 @@ int main(int argc, char **argv)
     auto arg = [&](int k) { return atoi(argv[k]); };
     if (what == "blends") blends(arg(2), arg(3), arg(4) != 0);
     else if (what == "uneven") uneven(arg(2), arg(3), arg(4));
+    else if (what == "allocations") allocations(argv[2], arg(3));
     else fault("unknown scenario");
     if (g_faults == 0) printf("ok\n");
     return g_faults == 0 ? 0 : 1;

@@ -41,3 +41,12 @@ def test_updates_read_their_own_staged_bits(driver, n, objectives):
 def test_one_large_lp_among_many_small_ones(driver, small, rows, cols):
     """No launch beyond 2^32 threads, no buffer of instances x the largest."""
     driver("uneven", small, rows, cols)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("call", ["layout:0,4,0,4", "layout:0,8,0,-16", "layout:2,8,4,8", "layout:-1,8,-1,8",
+                                  "layout:-2,4,-2,4", "layout:-3,8,-3,8", "layout:-6,8,-7,4", "solve"])
+def test_failed_allocations(driver, call, precision):
+    """Any allocation of a layout change or of a solve fails: the same call
+    made again works, and so does a solve without it."""
+    driver("allocations", call, precision)
