@@ -252,8 +252,8 @@ template <class V>
 void launch_setup_vectors(const SetupArgs<V> &a, hipStream_t s);
 // Norms of the instances [q0, q1) after their objective (and, with rows set,
 // their right-hand side) was written.  Instance q is summed in the pieces
-// [off[q], off[q + 1]) of the handle, whose partial sums are 4 doubles of part
-// each; off null: one piece an instance.
+// [off[q], off[q + 1]), whose partial sums are 4 doubles of part each; off
+// null: all pieces are q0's (q1 = q0 + 1), or every instance has one.
 constexpr int NORM_CHUNK = 2048, NORM_MAX_BLOCKS = 1024;
 __host__ __device__ inline int norm_blocks(int m, int n)
 {

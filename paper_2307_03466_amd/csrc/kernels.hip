@@ -2200,24 +2200,20 @@ __global__ __launch_bounds__(256) void k_norm_part(const NormArgs a, const Blend
 {
     __shared__ double red[4 * 4], sum[4];
     __shared__ int last;
-    int q = a.q0, piece = (int)blockIdx.x, first = 0;
-    if (!a.off) {
-        q += piece;
-        piece = 0;
-    } else {
-        first = a.off[q];
-        if (a.q1 - a.q0 > 1) {  // the instance that holds the piece
-            const int at = first + piece;
-            for (int hi = a.q1; hi - q > 1;) {
-                const int mid = q + (hi - q) / 2;
-                if (a.off[mid] <= at) q = mid;
-                else hi = mid;
-            }
-            first = a.off[q];
-            piece = at - first;
+    int q = a.q0, blk = (int)blockIdx.x, first = 0;
+    if (a.off) {  // the instance that holds the piece
+        const int at = a.off[q] + blk;
+        for (int hi = a.q1; hi - q > 1;) {
+            const int mid = q + (hi - q) / 2;
+            if (a.off[mid] <= at) q = mid;
+            else hi = mid;
         }
+        first = a.off[q];
+        blk = at - first;
+    } else if (a.q1 - q > 1) {
+        q += blk;
+        blk = 0;
     }
-    const int blk = piece;
     const InstInfo &I = a.info[q];
     const int m = I.row1 - I.row0, n = I.col1 - I.col0;
     const int nb = norm_blocks(m, n);

@@ -1742,10 +1742,15 @@ NormArgs norm_args(scylla_batch *h, int32_t q0, int32_t q1)
     a.st = h->st.as<InstState>();
     a.part = h->norm_part.as<double>();
     a.done = h->norm_done.as<int32_t>();
-    a.off = h->norm_off.as<int32_t>();
     a.q0 = q0;
     a.q1 = q1;
-    a.pieces = h->hnorm_off.empty() ? q1 - q0 : h->hnorm_off[q1] - h->hnorm_off[q0];
+    a.pieces = q1 - q0;
+    if (!h->hnorm_off.empty()) {
+        a.pieces = h->hnorm_off[q1] - h->hnorm_off[q0];
+        // (an update's instance needs no search)
+        if (q1 - q0 == 1) a.part += 4 * (size_t)h->hnorm_off[q0];
+        else a.off = h->norm_off.as<int32_t>();
+    }
     return a;
 }
 
