@@ -1621,9 +1621,9 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
         // under 1 %, and the GPU is not held for long.  With a time limit one
         // window, so that it is seen after each.
         const int64_t per = p->time_limit_s > 0.0 ? 1 : std::max(1, 4096 / R);
-        const int64_t checks = lim / R + (lim % R != 0 ? 2 : 1);
-        for (int64_t w = 0; w < checks; w += per) {
-            launch_windows_tiny(h, R, (int32_t)std::min(per, checks - w));
+        const int64_t end = lim / R + (lim % R != 0 ? 1 : 0);  // the check that reaches the limit
+        for (int64_t w = 0; w <= end; w += per) {
+            launch_windows_tiny(h, R, (int32_t)std::min(per - 1, end - w) + 1);
             HIPC(hipGetLastError());
             HIPC(hipEventRecord(h->ev, h->stream));
             HIPC(hipEventSynchronize(h->ev));

@@ -467,6 +467,24 @@ void uneven(int small, int rows, int cols)
     scylla_batch_destroy(h);
 }
 
+// The fused window with the largest iteration limit there is.
+void limit(int period)
+{
+    const Lp lp(5, 9, 2);
+    scylla_batch *h = create({lp.view()}, SCYLLA_FP64);
+    scylla_params p = solve_params(SCYLLA_FP64);
+    p.check_period = period;
+    scylla_result res;
+    for (int64_t lim : {INT64_MAX, INT64_MAX - 1, INT64_MAX - period, (int64_t)0, (int64_t)1, (int64_t)period}) {
+        p.iter_limit = lim;
+        g_launches.clear();
+        must(scylla_batch_solve(h, &p, 0, &res), "solve");
+        if (g_launches["k_tiny"] != 1 || res.status != ST_ITER)
+            fault("limit %lld: %ld launches, status %d", (long long)lim, g_launches["k_tiny"], res.status);
+    }
+    scylla_batch_destroy(h);
+}
+
 // Every allocation of a layout change or a solve fails once: the call says so,
 // and whatever follows, the same call again or a solve, launches nothing on
 // buffers that are not there.
@@ -528,6 +546,7 @@ int main(int argc, char **argv)
     if (what == "blends") blends(arg(2), arg(3), arg(4) != 0);
     else if (what == "uneven") uneven(arg(2), arg(3), arg(4));
     else if (what == "allocations") allocations(argv[2], arg(3));
+    else if (what == "limit") limit(arg(2));
     else fault("unknown scenario");
     if (g_faults == 0) printf("ok\n");
     return g_faults == 0 ? 0 : 1;

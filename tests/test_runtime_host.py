@@ -50,3 +50,10 @@ def test_failed_allocations(driver, call, precision):
     """Any allocation of a layout change or of a solve fails: the same call
     made again works, and so does a solve without it."""
     driver("allocations", call, precision)
+
+
+@pytest.mark.parametrize("period", [1, 3, 1024])
+def test_largest_iteration_limit(driver, period):
+    """The number of checks of a fused solve does not overflow: something is
+    launched, and the solve ends."""
+    driver("limit", period)
