@@ -1724,6 +1724,17 @@ static char *stage_room(scylla_batch *h, size_t bytes)
     return at;
 }
 
+// Updates are refused while the caller captures the handle's stream: a graph
+// that holds their launches would read the staging buffer again on every
+// replay, long after other updates filled it.  (Nothing is queued, and the
+// capture goes on.)
+static void refuse_capture(scylla_batch *h)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    HIPC(hipStreamIsCapturing(h->stream, &status));
+    if (status != hipStreamCaptureStatusNone) throw_err(-EIO, "the handle's stream is being captured");
+}
+
 static char *stage_data(scylla_batch *h, const void *src, size_t bytes)
 {
     char *at = stage_room(h, bytes);
@@ -1882,6 +1893,7 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
         const int32_t lo = h->col_off[inst], len = h->col_off[inst + 1] - lo;
         for (int32_t j = 0; j < len; ++j)
             if (!isfinite(c_hat[j])) throw_err(-EINVAL, "non-finite objective");
+        refuse_capture(h);
         // read by the kernel where it is staged (16 objectives and Hessians
         // of 10k columns with copies and casts of their own: 0.18 ms more)
         const char *at = stage_data(h, c_hat, sizeof(double) * (size_t)len);
@@ -1910,6 +1922,7 @@ int scylla_batch_set_quadratic(scylla_batch *h, int32_t inst, const double *q)
             for (int32_t j = 0; j < len; ++j)
                 if (!(q[j] >= 0.0) || !isfinite(q[j])) throw_err(-EINVAL, "q must be finite and >= 0");
         if (!q && !h->has_q) return 0;
+        refuse_capture(h);
         ensure_q(h);
         const char *at = q ? stage_data(h, q, sizeof(double) * (size_t)len) : nullptr;
         if (at) {
@@ -1938,6 +1951,7 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
         check_inst(h, inst);
         if (!xhat_bits) throw_err(-EINVAL, "xhat_bits is NULL");
         if (!isfinite(a) || !isfinite(kappa)) throw_err(-EINVAL, "a and kappa must be finite");
+        refuse_capture(h);
         const int32_t lo = h->col_off[inst], hi = h->col_off[inst + 1];
         const size_t nb = (size_t)(hi - lo + 7) / 8;
         // bits of up to 128k columns are read by the kernel where they are

@@ -485,6 +485,30 @@ void limit(int period)
     scylla_batch_destroy(h);
 }
 
+// Updates while the caller captures the handle's stream are refused and queue
+// nothing.
+void captured(int n)
+{
+    const Lp lp(4, n, 2);
+    scylla_batch *h = create({lp.view()}, SCYLLA_FP32);
+    std::vector<double> c(n, 2.0);
+    std::vector<uint8_t> bits((n + 7) / 8, 5);
+    must(scylla_batch_set_objective(h, 0, c.data()), "set_objective");
+    must(scylla_batch_set_quadratic(h, 0, c.data()), "set_quadratic");
+    must(hipStreamSynchronize(nullptr), "synchronize");
+    g_caller_captures = true;
+    const long before = g_launches["all"];
+    if (scylla_batch_set_objective(h, 0, c.data()) >= 0) fault("set_objective is accepted");
+    if (scylla_batch_set_quadratic(h, 0, c.data()) >= 0) fault("set_quadratic is accepted");
+    if (scylla_batch_set_quadratic(h, 0, nullptr) >= 0) fault("set_quadratic (none) is accepted");
+    if (scylla_batch_set_blend(h, 0, bits.data(), nullptr, 0.5, 1.0) >= 0) fault("set_blend is accepted");
+    if (scylla_batch_set_blend(h, 0, bits.data(), bits.data(), 0.5, 1.0) >= 0) fault("set_blend (bits) is accepted");
+    if (g_launches["all"] != before || !g_queue.empty()) fault("work was queued");
+    g_caller_captures = false;
+    must(scylla_batch_set_objective(h, 0, c.data()), "set_objective afterwards");
+    scylla_batch_destroy(h);
+}
+
 // Every allocation of a layout change or a solve fails once: the call says so,
 // and whatever follows, the same call again or a solve, launches nothing on
 // buffers that are not there.
@@ -547,6 +571,7 @@ int main(int argc, char **argv)
     else if (what == "uneven") uneven(arg(2), arg(3), arg(4));
     else if (what == "allocations") allocations(argv[2], arg(3));
     else if (what == "limit") limit(arg(2));
+    else if (what == "captured") captured(arg(2));
     else fault("unknown scenario");
     if (g_faults == 0) printf("ok\n");
     return g_faults == 0 ? 0 : 1;

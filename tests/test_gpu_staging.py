@@ -37,3 +37,32 @@ def test_bits_where_the_buffer_starts_over(first):
         for q, (r, c) in enumerate(zip(b.solve(tol=1e-300, iter_limit=0, autotune=0), (c0, c1, c2))):
             omega, rel = _expect(lps[q], c)
             assert abs(r["omega"] - omega) <= 1e-9 * omega and abs(r["rel_kkt"] - rel) <= 1e-9 * rel
+
+
+def test_updates_of_a_captured_stream_are_refused():
+    """A caller's graph must not hold launches that read the staging buffer;
+    the capture itself goes on, and the handle keeps its objective."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lp = _lp(5100, 3)
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    out = torch.zeros(8, device="cuda")
+    with pdhg.Batch([lp], precision=pdhg.FP64, stream=stream.cuda_stream) as b:
+        b.set_objective(0, lp.c)
+        b.solve(tol=1e-300, iter_limit=0, autotune=0)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            out.add_(1.0)
+            with pytest.raises(RuntimeError):
+                b.set_objective(0, 2.0 * lp.c)
+            with pytest.raises(RuntimeError):
+                b.set_blend(0, np.ones(lp.n, dtype=bool), 0.5, 1.0)
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert out.tolist() == [3.0] * 8
+        r = b.solve(tol=1e-300, iter_limit=0, autotune=0)[0]
+        omega, rel = _expect(lp, lp.c)
+        assert abs(r["omega"] - omega) <= 1e-9 * omega and abs(r["rel_kkt"] - rel) <= 1e-9 * rel

@@ -57,3 +57,9 @@ def test_largest_iteration_limit(driver, period):
     """The number of checks of a fused solve does not overflow: something is
     launched, and the solve ends."""
     driver("limit", period)
+
+
+@pytest.mark.parametrize("n", [50, 131000, 140000])
+def test_updates_of_a_captured_stream_are_refused(driver, n):
+    """Staged in place, staged whole, and larger than the staging buffer."""
+    driver("captured", n)
