@@ -683,14 +683,16 @@ hipGraphExec_t capture_iters(scylla_batch *h, int32_t R)
     return ex;
 }
 
-void ensure_graph(scylla_batch *h, int32_t R)
+// True if the graph had to be made.
+bool ensure_graph(scylla_batch *h, int32_t R)
 {
-    if (h->gexec && h->graph_R == R && h->graph_adapt == h->adaptive && h->graph_avg == h->avg_on) return;
+    if (h->gexec && h->graph_R == R && h->graph_adapt == h->adaptive && h->graph_avg == h->avg_on) return false;
     invalidate_graph(h);
     h->gexec = capture_iters(h, R);
     h->graph_R = R;
     h->graph_adapt = h->adaptive;
     h->graph_avg = h->avg_on;
+    return true;
 }
 
 // Partials of the running average's check.
@@ -1567,7 +1569,7 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
     }
     if (h->vbytes == 4) begin_solve<float>(h, p, warm, k_limits ? h->limits : nullptr, q0, q1);
     else begin_solve<double>(h, p, warm, k_limits ? h->limits : nullptr, q0, q1);
-    const double t0 = now_s();
+    double t0 = now_s();
     const int32_t R = p->check_period;
     auto running = [&](int32_t q) { return h->pinned[q].status == ST_RUN; };
     auto any_running = [&]() {
@@ -1654,7 +1656,10 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
                 else enqueue_iters<double>(h, (int32_t)n, h->stream);
                 HIPC(hipGetLastError());
             } else {
-                if (!h->cexec) ensure_graph(h, R);
+                // (made while the first check runs, once for a layout and
+                // period: not the loop's time)
+                const double tg = now_s();
+                if (!h->cexec && ensure_graph(h, R)) t0 += now_s() - tg;
                 HIPC(hipGraphLaunch(h->cexec ? h->cexec : h->gexec, h->stream));
             }
         }

@@ -509,6 +509,27 @@ void captured(int n)
     scylla_batch_destroy(h);
 }
 
+// A graph that takes long to make (once for a layout and check period) does not
+// use up a solve's time limit, nor count as its time.
+void slow_graph()
+{
+    const Lp lp(300, 500, 3);
+    scylla_batch *h = create({lp.view()}, SCYLLA_FP32);
+    scylla_params p = solve_params(SCYLLA_FP32);
+    p.fused_window = 0;
+    p.iter_limit = 1 << 20;
+    p.time_limit_s = 0.25;
+    g_instantiate_ms = 500;
+    for (int k = 0; k < 2; ++k) {
+        g_checks_to_run = 4;
+        scylla_result res;
+        must(scylla_batch_solve(h, &p, 0, &res), "solve");
+        if (g_launches["k_force_stop"] != 0) fault("solve %d was stopped", k);
+        if (res.solve_seconds > 0.25) fault("solve %d took %g s", k, res.solve_seconds);
+    }
+    scylla_batch_destroy(h);
+}
+
 // Every allocation of a layout change or a solve fails once: the call says so,
 // and whatever follows, the same call again or a solve, launches nothing on
 // buffers that are not there.
@@ -572,6 +593,7 @@ int main(int argc, char **argv)
     else if (what == "allocations") allocations(argv[2], arg(3));
     else if (what == "limit") limit(arg(2));
     else if (what == "captured") captured(arg(2));
+    else if (what == "slow_graph") slow_graph();
     else fault("unknown scenario");
     if (g_faults == 0) printf("ok\n");
     return g_faults == 0 ? 0 : 1;

@@ -63,3 +63,7 @@ def test_largest_iteration_limit(driver, period):
 def test_updates_of_a_captured_stream_are_refused(driver, n):
     """Staged in place, staged whole, and larger than the staging buffer."""
     driver("captured", n)
+
+
+def test_the_graph_is_not_the_loops_time(driver):
+    driver("slow_graph")
