@@ -300,7 +300,10 @@ typedef struct {
     int32_t count, precision, format;
     int32_t fused_eligible; /* 1 if every instance fits the fused window  */
     int64_t m_total, n_total, nnz_total;
-    int32_t row_chunk, col_chunk; /* tile sizes in use (nonzeros per tile) */
+    int32_t row_chunk, col_chunk; /* tile sizes in use (nonzeros per tile):
+                                     512 to 4096, or one that only the tuner
+                                     chooses, 256 (at most 262144 nonzeros)
+                                     or 8192 (sorted tiles)                */
     int32_t long_rows, long_cols; /* rows / columns split over several tiles */
     int32_t row_blocks, col_blocks; /* layout of each pass: 0 normal, 2, 4 or
                                        8 gather blocks, -1 LDS-staged, -6
@@ -308,7 +311,10 @@ typedef struct {
     int32_t row_staged_nnz, col_staged_nnz; /* staged tile size (nonzeros)  */
     int32_t row_staged_variant, col_staged_variant; /* staged kernel variant
                                        bits: 1 operand prefetch, 2 sub-tiles
-                                       of 8192 nonzeros (else 4096)         */
+                                       of 8192 nonzeros (else 4096); normal
+                                       layout: 4 = sorted tiles, the entries
+                                       of a tile in the order of what they
+                                       gather (the tuner's choice only)      */
     int32_t row_sliced, col_sliced; /* instances of an LDS-staged pass whose
                                        gathered vector is processed in LDS
                                        slices (partial sums + row combine)   */
@@ -324,18 +330,20 @@ typedef struct {
                                        LDS, rows reduced in registers        */
     int32_t row_cached, col_cached; /* 1: the pass reads the matrix with
                                        plain (cacheable) loads, 0: with
-                                       non-temporal loads                    */
+                                       non-temporal loads (in FP64, always
+                                       outside the normal layout)            */
 } scylla_batch_info;
 int scylla_batch_get_info(scylla_batch *h, scylla_batch_info *info);
 
-/* Matrix load policy of the iteration passes (FP32 path; the autotuner
- * chooses it by timing both passes together, a pinned layout starts with
- * 0): 1 = plain loads, which the device's last-level (Infinity) cache
- * keeps across iterations when an iteration's data fits in it, 0 =
- * non-temporal loads that stream past the caches.  Results do not depend
- * on it.  (For FP64 handles this call keeps non-temporal loads; the tuner may
- * choose plain ones for normal tiles.)  Call after scylla_batch_set_layout (which resets it).  Returns 0,
- * or -EINVAL (NULL handle, flags not 0 or 1). */
+/* Matrix load policy of the iteration passes (the autotuner chooses it by
+ * timing both passes together, a pinned layout starts with 0): 1 = plain
+ * loads, which the device's last-level (Infinity) cache keeps across
+ * iterations when an iteration's data fits in it, 0 = non-temporal loads that
+ * stream past the caches.  Results do not depend on it.  FP32 handles: an FP64
+ * handle accepts the call and goes back to non-temporal loads, whatever the
+ * flags (plain ones, in its normal layout, are the tuner's choice only).  Call
+ * after scylla_batch_set_layout (which resets it).  Returns 0, or -EINVAL (NULL
+ * handle, flags not 0 or 1). */
 int scylla_batch_set_cached_loads(scylla_batch *h, int32_t row_cached, int32_t col_cached);
 
 /* ------------------------------------------------------ pump loop
@@ -558,8 +566,12 @@ int scylla_batch_pump_ex(scylla_batch *h, const scylla_params *params, const uin
                          const scylla_pump_params *opt, scylla_pump_record *records,
                          scylla_pump_outcome *outcome, double *x_out);
 
-/* Pins the tile plan of both passes instead of autotuning it.  The
- * floating-point summation order (so the last bits of the iterates) is a
+/* Pins the tile plan of both passes instead of autotuning it.  (The tuner has
+ * more plans than this call: staged tiles of other sizes and variants, sorted
+ * tiles, and tiles of 256 or 8192 nonzeros, see scylla_batch_info.  What it chose
+ * is kept, and can be pinned, by the file that the environment variable
+ * SCYLLA_TUNE_CACHE names: one line a shape, read by a process's first tuning.)
+ * The floating-point summation order (so the last bits of the iterates) is a
  * function of the plan; a pinned plan makes results reproducible across
  * runs and devices.  *_blocks: 0 = normal layout, 2, 4 or 8 = gather-blocked
  * layout with that many blocks (one per four XCDs, per XCD pair or per XCD), -1 = LDS-staged

@@ -495,16 +495,21 @@ void ensure_layout(scylla_batch *h)
     laid_out(h);
 }
 
+// Whether the iteration passes of o read the matrix with plain loads: the
+// orientation's policy, in FP64 where there are kernels for both, in normal
+// tiles (an iteration of a 200k x 400k LP, 100 MB, 40 -> 36 us).
+bool plain_loads(const scylla_batch *h, const OrientRT &o)
+{
+    return o.cached && (h->vbytes == 4 || !(o.staged || o.direct || o.blocked));
+}
+
 template <class V>
 void launch_orient(scylla_batch *h, OrientRT &o, const PassArgs<V> &p, int jw, bool check, hipStream_t s)
 {
     const int dir = o.row ? DIR_ROW : DIR_COL;
     // the iteration passes read the matrix with the orientation's load
     // policy (the checks, once per window, stream it)
-    // (FP64: in normal tiles, which have kernels for both; an iteration of a
-    // 200k x 400k LP, 100 MB, 40 -> 36 us)
-    const bool plain = o.cached && (h->vbytes == 4 || !(o.staged || o.direct || o.blocked));
-    const int ifmt = h->fmt | (plain ? (int)FMT_CACHED : 0) | (o.sorted ? (int)FMT_SORTED : 0);
+    const int ifmt = h->fmt | (plain_loads(h, o) ? (int)FMT_CACHED : 0) | (o.sorted ? (int)FMT_SORTED : 0);
     // iteration launches take the compacted tile lists when there are any
     const bool cmp = o.cmp && !check;
     auto n4 = [](const std::vector<int32_t> &v) { return (int32_t)(v.size() / 4); };
@@ -2128,8 +2133,8 @@ int scylla_batch_get_info(scylla_batch *h, scylla_batch_info *info)
         info->col_blocks = h->ocol.direct ? -6 : (h->ocol.staged ? -1 : (h->ocol.blocked ? h->ocol.bh.B : 0));
         info->row_staged_nnz = h->orow.staged ? h->orow.staged_nnz : 0;
         info->col_staged_nnz = h->ocol.staged ? h->ocol.staged_nnz : 0;
-        info->row_staged_variant = h->orow.staged ? h->orow.svariant : 0;
-        info->col_staged_variant = h->ocol.staged ? h->ocol.svariant : 0;
+        info->row_staged_variant = h->orow.staged ? h->orow.svariant : (h->orow.sorted ? 4 : 0);
+        info->col_staged_variant = h->ocol.staged ? h->ocol.svariant : (h->ocol.sorted ? 4 : 0);
         for (int32_t q = 0; q < h->count; ++q) {
             info->row_sliced += h->orow.sliced && h->orow.xplan.sliced[q];
             info->col_sliced += h->ocol.sliced && h->ocol.xplan.sliced[q];
@@ -2144,8 +2149,8 @@ int scylla_batch_get_info(scylla_batch *h, scylla_batch_info *info)
         }
         info->row_staged_nnz = h->orow.direct ? h->orow.dnnz : info->row_staged_nnz;
         info->col_staged_nnz = h->ocol.direct ? h->ocol.dnnz : info->col_staged_nnz;
-        info->row_cached = h->orow.cached ? 1 : 0;
-        info->col_cached = h->ocol.cached ? 1 : 0;
+        info->row_cached = plain_loads(h, h->orow) ? 1 : 0;
+        info->col_cached = plain_loads(h, h->ocol) ? 1 : 0;
         return 0;
     });
 }
