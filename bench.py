@@ -101,7 +101,8 @@ def pass_kernels(info, is_col):
     launches in the layout `info` describes, or None for the LDS-staged
     layouts."""
     blocks = info["col_blocks"] if is_col else info["row_blocks"]
-    # the kernels' format parameter carries the cached-load flag (8)
+    # the kernels' format parameter carries the cached-load flag (8) and, in
+    # normal tiles, the sorted one (16)
     fmt = info["format"] | (8 if info.get("col_cached" if is_col else "row_cached") else 0)
     nt = info["col_tile_threads" if is_col else "row_tile_threads"] or 256
     ept = (info["col_chunk"] if is_col else info["row_chunk"]) // nt
@@ -109,7 +110,10 @@ def pass_kernels(info, is_col):
         return [f"void k_bpart<float, float, {fmt}, {nt}, {ept}>(PassArgs<float>, int, int)",
                 f"void k_bcombine<float, {1 if is_col else 0}>(PassArgs<float>, int)"]
     if blocks == 0:
-        return [f"void k_pass<float, {fmt}, {1 if is_col else 0}, {nt}, {ept}>(PassArgs<float>, int)"]
+        if info.get("col_staged_variant" if is_col else "row_staged_variant"):
+            fmt |= 16
+        name = "k_pass" if info.get("count", 1) == 1 else "k_pass_batch"
+        return [f"void {name}<float, {fmt}, {1 if is_col else 0}, {nt}, {ept}>(PassArgs<float>, int)"]
     return None
 
 

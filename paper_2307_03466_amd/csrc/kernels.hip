@@ -388,7 +388,7 @@ __device__ __forceinline__ TileRange tile_range(const int4 &T)
 
 // ------------------------------------------------------- iteration pass
 template <class V, int FMT, int DIR, int NT, int EPT, bool EARLY>
-__global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
+__device__ __forceinline__ void pass_tile(const PassArgs<V> &p, const int jw)
 {
     constexpr int CH = NT * EPT;
     __shared__ V prod[CH];
@@ -463,6 +463,19 @@ __global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
             p.ipart[2 * t + 1] = ip[1];
         }
     }
+}
+
+template <class V, int FMT, int DIR, int NT, int EPT>
+__global__ __launch_bounds__(NT) void k_pass(const PassArgs<V> p, const int jw)
+{
+    pass_tile<V, FMT, DIR, NT, EPT, true>(p, jw);
+}
+
+// The same over a batch (entries loaded once the instance is known to run).
+template <class V, int FMT, int DIR, int NT, int EPT>
+__global__ __launch_bounds__(NT) void k_pass_batch(const PassArgs<V> p, const int jw)
+{
+    pass_tile<V, FMT, DIR, NT, EPT, false>(p, jw);
 }
 
 // ------------------------------------------------------- sorted tiles
@@ -2506,8 +2519,8 @@ __global__ __launch_bounds__(256) void k_mip_reduce(const InstInfo *__restrict__
 template <class V, int FMT, int DIR, int NT, int EPT>
 static void launch_pass_t(const PassArgs<V> &p, int jw, hipStream_t s)
 {
-    if (p.early) hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT, true>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
-    else hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT, false>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
+    if (p.early) hipLaunchKernelGGL((k_pass<V, FMT, DIR, NT, EPT>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
+    else hipLaunchKernelGGL((k_pass_batch<V, FMT, DIR, NT, EPT>), dim3(p.ntiles), dim3(NT), 0, s, p, jw);
 }
 
 template <class V, int FMT, int DIR, int NT, int EPT>

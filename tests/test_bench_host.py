@@ -121,3 +121,36 @@ def test_pass_kernel_names_match_the_traffic_table():
     assert bench.measured_traffic(["void k_pass<float, 0, 1, 1024, 8>(PassArgs<float>, int)"]) is None
     info["col_blocks"] = -1
     assert bench.pass_kernels(info, True) is None
+
+
+def test_pass_kernel_names_are_the_librarys():
+    """Whatever tile, load policy, order of entries and instance count a
+    handle reports, the names looked up are kernels that the library has."""
+    import subprocess
+    from paper_2307_03466_amd import pdhg
+    if not os.path.exists(pdhg.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    names = {ln.split(" ", 2)[2].replace("scy::", "").replace("__device_stub__", "")
+             for ln in subprocess.run(["nm", "-C", pdhg.LIB_PATH], capture_output=True, text=True).stdout.splitlines()
+             if "__device_stub__" in ln}
+    tiles = [(256, 256), (256, 512), (256, 1024), (256, 2048), (256, 4096), (1024, 2048), (1024, 4096)]
+    seen = set()
+    for fmt in (0, 1, 2):
+        for cached in (0, 1):
+            for count in (1, 3):
+                for blocks in (0, 2):
+                    for nt, chunk in tiles + ([(1024, 8192)] if fmt == 0 and blocks == 0 else []):
+                        for variant in (0, 4):
+                            if (variant == 4 and (fmt != 0 or blocks or nt != 1024 or chunk < 4096)) or \
+                                    (variant == 0 and chunk == 8192) or (blocks and chunk == 256):
+                                continue
+                            info = dict(format=fmt, count=count)
+                            for d in ("row", "col"):
+                                info.update({d + "_blocks": blocks, d + "_chunk": chunk, d + "_tile_threads": nt,
+                                             d + "_cached": cached, d + "_staged_variant": variant})
+                            for is_col in (True, False):
+                                got = bench.pass_kernels(info, is_col)
+                                assert got and set(got) <= names, (info, got)
+                                seen.update(got)
+    assert any("k_pass_batch" in n for n in seen) and any("<float, 24," in n for n in seen)
