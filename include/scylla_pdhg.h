@@ -220,7 +220,14 @@ int scylla_batch_create(const scylla_lp *lps, int32_t count, int32_t precision, 
 void scylla_batch_destroy(scylla_batch *h);
 
 /* Replaces the objective of instance `inst` by c_hat[n_inst] (host, finite).
- * The original objective passed at creation is kept for blending. */
+ * The original objective passed at creation is kept for blending.
+ *
+ * This call, scylla_batch_set_quadratic and scylla_batch_set_blend order the
+ * update on the handle's stream and need not wait for it (whether they do
+ * depends on its size): the host arrays may be reused on return, every later
+ * call on the handle sees the update, and a device error in it is reported by
+ * a later call that waits.  While the stream is being captured into a graph
+ * they return -EIO with nothing queued. */
 int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_hat);
 
 /* Pump objective update on the device (Algorithm 1, objective update):
