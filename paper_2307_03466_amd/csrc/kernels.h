@@ -292,9 +292,10 @@ void launch_put(const double *src, double *dst, V *dst_v, int len, hipStream_t s
 void launch_norms(const NormArgs &a, hipStream_t s);
 template <class V>
 void launch_cast(const double *src, V *dst, int len, hipStream_t s);
+// Start points of the columns [clo, chi) and rows [rlo, rhi) projected.
 template <class V>
-void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const uint8_t *sense, int rlo,
-                    int rhi, int zero, hipStream_t s);
+void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const uint8_t *sense, int rlo, int rhi,
+                    hipStream_t s);
 // MIP-feasibility of x per instance (rows within tol (1 + |b_i|), bounds
 // and integrality within tol): rbad [m], cbad [n] scratch flags,
 // feasible [count] = 1 / 0; is_int null: all integer.

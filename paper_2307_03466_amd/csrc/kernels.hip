@@ -2271,17 +2271,30 @@ __global__ void k_cast(const double *src, V *dst, int len)
     if (i < len) dst[i] = (V)src[i];
 }
 
-// Start point: x = proj_[l,u](x), y = proj_Y(y) on [lo, hi) ranges; zero
-// first when `zero` is set.
+// Start points: proj_[l,u](v) of column j and proj_Y(v) of a row.
 template <class V>
-__global__ void k_project_primal(V *x, const V *l, const V *u, int lo, int hi, int zero)
+__device__ __forceinline__ V project_x(V v, const V *l, const V *u, int j)
 {
-    const int j = lo + blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= hi) return;
-    V v = zero ? (V)0 : x[j];
     v = v < l[j] ? l[j] : v;
-    v = v > u[j] ? u[j] : v;
-    x[j] = v;
+    return v > u[j] ? u[j] : v;
+}
+
+template <class V>
+__device__ __forceinline__ V project_y(V v, uint8_t sense)
+{
+    if (sense == 'G') return v > (V)0 ? v : (V)0;
+    if (sense == 'L') return v < (V)0 ? v : (V)0;
+    return v;
+}
+
+// x on [clo, clo + nc) and y on [rlo, rlo + nr), both in place.
+template <class V>
+__global__ __launch_bounds__(256) void k_project(V *x, const V *l, const V *u, int clo, int nc, V *y,
+                                                 const uint8_t *sense, int rlo, int nr)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < nc) x[clo + i] = project_x(x[clo + i], l, u, clo + i);
+    if (i < nr) y[rlo + i] = project_y(y[rlo + i], sense[rlo + i]);
 }
 
 // Start of a solve in one launch: thread q sets instance q's state (and its
@@ -2294,18 +2307,11 @@ __global__ __launch_bounds__(256) void k_begin(const BeginArgs<V> a)
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < a.chi - a.clo) {
         const int j = a.clo + i;
-        V v = a.warm ? a.x[j] : (V)0;
-        v = v < a.l[j] ? a.l[j] : v;
-        v = v > a.u[j] ? a.u[j] : v;
-        a.x[j] = v;
+        a.x[j] = project_x(a.warm ? a.x[j] : (V)0, a.l, a.u, j);
     }
     if (i < a.rhi - a.rlo) {
         const int r = a.rlo + i;
-        V v = a.warm ? a.y[r] : (V)0;
-        const uint8_t sn = a.sense[r];
-        if (sn == 'G') v = v > (V)0 ? v : (V)0;
-        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
-        a.y[r] = v;
+        a.y[r] = project_y(a.warm ? a.y[r] : (V)0, a.sense[r]);
     }
     if (i >= a.count) return;
     InstState &S = a.st[i];
@@ -2373,19 +2379,8 @@ __global__ __launch_bounds__(256) void k_start_set(const StartArgs<V> a)
 {
     if (*a.flag) return;
     const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < a.n) {
-        V v = a.x0 ? (V)a.x0[k] : a.x[k];
-        v = v < a.l[k] ? a.l[k] : v;
-        v = v > a.u[k] ? a.u[k] : v;
-        a.x[k] = v;
-    }
-    if (k < a.m) {
-        V v = a.y0 ? (V)a.y0[k] : a.y[k];
-        const uint8_t sn = a.sense[k];
-        if (sn == 'G') v = v > (V)0 ? v : (V)0;
-        else if (sn == 'L') v = v < (V)0 ? v : (V)0;
-        a.y[k] = v;
-    }
+    if (k < a.n) a.x[k] = project_x(a.x0 ? (V)a.x0[k] : a.x[k], a.l, a.u, k);
+    if (k < a.m) a.y[k] = project_y(a.y0 ? (V)a.y0[k] : a.y[k], a.sense[k]);
     if (a.omega && k < a.count && a.omega[k] > 0.0) a.st[k].omega = a.omega[k];
 }
 
@@ -2406,18 +2401,6 @@ void launch_start(const StartArgs<V> &a, int *host_flag, hipStream_t s)
     if (a.count > len) len = a.count;
     hipLaunchKernelGGL(k_start_set<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_start_flag, dim3(1), dim3(1), 0, s, a.flag, host_flag);
-}
-
-template <class V>
-__global__ void k_project_dual(V *y, const uint8_t *sense, int lo, int hi, int zero)
-{
-    const int i = lo + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= hi) return;
-    V v = zero ? (V)0 : y[i];
-    const uint8_t sn = sense[i];
-    if (sn == 'G') v = v > (V)0 ? v : (V)0;
-    else if (sn == 'L') v = v < (V)0 ? v : (V)0;
-    y[i] = v;
 }
 
 // ------------------------------------------------ MIP feasibility
@@ -2892,13 +2875,13 @@ void launch_cast(const double *src, V *dst, int len, hipStream_t s)
 }
 
 template <class V>
-void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const uint8_t *sense, int rlo,
-                    int rhi, int zero, hipStream_t s)
+void launch_project(V *x, const V *l, const V *u, int clo, int chi, V *y, const uint8_t *sense, int rlo, int rhi,
+                    hipStream_t s)
 {
-    if (chi > clo)
-        hipLaunchKernelGGL(k_project_primal<V>, dim3((chi - clo + 255) / 256), dim3(256), 0, s, x, l, u, clo, chi, zero);
-    if (rhi > rlo)
-        hipLaunchKernelGGL(k_project_dual<V>, dim3((rhi - rlo + 255) / 256), dim3(256), 0, s, y, sense, rlo, rhi, zero);
+    const int nc = chi - clo, nr = rhi - rlo, len = nc > nr ? nc : nr;
+    if (len > 0)
+        hipLaunchKernelGGL(k_project<V>, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, x, l, u, clo, nc, y, sense,
+                           rlo, nr);
 }
 
 template <class V>
@@ -2937,7 +2920,7 @@ void launch_mip_check(const MatView &M, int fmt, int m, int n, int count, const 
     template void launch_start<V>(const StartArgs<V> &, int *, hipStream_t);                           \
     template void launch_cast<V>(const double *, V *, int, hipStream_t);                               \
     template void launch_project<V>(V *, const V *, const V *, int, int, V *, const uint8_t *, int, int, \
-                                    int, hipStream_t);                                                 \
+                                    hipStream_t);                                                      \
     template void launch_blend<V>(const NormArgs &, const BlendArgs &, hipStream_t);                   \
     template void launch_objective<V>(const NormArgs &, const double *, V *, hipStream_t);             \
     template void launch_put<V>(const double *, double *, V *, int, hipStream_t);                      \

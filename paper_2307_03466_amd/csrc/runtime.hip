@@ -1454,12 +1454,10 @@ void check_inst(scylla_batch *h, int32_t inst)
 }
 
 template <class V>
-void project_start(scylla_batch *h, int32_t inst, int zero)
+void project_start(scylla_batch *h, int32_t inst)
 {
-    const int clo = inst < 0 ? 0 : h->col_off[inst], chi = inst < 0 ? h->N : h->col_off[inst + 1];
-    const int rlo = inst < 0 ? 0 : h->row_off[inst], rhi = inst < 0 ? h->M : h->row_off[inst + 1];
-    launch_project<V>(h->x.as<V>(), h->lv.as<V>(), h->uv.as<V>(), clo, chi, h->y.as<V>(),
-                      h->sense.as<uint8_t>(), rlo, rhi, zero, h->stream);
+    launch_project<V>(h->x.as<V>(), h->lv.as<V>(), h->uv.as<V>(), h->col_off[inst], h->col_off[inst + 1], h->y.as<V>(),
+                      h->sense.as<uint8_t>(), h->row_off[inst], h->row_off[inst + 1], h->stream);
 }
 
 template <class V>
@@ -2002,11 +2000,11 @@ int scylla_batch_set_start(scylla_batch *h, int32_t inst, const double *x0, cons
         if (h->vbytes == 4) {
             if (x0) put_range<float>(h, h->x, clo, clen, x0);
             if (y0) put_range<float>(h, h->y, rlo, rlen, y0);
-            project_start<float>(h, inst, 0);
+            project_start<float>(h, inst);
         } else {
             if (x0) put_range<double>(h, h->x, clo, clen, x0);
             if (y0) put_range<double>(h, h->y, rlo, rlen, y0);
-            project_start<double>(h, inst, 0);
+            project_start<double>(h, inst);
         }
         if (omega0 > 0.0) {
             std::vector<InstState> st;
