@@ -1571,9 +1571,13 @@ constexpr int TINY_K = sizeof(V) == 8 ? 8 : 16;
 // entries.  A pass is bound by instruction issue: its update costs a wave
 // about as much as 20 entries, so the rows take five eighths of the threads at
 // most (two or three waves a SIMD) rather than all of them, and more lanes only
-// where their entries would not fit the registers.  (An iteration of a 200 x
-// 500 set cover with all threads 0.82 us in either precision, now 0.76 us in
-// FP64 and 0.68 us in FP32.)
+// where their entries would not fit the registers.  Set covers of 20 x 50 to
+// 600 x 200, an iteration with its share of the checks: with all threads
+// 0.84-1.06 us, with five eighths 0.75-0.94 (200 x 500: 1.01 -> 0.88 in FP32,
+// 1.03 -> 0.90 in FP64; equal where both give the same lanes, from 230 x 575);
+// adaptive steps 2.65-3.27 -> 2.51-2.98.  Three quarters of the threads differ
+// from five eighths at 350 columns only (0.87 against 0.82).  One half is up to
+// 0.1 us faster below 130 rows or 320 columns and equal above.
 template <class V>
 __device__ __forceinline__ int tiny_lanes(int rows, int longest)
 {

@@ -192,6 +192,11 @@ void set_plan(scylla_batch *h, OrientRT &o, int32_t B, int32_t ept)
 }
 
 // Whether this handle's entries can be sorted by tile: FP64, or packed words.
+// There are no sorted kernels for FP32 and BF16 values.  (A trial of them, 128
+// iterations with FP32 values: 64 uneven LPs 11.1 -> 7.9 ms, 64 20k x 40k ones
+// 11.7 -> 10.5, a skewed one of 10M nonzeros 12.3 -> 10.5, 200k x 400k 4.1 ->
+// 3.7, 1M x 2M 18.0 -> 17.7 and with BF16 values 16.6 -> 17.4, where sorting was
+// not chosen and the tuner's picks differ.)
 bool can_sort(const scylla_batch *h, const OrientRT &o)
 {
     return (h->fmt == FMT_F64 || h->fmt == FMT_PACKED) && o.rows > 0 && h->NNZ > 0;
@@ -1621,10 +1626,14 @@ int batch_solve_impl(scylla_batch *h, const scylla_params *p, int32_t warm, scyl
     if (h->avg_on && !tiny) ensure_avg_parts(h);
 
     if (tiny) {
-        // As many windows a launch as make 4096 iterations (6-10 ms on a
+        // As many windows a launch as make 4096 iterations (4-12 ms on a
         // 200 x 500 set cover): the host's turn between launches then costs
         // under 1 %, and the GPU is not held for long.  With a time limit one
-        // window, so that it is seen after each.
+        // window and a wait, so that it is seen after each: 512 iterations of
+        // that cover in windows of 64, 16, 4 and 1 take 0.70, 1.5, 4.6 and 17
+        // ms, in launches of 4096 0.49, 0.74, 1.7 and 5.6 (one window a graph,
+        // two graphs ahead of the host and the matrix read from LDS: 1.3, 2.1,
+        // 5.1 and 17).
         const int64_t per = p->time_limit_s > 0.0 ? 1 : std::max(1, 4096 / R);
         const int64_t end = lim / R + (lim % R != 0 ? 1 : 0);  // the check that reaches the limit
         for (int64_t w = 0; w <= end; w += per) {

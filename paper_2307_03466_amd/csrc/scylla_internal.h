@@ -77,8 +77,9 @@ struct InstInfo {
                                      // row / column pass, up to three each
 };
 
-// Tile of an orientation: {a, b, inst, slot}.  slot < 0: rows [a, b);
-// slot >= 0: nonzeros [a, b) of one long row, partial sum goes to slot.
+// Tile of an orientation: {a, b, inst, slot}.  slot < 0: rows [a, b) (on the
+// device in the form that seal_tiles gives normal tiles); slot >= 0: nonzeros
+// [a, b) of one long row, partial sum goes to slot.
 // Long row descriptor: {row, first slot, number of segments, inst}.
 
 // ----------------------------------------------------------- host side
@@ -219,7 +220,8 @@ void plan_tiles(const std::vector<int32_t> &ptr, const std::vector<int32_t> &ins
 // The device form of normal tiles: a tile of rows {r0, r1, inst, -1} becomes
 // {r0, rows | nonzeros << TILE_ROW_BITS, inst, ~first nonzero}, so that a
 // workgroup knows its nonzeros without reading row pointers; segment tiles
-// stay.  Needs at most 2047 rows and 2^20 nonzeros a tile.
+// stay.  Needs at most 2047 rows and fewer than 2^20 nonzeros a tile (the plans'
+// have at most 2047 and 8192).
 constexpr int32_t TILE_ROW_BITS = 11;
 void seal_tiles(const std::vector<int32_t> &ptr, std::vector<int32_t> &tiles);
 
