@@ -1986,7 +1986,7 @@ int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bi
             return d.as<uint8_t>();
         };
         const uint8_t *xb = put(at, h->bits_tmp, xhat_bits);
-        const uint8_t *ib = int_bits ? put(at + ib_at, h->ibits_tmp, int_bits) : nullptr;
+        const uint8_t *ib = int_bits ? put(at ? at + ib_at : nullptr, h->ibits_tmp, int_bits) : nullptr;
         blend_instance(h, inst, xb, ib, a, kappa);
         HIPC(hipGetLastError());
         if (!in_place) HIPC(hipStreamSynchronize(h->stream));

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from paper_2307_03466_amd import instances as I
 from test_gpu_norms import M, _expect, _lp
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +26,21 @@ def test_one_large_lp_among_many_small_ones(before, after):
             for k, r in zip(which, b.solve(tol=1e-300, iter_limit=0, autotune=0)):
                 assert abs(r["omega"] - want[k][0]) <= tol[k] * want[k][0]
                 assert abs(r["rel_kkt"] - want[k][1]) <= tol[k] * want[k][1]
+
+
+def test_ranges_of_instances():
+    """The L2 loop refreshes the norms of one group of instances at a time:
+    two groups, of instances with different numbers of pieces, give the
+    results of one."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lps = [I.cover_knapsack(m, seed=m) for m in (2500, 300, 700, 5200, 400, 1500)]
+    out = []
+    with pdhg.Batch(lps) as b:
+        b.set_layout(0, 4, 0, 4)
+        for pipeline in (0, 1):
+            recs, fin, x = b.pump_ex(pump=dict(rounds=4, early_exit=0, distance=2, pipeline=pipeline), iter_limit=640)
+            out.append(([[(r["iterations"], r["rel_kkt"], r["xhat_obj"]) for r in k] for k in recs], x))
+    assert out[0][0] == out[1][0]
+    assert np.array_equal(out[0][1], out[1][1])
