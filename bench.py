@@ -637,7 +637,7 @@ def main():
                    "matrix_format": info["format_name"],
                    "layout": {"row_blocks": info["row_blocks"], "row_chunk": info["row_chunk"],
                               "col_blocks": info["col_blocks"], "col_chunk": info["col_chunk"]},
-                   "step": f"KKT check + decision + {R} PDHG iterations (one hipGraph)"},
+                   "step": f"KKT check + decision + {R} PDHG iterations (the iterations one hipGraph)"},
         "roofline": roofline,
         "roofline_passes": both,
         "path_GBps": round(path_bytes * f32["iter_per_s"] / 1e9, 1),

@@ -230,14 +230,6 @@ void scylla_batch_destroy(scylla_batch *h);
  * they return -EIO with nothing queued. */
 int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_hat);
 
-/* Pump objective update on the device (Algorithm 1, objective update):
- *   c_hat_j = a * kappa * c_j + (1 - a) * g_j
- * with c the objective given at creation, g_j = +1 if bit j of xhat_bits is 0
- * (rounded value at its lower bound), -1 if it is 1 (at its upper bound), and
- * g_j = 0 where bit j of int_bits is 0 (continuous variable).  Bits are
- * little-endian within each byte; each array holds ceil(n_inst / 8) bytes
- * (host).  int_bits may be NULL (all integer).  Typically a = 0.9^K and
- * kappa = sqrt(|I|) / ||c||_2. */
 /* Diagonal Hessian of instance `inst`'s objective: the handle then solves
  * min c_hat^T x + x^T diag(q) x / 2 (the diagonal-Hessian QPs Section 5
  * proposes for PDHG): the primal step solves each coordinate's proximal
@@ -248,6 +240,14 @@ int scylla_batch_set_objective(scylla_batch *h, int32_t inst, const double *c_ha
  * -EINVAL. */
 int scylla_batch_set_quadratic(scylla_batch *h, int32_t inst, const double *q);
 
+/* Pump objective update on the device (Algorithm 1, objective update):
+ *   c_hat_j = a * kappa * c_j + (1 - a) * g_j
+ * with c the objective given at creation, g_j = +1 if bit j of xhat_bits is 0
+ * (rounded value at its lower bound), -1 if it is 1 (at its upper bound), and
+ * g_j = 0 where bit j of int_bits is 0 (continuous variable).  Bits are
+ * little-endian within each byte; each array holds ceil(n_inst / 8) bytes
+ * (host).  int_bits may be NULL (all integer).  Typically a = 0.9^K and
+ * kappa = sqrt(|I|) / ||c||_2. */
 int scylla_batch_set_blend(scylla_batch *h, int32_t inst, const uint8_t *xhat_bits,
                            const uint8_t *int_bits, double a, double kappa);
 
